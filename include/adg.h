@@ -127,10 +127,14 @@ typedef struct adg_options {
                                   straight into its slot, and the adjoint recomputes nothing) */
   int32_t kernel;              /* adg_kernel; AUTO -> FUSED */
   int32_t lane_elems;          /* fused kernel: consecutive elements per lane, 1, 2 or 4 (<= every
-                                  asynchronous problem's pe_size); 0 -> 2, or 1 for a PE size of 1 */
+                                  asynchronous problem's pe_size); 0 -> the library's choice (upwind
+                                  advection with speed > 0 and at least 1024 elements: by the total size;
+                                  2 otherwise, or 1 for a PE size of 1) */
   uint32_t flags;              /* ADG_OPT_* bits, 0 = defaults */
   uint32_t fused_steps;        /* fused kernel: time steps per launch, 1 or 2 (halo of 2S elements per side,
-                                  half the state traffic per step); 0 -> 2.  Every (lane_elems,
+                                  half the state traffic per step); 0 -> the library's choice: 2, or up to 8
+                                  where every problem is upwind advection with speed > 0 and at least
+                                  1024 elements (without a recording horizon).  Every (lane_elems,
                                   fused_steps) pair gives bitwise the same results. */
 } adg_options;
 

@@ -1,6 +1,7 @@
 """Autotuner for the fused step kernel's launch shape: elements per lane
-(1, 2 or 4), time steps per launch (1 or 2) and, where the PE sizes allow
-it, the PE-face split on or off.
+(1, 2 or 4) and, where the problems do not all run in the linear form, time
+steps per launch (1 or 2) and the PE-face split on or off where the PE sizes
+allow it.
 
 The best pair depends on the problem set: register pressure grows with the
 elements per lane (fewer resident waves), larger tiles cut the halo
@@ -73,9 +74,19 @@ def split_possible(workloads, k: int) -> bool:
     return min(w.pe_size for w in asyn) >= 4 * k * RK_STAGES[workloads[0].rk]
 
 
+def linear(workloads) -> bool:
+    """Every problem runs in the fused kernel's linear form (upwind advection,
+    a > 0, at least 1024 elements): it takes up to eight steps per launch, the
+    library's choice (fused_steps 0), and has no PE-face split."""
+    return all(w.equation == "advection" and w.flux == "upwind" and w.speed > 0 and w.n_elem >= 1024 for w in workloads)
+
+
 def configs(workloads) -> List[Tuple[int, int, Optional[bool]]]:
     """Candidate (R, K, split): split None where the PE-face split does not
-    apply (the library then has nothing to choose)."""
+    apply (the library then has nothing to choose), K 0 for the library's
+    choice of the steps per launch."""
+    if linear(workloads):
+        return [(r, 0, None) for r in admissible(workloads)]
     out = []
     for r in admissible(workloads):
         for k in STEPS_PER_LAUNCH:

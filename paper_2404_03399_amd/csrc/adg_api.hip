@@ -3,11 +3,15 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <mutex>
+#include <set>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "adg.h"
+#include "adg_device.hpp"
 #include "adg_launch.hpp"
 
 using namespace adg;
@@ -228,7 +232,107 @@ int validate(const adg_problem* probs, int32_t n) {
   return ADG_OK;
 }
 
+// The fused kernel's linear form: upwind advection with a > 0 on meshes of
+// kLinMinElems elements or more, whatever the PEs and delays (so that a problem
+// without delays and its synchronous twin agree bit for bit), no recording.
+// Recorded runs keep the stage form: dJ/da can be a sum that cancels down to
+// rounding (a misfit without a mode in common with the state), where its value
+// is that of the order of operations.
+constexpr int64_t kLinMinElems = 1024;
+bool lin_of(const adg_problem& p, int kernel, int64_t n_rec) {
+  return kernel == ADG_KERNEL_FUSED && phys_of(p) == PHYS_ADV_UPWIND && p.speed > 0.0 && n_rec == 0 &&
+         p.n_elem >= kLinMinElems;
+}
+
+// Butcher coefficients of the integrators in extended precision (a: strictly
+// lower triangular, b), the 2N schemes from their published A and B.
+void butcher(int rk, long double (&a)[kMaxStages][kMaxStages], long double (&b)[kMaxStages]) {
+  const int S = rk_stages(rk);
+  for (int i = 0; i < kMaxStages; ++i) {
+    b[i] = 0.0L;
+    for (int j = 0; j < kMaxStages; ++j) a[i][j] = 0.0L;
+  }
+  if (rk == RK_RK4) {
+    a[1][0] = a[2][1] = 0.5L;
+    a[3][2] = 1.0L;
+    b[0] = b[3] = 1.0L / 6.0L;
+    b[1] = b[2] = 1.0L / 3.0L;
+  } else if (rk == RK_SSP3) {
+    a[1][0] = 1.0L;
+    a[2][0] = a[2][1] = 0.25L;
+    b[0] = b[1] = 1.0L / 6.0L;
+    b[2] = 2.0L / 3.0L;
+  } else if (rk == RK_HEUN) {
+    a[1][0] = 1.0L;
+    b[0] = b[1] = 0.5L;
+  } else {
+    // y_{s+1} = u + dt sum_{j<=s} beta_sj k_j, beta_sj = sum_{l=j..s} B_l prod_{m=j+1..l} A_m
+    for (int s = 0; s < S; ++s)
+      for (int j = 0; j <= s; ++j) {
+        long double acc = 0.0L, prod = 1.0L;
+        for (int l = j; l <= s; ++l) {
+          if (l > j) prod *= (long double)ls_a(rk, l);
+          acc += (long double)ls_b(rk, l) * prod;
+        }
+        (s + 1 < S ? a[s + 1][j] : b[j]) = acc;
+      }
+  }
+}
+
+// Table of the linear form (layout in adg_common.hpp): the stages of one step as
+// linear maps of the element's nodes, of the fluxes F_j at its left face and
+// of the differences delta_j at its right face, in extended precision, from
+// the folded operators Kdu, Kl, Kr.
+void lin_table(const DevProblem& d, int rk, double* out) {
+  const int S = rk_stages(rk), np = d.np;
+  long double A[kMaxStages][kMaxStages], B[kMaxStages];
+  butcher(rk, A, B);
+  const long double dt = d.dt, a = d.speed;
+  // columns of a stage value y_s: np of u, then S of F, then S of delta
+  constexpr int kCols = kMaxNp + 2 * kMaxStages;
+  const int cols = np + 2 * S;
+  long double y[kMaxStages + 1][kMaxNp][kCols] = {}, k[kMaxStages][kMaxNp][kCols] = {};
+  for (int s = 0; s <= S; ++s) {
+    for (int i = 0; i < np; ++i) {
+      y[s][i][i] = 1.0L;
+      for (int j = 0; j < s; ++j)
+        for (int c = 0; c < cols; ++c) y[s][i][c] += (s < S ? A[s][j] : B[j]) * k[j][i][c];
+    }
+    if (s == S) break;
+    for (int i = 0; i < np; ++i) {
+      for (int j = 0; j < np; ++j)
+        for (int c = 0; c < cols; ++c) k[s][i][c] += dt * (long double)d.Kdu[i * kMaxNp + j] * y[s][j][c];
+      k[s][i][np + s] += dt * (long double)d.Kl[i];
+      k[s][i][np + S + s] -= dt * (long double)d.Kr[i];
+    }
+  }
+  for (int i = 0; i < lin_tab_size(np, S); ++i) out[i] = 0.0;
+  for (int c = 0; c < cols; ++c) {
+    const int kind = c < np ? LIN_U : (c < np + S ? LIN_F : LIN_D), j = c - (kind == LIN_U ? 0 : np + (kind - 1) * S);
+    double* o = out + lin_col(np, S, kind, j);
+    // G_s less G_0 = a u_p (it holds no F or delta), u' less u
+    for (int s = kind == LIN_U ? 1 : j + 1; s < S; ++s)
+      *o++ = (double)(a * (y[s][np - 1][c] - (c == np - 1 ? 1.0L : 0.0L)));
+    for (int i = 0; i < np; ++i) *o++ = (double)(y[S][i][c] - (c == i ? 1.0L : 0.0L));
+  }
+}
+
+// Problems with the same operators (one mesh, many delay realizations) share
+// a table: key of the values it is formed from.
+struct LinKey {
+  uint32_t degree;
+  double speed, dt, length;
+  int64_t n_elem;
+  bool operator<(const LinKey& o) const {
+    return std::tie(degree, speed, dt, length, n_elem) < std::tie(o.degree, o.speed, o.dt, o.length, o.n_elem);
+  }
+};
+LinKey lin_key(const adg_problem& p) { return LinKey{p.degree, p.speed, p.dt, p.length, p.n_elem}; }
+
 struct Layout {
+  int64_t lin, lin_doubles;  // tables of the linear form
+  int64_t lin_extra;         // bytes that it takes beyond the stage form's (tables, longer work lists)
+  int lin_elems, kmax;       // elements per lane of the linear form, steps per launch
   int64_t probs, work_f, work_f2, work_s, first_s, ctr, ring, atsum, atk, state2, y0, y1, acc, qbuf, part, stats_out;
   int64_t groups, gstats;  // ensemble statistics: group CSR (2n+1 int32) and 4 doubles per group
   // adjoint recording (-1 if not recording); ckrec holds the fused kernel's
@@ -249,8 +353,9 @@ struct Layout {
 // later still read levels down to n + 2 - L - q (the local DG kernel's halo
 // waves read the ring at their start); with L + q slots level n + 1 never
 // shares a slot with a level the launch reads.
-int64_t depth_of(const adg_problem& p, int64_t n_rec) {
-  return n_rec > 0 ? n_rec + p.n_delays + q_of(p) : (int64_t)p.n_delays + q_of(p);
+// The linear form takes up to kLinSteps steps per launch: so many less two slots more.
+int64_t depth_of(const adg_problem& p, int64_t n_rec, int kernel) {
+  return n_rec + p.n_delays + q_of(p) + (lin_of(p, kernel, n_rec) ? kLinSteps - 2 : 0);
 }
 
 // Elements per lane of the fused kernel (0 if the request is invalid).
@@ -310,33 +415,104 @@ bool adj_two_steps(const adg_problem* probs) { return probs[0].equation == ADG_E
 // reverse stages keep R sets of Butcher accumulators in registers)
 int adj_lane_elems(int lane_elems) { return lane_elems >= 2 ? 2 : 1; }
 
+// Smallest PE size among the asynchronous problems of the linear form.
+int64_t lin_min_pes(const adg_problem* probs, int32_t n, int kernel, int64_t n_rec) {
+  int64_t m = (int64_t)1 << 62;
+  for (int32_t i = 0; i < n; ++i)
+    if (async_of(probs[i]) && lin_of(probs[i], kernel, n_rec)) m = std::min(m, probs[i].pe_size);
+  return m;
+}
+
+int64_t total_elems(const adg_problem* probs, int32_t n) {
+  int64_t t = 0;
+  for (int32_t i = 0; i < n; ++i) t += probs[i].n_elem;
+  return t;
+}
+
+// Elements per lane of the linear form: the option's or the library's choice,
+// halved until it divides every PE size (a PE face is then always the left
+// face of a lane's first element).  us per step at eight steps per launch,
+// R = 1, 2 and 4: 2^14 elements 1.58, 1.68, 2.04, 2^16 1.82, 1.74, 2.08, 2^18
+// 3.13, 2.54, 2.68, 2^19 4.80, 3.54, 3.46, 2^20 7.55, 5.67, 5.19: few elements
+// per lane spread a small mesh over more waves, many make the halo small.
+int lin_elems_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
+  const int kern = kernel_of(probs, opt);
+  const int64_t elems = total_elems(probs, n);
+  int R = elems >= (int64_t)1 << 19 ? 4 : (elems >= (int64_t)1 << 16 ? 2 : 1);
+  if (opt && (opt->lane_elems != 0 || (opt->flags & ADG_OPT_ONE_LAUNCH)))
+    R = opt->flags & ADG_OPT_ONE_LAUNCH ? 2 : std::max(1, (int)opt->lane_elems);
+  for (int32_t i = 0; i < n; ++i)
+    if (lin_of(probs[i], kern, n_rec) && async_of(probs[i]))
+      while (probs[i].pe_size % R) R >>= 1;
+  return R;
+}
+
+// Steps per launch: the option's, or the library's choice.  In the linear form
+// eight (one element per lane on meshes of more than 2^18 elements: four, its
+// halo takes half the lanes), as long as a workgroup's PE-face records leave
+// room for three workgroups in the 160 KB of LDS.  us per step, 2^20 elements,
+// p = 3, RK4, PE 256: R = 4 10.1, 7.0 and 5.0 with two, four and eight steps,
+// R = 2 9.0, 6.3 and 5.5, R = 1 9.0, 6.9 and 7.6; 2^22, PE 4 (R = 4): 135 with
+// two steps (below 32 KB), 88 with four (below 48 KB).
+constexpr int kLinLdsBytes = 48 * 1024;
+int kmax_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
+  const int kern = kernel_of(probs, opt);
+  if (kern != ADG_KERNEL_FUSED) return 1;
+  const int req = opt ? (int)opt->fused_steps : 0;
+  if (req != 0 || (opt && (opt->flags & ADG_OPT_ONE_LAUNCH))) return req == 1 ? 1 : 2;
+  for (int32_t i = 0; i < n; ++i)
+    if (!lin_of(probs[i], kern, n_rec)) return 2;
+  const int64_t pes = lin_min_pes(probs, n, kern, n_rec);
+  const int R = lin_elems_of(probs, n, opt, n_rec);
+  const int S = rk_stages((int)probs[0].rk), nf = std::min(64, lin_faces(R, pes));
+  for (int K = R >= 2 || total_elems(probs, n) <= (int64_t)1 << 18 ? kLinSteps : 4; K > 2; K >>= 1)
+    if (8 * kWavesPerBlock * lin_lds_words(S, K, nf) <= kLinLdsBytes) return K;
+  return 2;
+}
+
+// Owned elements of a work item of problem p in the list for K steps.
+int tile_of(const adg_problem& p, bool lin, int R, int lin_R, int K) {
+  return lin ? lin_tile_elems(rk_stages((int)p.rk), lin_R, K, async_of(p))
+                           : fused_tile((int)p.rk, R, std::min(K, 2));
+}
+
 Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
   Layout L{};
   const int S = rk_stages((int)probs[0].rk);
   const int R = std::max(1, lane_elems_of(probs, n, opt));
-  const int T = fused_tile((int)probs[0].rk, R, 1);
-  const int T2 = fused_tile((int)probs[0].rk, R, 2);
+  const int kern = kernel_of(probs, opt);
+  L.lin_elems = lin_elems_of(probs, n, opt, n_rec);
+  L.kmax = kmax_of(probs, n, opt, n_rec);
+  // the second work list holds launches of two steps also where one is asked
+  // for, so that the recording of every state can take it
+  const int K2 = std::max(2, L.kmax);
+  std::set<LinKey> tables;
   const int T1 = adj_tile_elems((int)probs[0].rk, probs[0].equation == ADG_EQ_BURGERS);
   const int TA2 = adj_tile_elems2((int)probs[0].rk, adj_lane_elems(R));
-  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa = 0, nwa2 = 0, tot = 0, ring = 0, at = 0, nww[2] = {0, 0};
+  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa = 0, nwa2 = 0, tot = 0, ring = 0, at = 0, nww[2] = {0, 0}, nwx = 0;
   const bool split = pe_split_of(probs, n, opt);
   for (int32_t i = 0; i < n; ++i) {
     const adg_problem& p = probs[i];
+    const bool lin = lin_of(p, kern, n_rec);
+    const int T = tile_of(p, lin, R, L.lin_elems, 1), T2 = tile_of(p, lin, R, L.lin_elems, K2);
     nwf += (p.n_elem + T - 1) / T;
     nwf2 += (p.n_elem + T2 - 1) / T2;
+    if (lin && tables.insert(lin_key(p)).second) L.lin_doubles += lin_tab_size((int)p.degree + 1, S);
+    nwx += (p.n_elem + T - 1) / T + (p.n_elem + T2 - 1) / T2;
+    for (int K = 1; K <= 2; ++K) nwx -= (p.n_elem + fused_tile((int)p.rk, R, K) - 1) / fused_tile((int)p.rk, R, K);
     nwa += (p.n_elem + T1 - 1) / T1;
     nwa2 += (p.n_elem + TA2 - 1) / TA2;
     nws += (p.n_elem + kBlock - 1) / kBlock;
     tot += ld_of(p) * (p.degree + 1);
-    if (split && async_of(p))  // window items of the PE-face split, in the same lists
+    if (split && !lin && async_of(p))  // window items of the PE-face split, in the same lists
       for (int K = 1; K <= 2; ++K) {
         const int64_t fw = fused_windows_per_wave((int)p.rk, K);
         nww[K - 1] += (p.n_elem / p.pe_size + fw - 1) / fw;
       }
     if (async_of(p)) {
       // local DG keeps a second ring of the same shape for u-hat
-      ring += (is_ldg(probs) ? 2 : 1) * (p.n_elem / p.pe_size) * S * depth_of(p, n_rec);
-      at += kRecSlots * (p.n_elem / p.pe_size);
+      ring += (is_ldg(probs) ? 2 : 1) * (p.n_elem / p.pe_size) * S * depth_of(p, n_rec, kern);
+      if (!lin) at += kRecSlots * (p.n_elem / p.pe_size);
     }
   }
   L.at_entries = at;
@@ -347,10 +523,10 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   L.n_work_a2 = n_rec > 0 && adj_two_steps(probs) ? (int32_t)nwa2 : 0;
   L.total_doubles = tot;
   L.ring_doubles = ring;
-  const int kern = kernel_of(probs, opt);
   int64_t off = 0;
   auto take = [&](int64_t bytes) { const int64_t o = off; off = align_up(off + bytes, kAlign); return o; };
   L.probs = take((int64_t)sizeof(DevProblem) * n);
+  L.lin = take(8 * L.lin_doubles);
   L.work_f = take((int64_t)sizeof(WorkItem) * L.n_work_f);
   L.work_f2 = take((int64_t)sizeof(WorkItem) * L.n_work_f2);
   L.work_s = take((int64_t)sizeof(WorkItem) * nws);
@@ -396,6 +572,9 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
     }
   }
   L.total = off;
+  if (L.lin_doubles > 0)
+    L.lin_extra = align_up(8 * L.lin_doubles, kAlign) + (int64_t)sizeof(WorkItem) * std::max<int64_t>(nwx, 0) +
+                  (int64_t)sizeof(int64_t) * n + 3 * kAlign;
   return L;
 }
 
@@ -423,9 +602,12 @@ struct adg_ctx {
   const double* graph_u = nullptr;
   int graph_steps = 0;
 
-  int32_t group[2][kFusedRanges + 1] = {};  // fused work lists, 1 and 2 steps per launch
+  // fused work lists: one step per launch, and several (the list's halo holds
+  // kmax steps, or two)
+  int32_t group[2][kFusedRanges + 1] = {};
   int32_t grid[2][kFusedRanges] = {};
   int32_t single[2][kFusedRanges] = {};
+  LinRange lin_range[2][kFusedRanges] = {};
   int32_t one_launch = 0;  // ADG_OPT_ONE_LAUNCH
   int32_t mode[2][kFusedRanges] = {};       // fused_mode of each range of those lists
   bool split = false;                       // PE-face split in use
@@ -438,6 +620,7 @@ struct adg_ctx {
 
   StepArgs base_args(int64_t work_off, int32_t n_work, int K = 1) const {
     StepArgs a{};
+    const int list = K > 1 ? 1 : 0;  // work list
     a.probs = (const DevProblem*)(ws + L.probs);
     a.work = (const WorkItem*)(ws + work_off);
     a.n_work = n_work;
@@ -445,10 +628,15 @@ struct adg_ctx {
     a.ctr = (int64_t*)(ws + L.ctr);
     a.atsum = (double*)(ws + L.atsum);
     a.atk = (RecWord*)(ws + L.atk);
-    for (int i = 0; i <= kFusedRanges; ++i) a.group[i] = group[K - 1][i];
-    for (int i = 0; i < kFusedRanges; ++i) a.grid[i] = grid[K - 1][i];
-    for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[K - 1][i];
-    for (int i = 0; i < kFusedRanges; ++i) a.mode[i] = mode[K - 1][i];
+    for (int i = 0; i <= kFusedRanges; ++i) a.group[i] = group[list][i];
+    for (int i = 0; i < kFusedRanges; ++i) a.grid[i] = grid[list][i];
+    for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[list][i];
+    for (int i = 0; i < kFusedRanges; ++i) a.mode[i] = mode[list][i];
+    a.lin = (const double*)(ws + L.lin);
+    a.lin_elems = L.lin_elems;
+    a.lin_km = list == 0 ? 1 : std::max(2, L.kmax);
+    a.lin_halo = lin_halo(S, L.lin_elems, a.lin_km);
+    for (int i = 0; i < kFusedRanges; ++i) a.lin_range[i] = lin_range[list][i];
     a.lane_elems = lane_elems;
     a.one_launch = one_launch;
     a.steps = K;
@@ -456,7 +644,7 @@ struct adg_ctx {
     return a;
   }
   StepArgs fused_args(int K = 1) const {
-    return K == 2 ? base_args(L.work_f2, L.n_work_f2, 2) : base_args(L.work_f, L.n_work_f, 1);
+    return K > 1 ? base_args(L.work_f2, L.n_work_f2, K) : base_args(L.work_f, L.n_work_f, 1);
   }
   StepArgs stage_args() const { return base_args(L.work_s, L.n_work_s); }
 
@@ -471,7 +659,7 @@ struct adg_ctx {
   }
   // copy the fused kernel's PE-face records to / from checkpoint slot k
   int save_records(int64_t k, bool restore) {
-    if (L.ckrec < 0) return ADG_OK;
+    if (L.ckrec < 0 || L.at_entries == 0) return ADG_OK;
     char* rec = ws + L.ckrec + L.rec_bytes * k;
     char* sum = ws + L.atsum;
     char* kk = ws + L.atk;
@@ -487,8 +675,6 @@ struct adg_ctx {
 
 namespace {
 
-// Enqueue K steps (K = 2 only for the fused kernel); for the fused kernel the
-// result lands in *cur after a swap with the internal buffer.
 // K fused steps uin -> uout (with K = 2 also the state after the first step
 // into umid, if not null).
 int launch_fused(const adg_ctx* c, int K, const double* uin, double* uout, double* umid, int32_t step_offset,
@@ -499,6 +685,8 @@ int launch_fused(const adg_ctx* c, int K, const double* uin, double* uout, doubl
   return ADG_OK;
 }
 
+// Enqueue K steps (K > 1 only for the fused kernel); for the fused kernel the
+// result lands in *cur after a swap with the internal buffer.
 int enqueue_steps(adg_ctx* c, double** cur, double** other, int32_t step_offset, int K, hipStream_t st) {
   if (c->kernel == ADG_KERNEL_FUSED) {
     if (int rc = launch_fused(c, K, *cur, *other, nullptr, step_offset, st)) return rc;
@@ -520,11 +708,17 @@ int enqueue_steps(adg_ctx* c, double** cur, double** other, int32_t step_offset,
   return ADG_OK;
 }
 
-// Steps [0, m) of a batch: two per launch where the kernel allows.
+// Steps of the next launch with `left` steps to go.
+int next_steps(const adg_ctx* c, int64_t left) {
+  int K = c->L.kmax;
+  while (K > left) K >>= 1;
+  return K;
+}
+
+// Steps [0, m) of a batch: as many per launch as the kernel allows.
 int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, hipStream_t st) {
-  const int kmax = c->kernel == ADG_KERNEL_FUSED ? c->fused_steps : 1;
   for (int32_t i = 0; i < m;) {
-    const int K = (kmax == 2 && i + 1 < m) ? 2 : 1;
+    const int K = next_steps(c, m - i);
     const int rc = enqueue_steps(c, cur, other, i, K, st);
     if (rc) return rc;
     i += K;
@@ -586,8 +780,12 @@ int build_graph(adg_ctx* c, double* d_u) {
 // memory: one array per GPU the library runs on, held until the process ends.
 // Host code never uses this name as a device address (on the host it is a
 // stand-in); its per-device address comes from hipGetSymbolAddress.
+// What the linear form adds (mostly its tables, 1.4 KB at most for a problem
+// of 1024 elements or more) comes on top of the documented size, so that what
+// fits it does not depend on the form.
 constexpr int64_t kScratchBytes = ADG_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr int64_t kScratchExtra = 8ll << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchExtra];
 
 namespace {
 
@@ -715,6 +913,8 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   // descriptors
   c->dev.resize(n_probs);
   int64_t uoff = 0, roff = 0, aoff = 0;
+  std::vector<double> lin_tabs;
+  std::map<LinKey, int64_t> lin_at;
   for (int32_t i = 0; i < n_probs; ++i) {
     const adg_problem& p = probs[i];
     DevProblem& d = c->dev[i];
@@ -728,7 +928,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     d.np = (int)p.degree + 1;
     d.q = q_of(p);
     d.n_delays = (int)p.n_delays;
-    d.depth = (int32_t)depth_of(p, n_steps_record);
+    d.depth = (int32_t)depth_of(p, n_steps_record, c->kernel);
     d.per_stage = p.delay_granularity == ADG_DELAY_PER_STAGE;
     d.caa = p.delay_granularity == ADG_DELAY_CAA;
     d.scheme = (int)p.scheme;
@@ -748,10 +948,10 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
       const int64_t one_ring = d.n_pe * c->S * (int64_t)d.depth;
       d.ring2_off = roff + one_ring;
       roff += (is_ldg(probs) ? 2 : 1) * one_ring;
-      aoff += kRecSlots * d.n_pe;
+      if (!lin_of(p, c->kernel, n_steps_record)) aoff += kRecSlots * d.n_pe;
     }
-    d.seed = p.seed;
-    for (int k = 0; k + 1 < d.n_delays; ++k) d.thr[k] = p.delay_threshold[k];
+    d.seed_mix = splitmix64(p.seed);
+    for (int k = 0; k + 1 < kMaxL; ++k) d.thr[k] = k + 1 < d.n_delays ? p.delay_threshold[k] : ~0ull;
     const double dx = p.length / (double)p.n_elem;
     d.two_over_dx = 2.0 / dx;
     d.half_dx = 0.5 * dx;
@@ -774,10 +974,19 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
       for (int i = 0; i <= pn; ++i) d.Kdu[i * kMaxNp + pn] -= d.Kr[i] * p.speed;
     }
     d.depth_div = make_fast_div((uint32_t)d.depth);
+    d.lin_off = -1;
+    if (lin_of(p, c->kernel, n_steps_record)) {
+      const auto it = lin_at.emplace(lin_key(p), (int64_t)lin_tabs.size());
+      if (it.second) {
+        lin_tabs.resize(lin_tabs.size() + lin_tab_size(d.np, c->S));
+        lin_table(d, c->rk, lin_tabs.data() + it.first->second);
+      }
+      d.lin_off = it.first->second;
+    }
     for (int k = 0; k < d.n_delays; ++k)
       for (int j = 0; j < d.q; ++j) d.atc[k][j] = at_coefficient(d.q, k, j);
   }
-  if (roff != c->L.ring_doubles || aoff != c->L.at_entries) {
+  if (roff != c->L.ring_doubles || aoff != c->L.at_entries || (int64_t)lin_tabs.size() != c->L.lin_doubles) {
     delete c;
     return fail(ADG_E_INVALID, "internal: ring or record layout does not match the workspace layout");
   }
@@ -796,19 +1005,19 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   // PE-face paths compiled out
   c->split = pe_split_of(probs, n_probs, opt);
   c->one_launch = (opt && (opt->flags & ADG_OPT_ONE_LAUNCH)) ? 1 : 0;
-  for (int K = 1; K <= 2; ++K) {
-    const int T = fused_tile(c->rk, c->lane_elems, K);
+  for (int K = 1; K <= 2; ++K) {  // the lists of one and of several steps per launch
+    const int KL = K == 1 ? 1 : std::max(2, c->L.kmax);
     const int fw = fused_windows_per_wave(c->rk, K);
     std::vector<WorkItem>& wf = wfk[K - 1];
     wf.reserve(K == 1 ? c->L.n_work_f : c->L.n_work_f2);
     // ranges per degree, np = 5, 4, 3, 2 (order is sorted by degree,
     // descending), each split into the a > 0 upwind form and the rest
     for (int gi = 0; gi < kFusedRanges; ++gi) {
-      const int np = 5 - gi / 2;
-      const bool pos_range = (gi & 1) == 0;
+      const int np = 5 - gi / kForms, form = gi % kForms;
       auto in_range = [&](int32_t i) {
-        const bool pos = c->phys == PHYS_ADV_UPWIND && probs[i].speed > 0.0;
-        return (int)probs[i].degree + 1 == np && pos == pos_range;
+        const int f = lin_of(probs[i], c->kernel, n_steps_record) ? FORM_LIN
+                      : c->phys == PHYS_ADV_UPWIND && probs[i].speed > 0.0 ? FORM_POS : FORM_GEN;
+        return (int)probs[i].degree + 1 == np && f == form;
       };
       c->group[K - 1][gi] = (int32_t)wf.size();
       bool range_async = false;
@@ -816,8 +1025,15 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
         if (in_range(i) && async_of(probs[i])) range_async = true;
       for (int32_t i : order) {
         if (!in_range(i)) continue;
+        const bool lin = form == FORM_LIN;
+        const int T = tile_of(probs[i], lin, c->lane_elems, c->L.lin_elems, KL);
         const int64_t nt = (probs[i].n_elem + T - 1) / T;
-        const bool win = c->split && async_of(probs[i]);
+        const bool win = c->split && !lin && async_of(probs[i]);
+        if (lin && async_of(probs[i])) {
+          LinRange& lr = c->lin_range[K - 1][gi];
+          lr.n_faces = std::max(lr.n_faces, std::min(64, lin_faces(c->L.lin_elems, probs[i].pe_size)));
+          lr.lds_words = lin_lds_words(c->S, KL, lr.n_faces);
+        }
         const int64_t ng = win ? (probs[i].n_elem / probs[i].pe_size + fw - 1) / fw : 0;
         const int64_t gstride = (int64_t)fw * probs[i].pe_size;  // elements between window groups
         // merge by first element: window group g at g * fw * pe_size, tile t at t * T
@@ -831,7 +1047,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
           }
         }
       }
-      c->mode[K - 1][gi] = !range_async ? FUSED_NOPE : (c->split ? FUSED_SPLIT : FUSED_FULL);
+      c->mode[K - 1][gi] = form == FORM_LIN || !range_async ? FUSED_NOPE : (c->split ? FUSED_SPLIT : FUSED_FULL);
     }
     c->group[K - 1][kFusedRanges] = (int32_t)wf.size();
     if ((int64_t)wf.size() != (K == 1 ? c->L.n_work_f : c->L.n_work_f2)) {
@@ -882,6 +1098,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     return ADG_OK;
   };
   if ((rc = up(c->L.probs, c->dev.data(), (int64_t)sizeof(DevProblem) * n_probs)) ||
+      (c->L.lin_doubles > 0 && (rc = up(c->L.lin, lin_tabs.data(), 8 * c->L.lin_doubles))) ||
       (rc = up(c->L.work_f, wfk[0].data(), (int64_t)sizeof(WorkItem) * wfk[0].size())) ||
       (rc = up(c->L.work_f2, wfk[1].data(), (int64_t)sizeof(WorkItem) * wfk[1].size())) ||
       (rc = up(c->L.work_s, ws_.data(), (int64_t)sizeof(WorkItem) * ws_.size())) ||
@@ -910,7 +1127,8 @@ int adg_init_scratch(adg_ctx** out, const adg_problem* probs, int32_t n_probs, c
   int64_t need = 0;
   int rc = adg_workspace_size(probs, n_probs, opt, 0, &need);
   if (rc) return rc;
-  if (need > kScratchBytes)
+  const int64_t extra = make_layout(probs, n_probs, opt, 0).lin_extra;
+  if (need - extra > kScratchBytes || extra > kScratchExtra)
     return fail(ADG_E_WORKSPACE, "adg_init_scratch: these problems need " + std::to_string(need) +
                                      " bytes of workspace; the static scratch array holds " +
                                      std::to_string(kScratchBytes));

@@ -78,8 +78,8 @@ struct DevProblem {
   int32_t async_faces;   // 1 if PE faces use delayed data (scheme != DG and P > 1)
   int32_t caa;           // delays follow the communication-avoiding cycle
   FastDiv pe_div;        // division by pe_size
-  uint64_t seed;
-  uint64_t thr[kMaxL - 1];
+  uint64_t seed_mix;     // first link of the delay hash, mix(seed)
+  uint64_t thr[kMaxL - 1];  // thresholds; unused ones 2^64 - 1, above every 53-bit uniform
   double two_over_dx;
   double speed;
   double dt;
@@ -100,8 +100,38 @@ struct DevProblem {
   // Kdu[i][p] = Kd[i][p] - Kr[i] a, so Kd y - Kr (a y_p) = Kdu y.
   double Kdu[kMaxNp * kMaxNp];
   FastDiv depth_div;     // division by the ring depth (step indices < 2^31)
+  int64_t lin_off;       // offset of the problem's LinTab in the table region (doubles), -1: none
   double atc[kMaxL][kMaxQ];    // c_j(k), j < q, k < L
 };
+
+// Coefficients of one RK step of an element with np nodes and S stages, for
+// upwind advection with a > 0 in flux-sequence form.  With M = dt Kdu,
+// y_s = u + sum_{j<s} a_sj k_j, k_j = M y_j + dt Kl F_j - dt Kr delta_j (F_j
+// the flux applied at the left face, delta_j the applied minus the raw flux at
+// the right face, 0 at an interior face):
+//   G_s = a y_s(last node) = G_0 + Z_s u + sum_{j<s} (W_sj F_j + WR_sj delta_j),  G_0 = a u_p,
+//   u'  = u + A u + sum_s (Phi_s F_s + Psi_s delta_s).
+// The table holds columns, the coefficients that one input multiplies:
+//   node j:   Z_1j .. Z_{S-1,j}, A_0j .. A_pj
+//   F_s:      W_{s+1,s} .. W_{S-1,s}, Phi_0s .. Phi_ps
+//   delta_s:  WR, Psi in the same order
+// A kernel lane holds the entries (lane mod 16) of a run of 16, so a column
+// never crosses a multiple of 16: lin_col gives each column's first entry.
+enum LinCol : int { LIN_U = 0, LIN_F = 1, LIN_D = 2 };
+constexpr int lin_col_len(int np, int S, int kind, int j) { return kind == LIN_U ? S - 1 + np : S - 1 - j + np; }
+constexpr int lin_col(int np, int S, int kind, int j) {
+  int at = 0;
+  for (int k = 0; k <= LIN_D; ++k)
+    for (int i = 0; i < (k == LIN_U ? np : S); ++i) {
+      const int n = lin_col_len(np, S, k, i);
+      if (at / 16 != (at + n - 1) / 16) at = (at + 15) / 16 * 16;
+      if (k == kind && i == j) return at;
+      at += n;
+    }
+  return at;
+}
+// doubles of a table: whole runs of 16
+constexpr int lin_tab_size(int np, int S) { return (lin_col(np, S, LIN_D, S) + 15) / 16 * 16; }
 
 struct WorkItem {
   int32_t prob;
@@ -120,10 +150,9 @@ __host__ __device__ inline uint64_t splitmix64(uint64_t x) {
 // The delay hash chains SplitMix64 over (seed, step, stage key, boundary):
 // h = mix(mix(mix(mix(seed) ^ step) ^ key) ^ boundary).  The first three
 // links do not depend on the boundary.
-__host__ __device__ inline uint64_t delay_prefix(uint64_t seed, int64_t step, int32_t key) {
-  uint64_t h = splitmix64(seed);
-  h = splitmix64(h ^ (uint64_t)step);
-  return splitmix64(h ^ (uint64_t)(int64_t)key);
+// delay_prefix starts from the first link, mix(seed).
+__host__ __device__ inline uint64_t delay_prefix(uint64_t seed_mix, int64_t step, int32_t key) {
+  return splitmix64(splitmix64(seed_mix ^ (uint64_t)step) ^ (uint64_t)(int64_t)key);
 }
 
 // Delay before clamping: number of thresholds at or below the 53-bit
@@ -138,7 +167,7 @@ __host__ __device__ inline int delay_from_prefix(uint64_t prefix, int64_t bounda
 
 __host__ __device__ inline int draw_delay(uint64_t seed, int64_t step, int32_t key, int64_t boundary,
                                           const uint64_t* thr, int n_delays) {
-  return delay_from_prefix(delay_prefix(seed, step, key), boundary, thr, n_delays);
+  return delay_from_prefix(delay_prefix(splitmix64(seed), step, key), boundary, thr, n_delays);
 }
 
 // Communication-avoiding schedule (Sec. 7): of every five steps the first two

@@ -65,16 +65,16 @@ __device__ __forceinline__ int ring_slot(int slot_n, int back, int depth) {
 }
 
 // Clamped delay of boundary b at (step n, stage s): the hash of
-// draw_delay with the threshold count unrolled over kMaxL - 1 (the threshold
-// loads issue together instead of one per loop trip).
+// draw_delay with the threshold count unrolled over kMaxL - 1 (unused
+// thresholds lie above every uniform).
 __device__ __forceinline__ int pe_delay(const DevProblem& P, int64_t n, int s, uint32_t b) {
   int k = 0;
   if (P.caa) {
     k = caa_delay(n);
   } else {
-    const uint64_t u = splitmix64(delay_prefix(P.seed, n, P.per_stage ? s : 0) ^ (uint64_t)b) >> 11;
+    const uint64_t u = splitmix64(delay_prefix(P.seed_mix, n, P.per_stage ? s : 0) ^ (uint64_t)b) >> 11;
 #pragma unroll
-    for (int i = 0; i < kMaxL - 1; ++i) k += (i < P.n_delays - 1 && u >= P.thr[i]) ? 1 : 0;
+    for (int i = 0; i < kMaxL - 1; ++i) k += u >= P.thr[i] ? 1 : 0;
   }
   return clamp_delay(k, n, P.q);
 }

@@ -1,7 +1,7 @@
 // Fused step kernel: one wave64 per tile, all RK stages of one or two time
 // steps on chip.  Compiled once per integrator (-DADG_RK=0 .. 4) so that the
 // instantiations build in parallel.
-#include "adg_device.hpp"
+#include "adg_linear.hpp"
 
 #ifndef ADG_RK
 #error "compile once per integrator with -DADG_RK=0, 1, 2, 3 or 4"
@@ -404,16 +404,21 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(const DevProblem* __restr
 struct FusedRangeTable {
   int32_t group[kFusedRanges + 1];
 };
+struct LinTable {  // the linear form's tables and geometry over every range
+  const double* tab;
+  int32_t elems, halo, n_faces, lds_words;
+};
 
 template <int RK, int PHYS, int R, int K>
 __global__ __launch_bounds__(kBlock) void k_fused_all(const DevProblem* __restrict__ probs,
                                                       const WorkItem* __restrict__ work,
                                                       const int64_t* __restrict__ ctr, double* __restrict__ ring,
                                                       double* __restrict__ atsum, RecWord* __restrict__ atk,
-                                                      const FusedRangeTable rt, const double* __restrict__ uin,
-                                                      double* __restrict__ uout, double* __restrict__ umid,
-                                                      int32_t step_offset) {
+                                                      const FusedRangeTable rt, const LinTable lt,
+                                                      const double* __restrict__ uin, double* __restrict__ uout,
+                                                      double* __restrict__ umid, int32_t step_offset) {
   __shared__ WaveSmemK<K, rk_stages(RK)> sm;
+  extern __shared__ double lin_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int lane = (int)(threadIdx.x % kWave);
   const int w = xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
@@ -425,18 +430,37 @@ __global__ __launch_bounds__(kBlock) void k_fused_all(const DevProblem* __restri
   int gi = 0;  // uniform
 #pragma unroll
   for (int g = 1; g < kFusedRanges; ++g) gi += w >= rt.group[g] ? 1 : 0;
-  // even ranges hold the a > 0 upwind form, which exists for upwind advection only
-  constexpr bool kPos = PHYS == PHYS_ADV_UPWIND;
-  constexpr int PH0 = kPos ? PHYS_ADV_UPWIND_POS : PHYS;
-  if (kPos && (gi & 1) == 0) {
-    switch (gi) {
+  // the linear form and the a > 0 upwind form exist for upwind advection only
+  constexpr bool kUp = PHYS == PHYS_ADV_UPWIND;
+  constexpr int PH0 = kUp ? PHYS_ADV_UPWIND_POS : PHYS;
+  const int form = gi % kForms, ni = gi / kForms;
+  if (kUp && form == FORM_LIN) {
+    constexpr int S = rk_stages(RK);
+    auto go = [&](auto np, auto r) {
+      lin_tile<decltype(np)::value, S, decltype(r)::value>(P, lt.tab + P.lin_off, wi, ring, n, K, lt.halo, uin, uout,
+                                                           lt.n_faces, lin_lds + wv * lt.lds_words, lane);
+    };
+    auto go_np = [&](auto r) {
+      switch (ni) {
+        case 0: go(std::integral_constant<int, 5>{}, r); break;
+        case 1: go(std::integral_constant<int, 4>{}, r); break;
+        case 2: go(std::integral_constant<int, 3>{}, r); break;
+        default: go(std::integral_constant<int, 2>{}, r); break;
+      }
+    };
+    if (lt.elems == R)
+      go_np(std::integral_constant<int, R>{});
+    else  // an odd PE size
+      go_np(std::integral_constant<int, 1>{});
+  } else if (kUp && form == FORM_POS) {
+    switch (ni) {
       case 0: wave_tile<5, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
-      case 2: wave_tile<4, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
-      case 4: wave_tile<3, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
+      case 1: wave_tile<4, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
+      case 2: wave_tile<3, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
       default: wave_tile<2, RK, PH0, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
     }
   } else {
-    switch (gi / 2) {
+    switch (ni) {
       case 0: wave_tile<5, RK, PHYS, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
       case 1: wave_tile<4, RK, PHYS, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
       case 2: wave_tile<3, RK, PHYS, R, K, TILE_FULL>(P, wi, A, n, uin, uout, umid, sm, wv, lane); break;
@@ -730,7 +754,7 @@ template <int RK>
 static void fused_ldg_np(const StepArgs& a, const double* uin, double* uout, int32_t off, hipStream_t st) {
   for (int gi = 0; gi < kFusedRanges; ++gi) {
     if (a.group[gi + 1] <= a.group[gi]) continue;
-    switch (gi / 2) {  // np = 5, 4, 3, 2
+    switch (gi / kForms) {  // np = 5, 4, 3, 2
       case 0: fused_ldg_go<5, RK>(a, gi, uin, uout, off, st); break;
       case 1: fused_ldg_go<4, RK>(a, gi, uin, uout, off, st); break;
       case 2: fused_ldg_go<3, RK>(a, gi, uin, uout, off, st); break;
@@ -771,7 +795,11 @@ static void fused_go(const StepArgs& a, int gi, const double* uin, double* uout,
 template <int NP, int RK, int PHYS>
 static void fused_form(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   if constexpr (PHYS == PHYS_ADV_UPWIND) {
-    if ((gi & 1) == 0) {  // the problems with a > 0
+    if (gi % kForms == FORM_LIN) {
+      launch_lin_s<rk_stages(RK)>(a, gi, uin, uout, off, st);
+      return;
+    }
+    if (gi % kForms == FORM_POS) {
       fused_go<NP, RK, PHYS_ADV_UPWIND_POS>(a, gi, uin, uout, off, st);
       return;
     }
@@ -783,7 +811,7 @@ template <int RK, int PHYS>
 static void fused_np(const StepArgs& a, const double* uin, double* uout, int32_t off, hipStream_t st) {
   for (int gi = 0; gi < kFusedRanges; ++gi) {
     if (a.group[gi + 1] <= a.group[gi]) continue;
-    switch (gi / 2) {  // np = 5, 4, 3, 2
+    switch (gi / kForms) {  // np = 5, 4, 3, 2
       case 0: fused_form<5, RK, PHYS>(a, gi, uin, uout, off, st); break;
       case 1: fused_form<4, RK, PHYS>(a, gi, uin, uout, off, st); break;
       case 2: fused_form<3, RK, PHYS>(a, gi, uin, uout, off, st); break;
@@ -807,13 +835,19 @@ template <int RK, int PHYS>
 static void fused_all_go(const StepArgs& a, const double* uin, double* uout, int32_t off, hipStream_t st) {
   FusedRangeTable rt;
   for (int i = 0; i <= kFusedRanges; ++i) rt.group[i] = a.group[i];
+  LinTable lt{a.lin, a.lin_elems, a.lin_halo, 0, 0};
+  for (int i = FORM_LIN; i < kFusedRanges; i += kForms) {
+    lt.n_faces = a.lin_range[i].n_faces > lt.n_faces ? a.lin_range[i].n_faces : lt.n_faces;
+    lt.lds_words = a.lin_range[i].lds_words > lt.lds_words ? a.lin_range[i].lds_words : lt.lds_words;
+  }
+  const size_t lds = 8 * (size_t)(kWavesPerBlock * lt.lds_words);
   const dim3 g(fused_grid(a.group[kFusedRanges])), b(kBlock);
   if (a.steps == 2)
-    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2, 2>), g, b, 0, st, a.probs, a.work, a.ctr, a.ring, a.atsum, a.atk, rt,
-                       uin, uout, a.umid, off);
+    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2, 2>), g, b, lds, st, a.probs, a.work, a.ctr, a.ring, a.atsum, a.atk,
+                       rt, lt, uin, uout, a.umid, off);
   else
-    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2, 1>), g, b, 0, st, a.probs, a.work, a.ctr, a.ring, a.atsum, a.atk, rt,
-                       uin, uout, nullptr, off);
+    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2, 1>), g, b, lds, st, a.probs, a.work, a.ctr, a.ring, a.atsum, a.atk,
+                       rt, lt, uin, uout, nullptr, off);
 }
 
 template <int RK>

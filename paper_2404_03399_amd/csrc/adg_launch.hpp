@@ -5,6 +5,22 @@
 
 namespace adg {
 
+// Work items of the fused kernel are sorted by descending np and, within a
+// degree, by form: range g = kForms (5 - np) + v, [group[g], group[g + 1]),
+// holds the items of degree np - 1 in form v: upwind advection with a > 0 in
+// the linear form (adg_linear.hpp, tiles of its own) or stage by stage with
+// the interior right-face flux folded into the volume operator, and the
+// general form of the context's equation.  Each problem therefore runs the
+// same kernel in a batch as in a context of its own.
+enum FusedForm : int { FORM_LIN = 0, FORM_POS = 1, FORM_GEN = 2 };
+constexpr int kForms = 3;
+constexpr int kFusedRanges = 4 * kForms;
+
+struct LinRange {
+  int32_t n_faces;     // most PE faces that a wave of the range holds
+  int32_t lds_words;   // doubles of LDS per wave
+};
+
 struct StepArgs {
   const DevProblem* probs;   // device descriptors
   const WorkItem* work;      // device work list, one item per workgroup
@@ -13,28 +29,25 @@ struct StepArgs {
   int64_t* ctr;              // ctr[0] = steps completed by earlier batches, ctr[2] = non-finite flag
   double* atsum;             // fused kernel: AT sums of past levels, [kRecSlots][P][S] per problem
   RecWord* atk;              // fused kernel: clamped delays, [kRecSlots][P] words per problem (byte s = stage s)
-  int32_t group[9];          // fused kernel: work-item ranges per degree and form (below)
-  int32_t grid[8];           // fused kernel: workgroups per range
-  int32_t single[8];         // fused kernel: the only problem of a range, or -1
+  int32_t group[kFusedRanges + 1];          // fused kernel: work-item ranges per degree and form (below)
+  int32_t grid[kFusedRanges];           // fused kernel: workgroups per range
+  int32_t single[kFusedRanges];         // fused kernel: the only problem of a range, or -1
   int32_t lane_elems;        // fused kernel: elements per lane (1, 2 or 4)
-  int32_t steps;             // fused kernel: time steps per launch (1 or 2)
+  int32_t steps;             // fused kernel: time steps per launch (1 or 2; up to kLinSteps in the linear form)
   double* qbuf;              // local DG: q = u_x of the current stage input (state layout)
   double* umid;              // fused kernel, two steps per launch: also write the state after
                              // the first step here (state layout), or null
-  int32_t mode[8];           // fused kernel: fused_mode of each range (FUSED_SPLIT ranges mark
+  const double* lin;         // linear form: tables of the problems
+  int32_t lin_elems;         // linear form: elements per lane (1, 2 or 4)
+  int32_t lin_km;            // linear form: steps per launch that the work list's halo holds
+  int32_t lin_halo;          // linear form: halo lanes on the left
+  LinRange lin_range[kFusedRanges];     // linear form, per range
+  int32_t mode[kFusedRanges];           // fused kernel: fused_mode of each range (FUSED_SPLIT ranges mark
                              // their window items by tile index -(window group + 1))
   int32_t one_launch;        // fused kernel: one launch over every range (two elements per lane,
                              // every range FUSED_FULL), else one launch per range
 };
 
-// Work items of the fused kernel are sorted by descending np and, within a
-// degree, by form: range g = 2 (5 - np) + v, [group[g], group[g + 1]), holds
-// the items of degree np - 1 that take the a > 0 upwind form (v = 0: upwind
-// advection with a positive speed, whose interior right-face flux is folded
-// into the volume operator) or the general form of the context's equation
-// (v = 1).  Each problem therefore runs the same kernel in a batch as in a
-// context of its own.
-constexpr int kFusedRanges = 8;
 
 // Fused step kernel geometry: one wave64 per work item, R in {1, 2, 4}
 // consecutive elements per lane, K in {1, 2} time steps per launch, halo of
@@ -55,6 +68,26 @@ __host__ __device__ constexpr int fused_tile(int rk, int R, int K) { return R * 
 enum fused_mode { FUSED_FULL = 0, FUSED_NOPE = 1, FUSED_SPLIT = 2 };
 __host__ __device__ constexpr int fused_window(int rk, int K) { return 4 * K * rk_stages(rk); }
 __host__ __device__ constexpr int fused_windows_per_wave(int rk, int K) { return kWave / fused_window(rk, K); }
+
+// Linear form: halo lanes on the left for K steps, one lane more on the right
+// where a problem has PE faces (the element right of the last owned one, whose
+// left face may be one); owned elements per work item.
+__host__ __device__ constexpr int lin_halo(int S, int R, int K) { return (K * S + R - 1) / R; }
+__host__ __device__ constexpr int lin_tile_elems(int S, int R, int K, bool async) {
+  return R * (kWave - lin_halo(S, R, K) - (async ? 1 : 0));
+}
+// PE faces of a wave's 64 R elements at most (R <= PE size, so one per lane)
+__host__ __device__ constexpr int lin_faces(int R, int64_t pe_size) {
+  return (int)((kWave * R - 1) / pe_size) + 1;
+}
+// LDS of a wave in doubles (layout in adg_linear.hpp)
+__host__ __device__ constexpr int lin_lds_words(int S, int K, int n_faces) {
+  return n_faces > 0 ? kMaxL * kMaxQ + S + n_faces * (K * S + K + 1) : 0;
+}
+constexpr int kLinSteps = 8;  // most steps per launch
+// One range of the linear form (compiled per stage count).
+template <int S>
+void launch_lin_s(const StepArgs& a, int gi, const double* uin, double* uout, int32_t step_offset, hipStream_t stream);
 
 // Workgroups of the fused kernel for n_work items (kWavesPerBlock per group).
 inline int fused_grid(int n_work) { return n_work < 1 ? 1 : (n_work + kWavesPerBlock - 1) / kWavesPerBlock; }
