@@ -127,38 +127,32 @@ typedef struct adg_options {
                                   straight into its slot, and the adjoint recomputes nothing) */
   int32_t kernel;              /* adg_kernel; AUTO -> FUSED */
   int32_t lane_elems;          /* fused kernel: consecutive elements per lane, 1, 2 or 4 (<= every
-                                  asynchronous problem's pe_size); 0 -> the library's choice (upwind
-                                  advection with speed > 0 and at least 1024 elements: by the total size;
-                                  2 otherwise, or 1 for a PE size of 1) */
+                                  asynchronous problem's pe_size); 0 -> the library's choice (by the
+                                  form and the total size; viscous Burgers: 2, or 1 for a PE size of 1).
+                                  Where it does not divide every PE size, half of it, until it does */
   uint32_t flags;              /* ADG_OPT_* bits, 0 = defaults */
   uint32_t fused_steps;        /* fused kernel: time steps per launch, 1 or 2 (halo of 2S elements per side,
-                                  half the state traffic per step); 0 -> the library's choice: 2, or up to 8
-                                  where every problem is upwind advection with speed > 0 and at least
-                                  1024 elements (without a recording horizon).  Every (lane_elems,
-                                  fused_steps) pair gives bitwise the same results. */
+                                  half the state traffic per step); 0 -> the library's choice, up to 8 by
+                                  the sizes (viscous Burgers: 2).  Every (lane_elems, fused_steps) pair gives
+                                  bitwise the same results. */
 } adg_options;
 
-/* adg_options.flags.  Fused kernel, PE-face split (only PE faces see
- * delayed data, Secs. 3, 5): within one launch, tile waves without any
- * PE-face handling advance every tile, and window waves recompute windows of
- * 4 K S elements around each PE face (K steps per launch, S stages), owning
- * the 2 K S elements that the face's delayed flux can reach, which the tile
- * waves leave alone; the result is bitwise that of the unsplit kernel.  By default the split is
- * used when a wave holds at least two windows of the longest launch and
- * every asynchronous problem's PE size holds four (RK4 with two steps per
- * launch: PE size >= 128); ADG_OPT_PE_SPLIT_OFF never splits,
- * ADG_OPT_PE_SPLIT_ON splits whenever the PE sizes hold one window.  Bits
- * other than those defined here: ADG_E_INVALID. */
+/* adg_options.flags.  ADG_OPT_PE_SPLIT_ON / OFF chose between two forms of the
+ * fused kernel with bitwise the same results; it has one form now, which keeps
+ * waves with and without PE faces apart by itself, and the bits only decide
+ * whether the workspace holds room for the window lists of the split form (by
+ * default where every asynchronous problem's PE size holds four windows of 4 K S
+ * elements, K steps per launch, S stages).  Both together, and bits other than
+ * those defined here: ADG_E_INVALID. */
 #define ADG_OPT_PE_SPLIT_OFF 1u
 #define ADG_OPT_PE_SPLIT_ON 2u
 /* ADG_OPT_ONE_LAUNCH: the fused kernel advances every problem of a batch in
  * one launch per step batch instead of one launch per degree range (Sec. 4.3
- * ensembles mix degrees): each wave takes its range's tile with the PE-face
- * paths compiled in, so every range runs at the register footprint of the
- * degree-4 tile; the results are bitwise those of the per-range launches.
- * Needs the fused kernel with lane_elems 0 or 2 and no PE-face split
- * (together with ADG_OPT_PE_SPLIT_ON: ADG_E_INVALID); viscous Burgers:
- * ADG_E_UNSUPPORTED. */
+ * ensembles mix degrees): each wave takes its range's tile, so every range runs
+ * at the register footprint of the degree-4 tile; the results are bitwise those
+ * of the per-range launches.  Two steps per launch at most.  Needs the fused
+ * kernel with lane_elems 0 or 2 and no ADG_OPT_PE_SPLIT_ON (together:
+ * ADG_E_INVALID); viscous Burgers: ADG_E_UNSUPPORTED. */
 #define ADG_OPT_ONE_LAUNCH 4u
 
 typedef struct adg_ctx adg_ctx;  /* opaque, host side, library owned */
@@ -229,7 +223,10 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
  * the same device takes it over, after which every call on the earlier
  * context except adg_step_count and adg_destroy returns ADG_E_STATE; calls
  * that overlap in time on one GPU (several threads or streams) race on the
- * array.  The step counter, rings and records are cleared as by adg_init.
+ * array.  The step counter and rings are cleared as by adg_init.
+ * Where the library's choice of steps per launch (fused_steps 0) does not fit,
+ * two steps per launch are taken; the operator tables of upwind advection
+ * (1.4 KB at most per problem) come on top of the array's size.
  * adg_run with ADG_RUN_GRAPH creates a capture stream and a graph; run
  * without that flag when nothing may be created. */
 #define ADG_SCRATCH_BYTES (64ll << 20)

@@ -74,19 +74,9 @@ def split_possible(workloads, k: int) -> bool:
     return min(w.pe_size for w in asyn) >= 4 * k * RK_STAGES[workloads[0].rk]
 
 
-def linear(workloads) -> bool:
-    """Every problem runs in the fused kernel's linear form (upwind advection,
-    a > 0, at least 1024 elements): it takes up to eight steps per launch, the
-    library's choice (fused_steps 0), and has no PE-face split."""
-    return all(w.equation == "advection" and w.flux == "upwind" and w.speed > 0 and w.n_elem >= 1024 for w in workloads)
-
-
 def configs(workloads) -> List[Tuple[int, int, Optional[bool]]]:
     """Candidate (R, K, split): split None where the PE-face split does not
-    apply (the library then has nothing to choose), K 0 for the library's
-    choice of the steps per launch."""
-    if linear(workloads):
-        return [(r, 0, None) for r in admissible(workloads)]
+    apply (the library then has nothing to choose)."""
     out = []
     for r in admissible(workloads):
         for k in STEPS_PER_LAUNCH:
@@ -97,10 +87,23 @@ def configs(workloads) -> List[Tuple[int, int, Optional[bool]]]:
     return out
 
 
+def linear(workloads) -> bool:
+    """Every problem runs in the fused kernel's linear form (upwind advection,
+    a > 0, at least 1024 elements): it takes up to eight steps per launch, more
+    than can be asked for, and has no PE-face split."""
+    return all(w.equation == "advection" and w.flux == "upwind" and w.speed > 0 and w.n_elem >= 1024 for w in workloads)
+
+
+def timed_configs(workloads) -> List[Tuple[int, int, Optional[bool]]]:
+    """The candidates that `tune` times: in the linear form the elements per
+    lane at the library's own steps per launch (K = 0), else `configs`."""
+    return [(r, 0, None) for r in admissible(workloads)] if linear(workloads) else configs(workloads)
+
+
 def tune(workloads, steps: int = 32, use_cache: bool = True, verbose: bool = False,
          reps: int = 3) -> Tuple[int, int, Optional[bool]]:
-    """(elements per lane, steps per launch, PE-face split) with the shortest
-    time per step: for each candidate the step graph is captured first
+    """(elements per lane, steps per launch (0: the library's choice), PE-face
+    split) with the shortest time per step: for each candidate the step graph is captured first
     (outside the timing), then `reps` runs of `steps` graph-replayed steps are
     timed with HIP events and the median is kept."""
     import torch
@@ -124,7 +127,7 @@ def tune(workloads, steps: int = 32, use_cache: bool = True, verbose: bool = Fal
     steps = max(16, steps - steps % 16)  # whole graph replays only
     timings = {}
     u_init = None  # the state layout does not depend on the launch shape
-    for r, k, split in configs(workloads):
+    for r, k, split in timed_configs(workloads):
         s = Solver(workloads, lane_elems=r, fused_steps=k, pe_split=split)
         if u_init is None:
             u_init = s.initial_state()

@@ -235,9 +235,12 @@ int validate(const adg_problem* probs, int32_t n) {
 // The fused kernel's linear form: upwind advection with a > 0 on meshes of
 // kLinMinElems elements or more, whatever the PEs and delays (so that a problem
 // without delays and its synchronous twin agree bit for bit), no recording.
-// Recorded runs keep the stage form: dJ/da can be a sum that cancels down to
-// rounding (a misfit without a mode in common with the state), where its value
-// is that of the order of operations.
+// Below that a launch is latency and the forms are equal: 64 elements, p = 2,
+// RK4, 255 steps 375 us against 397 stage by stage, 160 problems of 512
+// elements, p = 1, Heun, 200 steps 360 against 324.  Recorded runs keep the
+// stage form: dJ/da can be a sum that cancels down to rounding (a misfit
+// without a mode in common with the state), where its value is that of the
+// order of operations.
 constexpr int64_t kLinMinElems = 1024;
 bool lin_of(const adg_problem& p, int kernel, int64_t n_rec) {
   return kernel == ADG_KERNEL_FUSED && phys_of(p) == PHYS_ADV_UPWIND && p.speed > 0.0 && n_rec == 0 &&
@@ -329,33 +332,33 @@ struct LinKey {
 };
 LinKey lin_key(const adg_problem& p) { return LinKey{p.degree, p.speed, p.dt, p.length, p.n_elem}; }
 
+// Launch shape of the fused kernel: elements per lane and most steps per launch.
+struct Shape {
+  int elems, kmax;
+};
+
 struct Layout {
+  Shape shape;               // launch shape of the fused kernel
+  int depth_steps;           // steps per launch that the ring holds
   int64_t lin, lin_doubles;  // tables of the linear form
-  int64_t lin_extra;         // bytes that it takes beyond the stage form's (tables, longer work lists)
-  int lin_elems, kmax;       // elements per lane of the linear form, steps per launch
-  int64_t probs, work_f, work_f2, work_s, first_s, ctr, ring, atsum, atk, state2, y0, y1, acc, qbuf, part, stats_out;
+  int64_t probs, work_f, work_f2, work_s, first_s, ctr, ring, state2, y0, y1, acc, qbuf, part, stats_out;
   int64_t groups, gstats;  // ensemble statistics: group CSR (2n+1 int32) and 4 doubles per group
-  // adjoint recording (-1 if not recording); ckrec holds the fused kernel's
-  // PE-face records (AT sums, delays) at every checkpoint plus one spare slot
-  int64_t ckpt, useg, ybuf, lam, q, adjring, cpart, ckrec, work_a, work_a2;
+  // adjoint recording (-1 if not recording)
+  int64_t ckpt, useg, ybuf, lam, q, adjring, cpart, work_a, work_a2;
   int64_t total;
   int32_t n_work_f, n_work_f2, n_work_s, n_work_a, n_work_a2;
-  int64_t rec_atsum_bytes, rec_atk_bytes, rec_bytes;
   int64_t total_doubles;
   int64_t ring_doubles;
-  int64_t at_entries;  // boundaries x kRecSlots (x S for the sums)
   int64_t n_rec, ckpt_every, n_ckpt;
 };
 
-// Ring slots per (boundary, stage): the AT window L + q - 1 plus one, or,
-// when an adjoint recording horizon is given, the whole run (every level is
-// kept).  A two-step launch writes levels n and n + 1 while waves that start
-// later still read levels down to n + 2 - L - q (the local DG kernel's halo
-// waves read the ring at their start); with L + q slots level n + 1 never
-// shares a slot with a level the launch reads.
-// The linear form takes up to kLinSteps steps per launch: so many less two slots more.
-int64_t depth_of(const adg_problem& p, int64_t n_rec, int kernel) {
-  return n_rec + p.n_delays + q_of(p) + (lin_of(p, kernel, n_rec) ? kLinSteps - 2 : 0);
+// Ring slots per (boundary, stage): when an adjoint recording horizon is given
+// the whole run (every level is kept), and L + q + kmax - 2 more: a launch of K
+// steps writes levels n .. n + K - 1 while waves that start later still read
+// levels down to n + 2 - L - q; with that many slots no level written in a
+// launch shares a slot with one that it reads.
+int64_t depth_of(const adg_problem& p, int64_t n_rec, int kmax) {
+  return n_rec + p.n_delays + q_of(p) + std::max(kmax, 2) - 2;
 }
 
 // Elements per lane of the fused kernel (0 if the request is invalid).
@@ -415,65 +418,84 @@ bool adj_two_steps(const adg_problem* probs) { return probs[0].equation == ADG_E
 // reverse stages keep R sets of Butcher accumulators in registers)
 int adj_lane_elems(int lane_elems) { return lane_elems >= 2 ? 2 : 1; }
 
-// Smallest PE size among the asynchronous problems of the linear form.
-int64_t lin_min_pes(const adg_problem* probs, int32_t n, int kernel, int64_t n_rec) {
-  int64_t m = (int64_t)1 << 62;
-  for (int32_t i = 0; i < n; ++i)
-    if (async_of(probs[i]) && lin_of(probs[i], kernel, n_rec)) m = std::min(m, probs[i].pe_size);
-  return m;
-}
-
 int64_t total_elems(const adg_problem* probs, int32_t n) {
   int64_t t = 0;
   for (int32_t i = 0; i < n; ++i) t += probs[i].n_elem;
   return t;
 }
 
-// Elements per lane of the linear form: the option's or the library's choice,
-// halved until it divides every PE size (a PE face is then always the left
-// face of a lane's first element).  us per step at eight steps per launch,
-// R = 1, 2 and 4: 2^14 elements 1.58, 1.68, 2.04, 2^16 1.82, 1.74, 2.08, 2^18
-// 3.13, 2.54, 2.68, 2^19 4.80, 3.54, 3.46, 2^20 7.55, 5.67, 5.19: few elements
-// per lane spread a small mesh over more waves, many make the halo small.
-int lin_elems_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
+int form_of(const adg_problem& p, int kernel, int64_t n_rec) {
+  return lin_of(p, kernel, n_rec) ? FORM_LIN : phys_of(p) == PHYS_ADV_UPWIND && p.speed > 0.0 ? FORM_POS : FORM_GEN;
+}
+
+// Owned elements of a work item of the list for K steps.
+int tile_of(const adg_problem& p, int form, const Shape& s, int K) {
+  if (form == FORM_GEN) return fused_tile((int)p.rk, s.elems, K);
+  return fused_tile_left((int)p.rk, s.elems, K, async_of(p));
+}
+
+// Doubles of LDS per wave for problem p in launches of K steps.
+int lds_of(const adg_problem& p, int elems, int K) {
+  return async_of(p) ? fused_lds_words(rk_stages((int)p.rk), K, fused_faces(elems, p.pe_size)) : 0;
+}
+
+// Elements per lane R: the option's or the library's choice, halved until it
+// divides every PE size (a PE face is then always the left face of a lane's
+// first element).  Few elements per lane spread a small mesh over more waves,
+// many make the halo small.  Steps per launch K: the option's, or the library's
+// choice: the most, eight, as long as the halo leaves enough of the lanes (on
+// small meshes, where a launch is latency, few are enough) and a workgroup's
+// PE-face records leave room for three workgroups in the 160 KB of LDS.
+// Measured, us per step, PE 256, p = 3, RK4 unless stated (R and K in brackets):
+//   linear form   2^14 elements (1,8) 1.58, (2,8) 1.68, (4,8) 2.04; 2^16 1.82,
+//                 1.74, 2.08; 2^18 3.13, 2.54, 2.68; 2^19 4.80, 3.54, 3.46; 2^20
+//                 7.55, 5.67, 5.19; (1,4) 3.32 at 2^18, 6.99 at 2^20; (4,2) 10.1,
+//                 (4,4) 7.0 at 2^20; 2^22, PE 4 (4,2) 135 (below 32 KB of LDS),
+//                 (4,4) 88 (below 48 KB)
+//   a > 0, stage  64 elements, p = 2 (1,8) 1.57, (2,8) 2.19, (4,8) 3.45; recorded
+//                 2^20 (128 steps and their adjoint, ms) (2,4) 6.32, (2,8) 6.18,
+//                 (4,4) 6.30, (4,8) 5.95
+//   general, central flux   2^12 (1,4) 2.25, (2,8) 2.30, (4,8) 2.77; 2^16 2.74,
+//                 2.76, 2.93; 2^18 5.01, 4.25, 4.12; 2^22 (2,4) 31.8, (4,4) 29.3,
+//                 (4,8) 31.0; five stages (lsrk4, p = 2) 2^22 (4,4) 27.0, (4,8)
+//                 30.6; 10^5, p = 4, lsrk4, PE 30 (2,2) 4.2, (2,4) 4.5, (2,8) 5.4
+//   general, Burgers, SSP-RK3, p = 2   2^22 (2,4) 26.2, (4,4) 24.0, (4,8) 23.7
+constexpr int kFaceLdsBytes = 48 * 1024;
+Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
   const int kern = kernel_of(probs, opt);
+  Shape s{std::max(1, lane_elems_of(probs, n, opt)), kern == ADG_KERNEL_FUSED ? std::max(1, fused_steps_of(opt)) : 1};
+  if (kern != ADG_KERNEL_FUSED || is_ldg(probs)) return s;
   const int64_t elems = total_elems(probs, n);
-  int R = elems >= (int64_t)1 << 19 ? 4 : (elems >= (int64_t)1 << 16 ? 2 : 1);
-  if (opt && (opt->lane_elems != 0 || (opt->flags & ADG_OPT_ONE_LAUNCH)))
-    R = opt->flags & ADG_OPT_ONE_LAUNCH ? 2 : std::max(1, (int)opt->lane_elems);
+  const bool one_launch = opt && (opt->flags & ADG_OPT_ONE_LAUNCH);
+  bool all_lin = true, gen = false;
+  for (int32_t i = 0; i < n; ++i) {
+    const int f = form_of(probs[i], kern, n_rec);
+    all_lin = all_lin && f == FORM_LIN;
+    gen = gen || f == FORM_GEN;
+  }
+  if (one_launch)
+    s.elems = 2;
+  else if (!opt || opt->lane_elems == 0) {
+    const int64_t two = all_lin ? (int64_t)1 << 16 : (gen ? 0 : (int64_t)1 << 17);
+    const int64_t four = all_lin ? (int64_t)1 << 19 : (int64_t)1 << 18;
+    s.elems = elems >= four ? 4 : (elems >= two ? 2 : 1);
+  }
   for (int32_t i = 0; i < n; ++i)
-    if (lin_of(probs[i], kern, n_rec) && async_of(probs[i]))
-      while (probs[i].pe_size % R) R >>= 1;
-  return R;
-}
-
-// Steps per launch: the option's, or the library's choice.  In the linear form
-// eight (one element per lane on meshes of more than 2^18 elements: four, its
-// halo takes half the lanes), as long as a workgroup's PE-face records leave
-// room for three workgroups in the 160 KB of LDS.  us per step, 2^20 elements,
-// p = 3, RK4, PE 256: R = 4 10.1, 7.0 and 5.0 with two, four and eight steps,
-// R = 2 9.0, 6.3 and 5.5, R = 1 9.0, 6.9 and 7.6; 2^22, PE 4 (R = 4): 135 with
-// two steps (below 32 KB), 88 with four (below 48 KB).
-constexpr int kLinLdsBytes = 48 * 1024;
-int kmax_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
-  const int kern = kernel_of(probs, opt);
-  if (kern != ADG_KERNEL_FUSED) return 1;
-  const int req = opt ? (int)opt->fused_steps : 0;
-  if (req != 0 || (opt && (opt->flags & ADG_OPT_ONE_LAUNCH))) return req == 1 ? 1 : 2;
-  for (int32_t i = 0; i < n; ++i)
-    if (!lin_of(probs[i], kern, n_rec)) return 2;
-  const int64_t pes = lin_min_pes(probs, n, kern, n_rec);
-  const int R = lin_elems_of(probs, n, opt, n_rec);
-  const int S = rk_stages((int)probs[0].rk), nf = std::min(64, lin_faces(R, pes));
-  for (int K = R >= 2 || total_elems(probs, n) <= (int64_t)1 << 18 ? kLinSteps : 4; K > 2; K >>= 1)
-    if (8 * kWavesPerBlock * lin_lds_words(S, K, nf) <= kLinLdsBytes) return K;
-  return 2;
-}
-
-// Owned elements of a work item of problem p in the list for K steps.
-int tile_of(const adg_problem& p, bool lin, int R, int lin_R, int K) {
-  return lin ? lin_tile_elems(rk_stages((int)p.rk), lin_R, K, async_of(p))
-                           : fused_tile((int)p.rk, R, std::min(K, 2));
+    if (async_of(probs[i]))
+      while (probs[i].pe_size % s.elems) s.elems >>= 1;
+  if ((opt && opt->fused_steps != 0) || one_launch) return s;
+  const int most_halo = gen ? (elems <= (int64_t)1 << 16 ? 21 : 8)
+                        : all_lin ? (elems <= (int64_t)1 << 18 ? 40 : 20) : (elems <= (int64_t)1 << 17 ? 40 : 16);
+  auto fits = [&](int K) {
+    if (fused_halo((int)probs[0].rk, s.elems, K) > most_halo) return false;
+    for (int32_t i = 0; i < n; ++i)
+      if (8 * kWavesPerBlock * lds_of(probs[i], s.elems, K) > kFaceLdsBytes) return false;
+    return true;
+  };
+  int K = kMaxSteps;
+  while (K > 2 && !fits(K)) K >>= 1;
+  s.kmax = K;
+  return s;
 }
 
 Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
@@ -481,43 +503,49 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   const int S = rk_stages((int)probs[0].rk);
   const int R = std::max(1, lane_elems_of(probs, n, opt));
   const int kern = kernel_of(probs, opt);
-  L.lin_elems = lin_elems_of(probs, n, opt, n_rec);
-  L.kmax = kmax_of(probs, n, opt, n_rec);
-  // the second work list holds launches of two steps also where one is asked
-  // for, so that the recording of every state can take it
-  const int K2 = std::max(2, L.kmax);
+  L.shape = shape_of(probs, n, opt, n_rec);
+  // the list of several steps also where the option asks for one: the
+  // recording of every state can take it
+  const int K2 = std::max(2, L.shape.kmax);
+  // room as without ADG_OPT_ONE_LAUNCH (whose own shape may be another), so
+  // that the workspace does not depend on it
+  adg_options plain = opt ? *opt : adg_options{};
+  plain.flags &= ~ADG_OPT_ONE_LAUNCH;
+  const Shape rs = shape_of(probs, n, &plain, n_rec);
+  const int RK2 = std::max(2, rs.kmax);
+  L.depth_steps = std::max(K2, RK2);
   std::set<LinKey> tables;
   const int T1 = adj_tile_elems((int)probs[0].rk, probs[0].equation == ADG_EQ_BURGERS);
   const int TA2 = adj_tile_elems2((int)probs[0].rk, adj_lane_elems(R));
-  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa = 0, nwa2 = 0, tot = 0, ring = 0, at = 0, nww[2] = {0, 0}, nwx = 0;
+  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa = 0, nwa2 = 0, tot = 0, ring = 0, room1 = 0, room2 = 0,
+          win[2] = {0, 0};
   const bool split = pe_split_of(probs, n, opt);
   for (int32_t i = 0; i < n; ++i) {
     const adg_problem& p = probs[i];
-    const bool lin = lin_of(p, kern, n_rec);
-    const int T = tile_of(p, lin, R, L.lin_elems, 1), T2 = tile_of(p, lin, R, L.lin_elems, K2);
-    nwf += (p.n_elem + T - 1) / T;
-    nwf2 += (p.n_elem + T2 - 1) / T2;
-    if (lin && tables.insert(lin_key(p)).second) L.lin_doubles += lin_tab_size((int)p.degree + 1, S);
-    nwx += (p.n_elem + T - 1) / T + (p.n_elem + T2 - 1) / T2;
-    for (int K = 1; K <= 2; ++K) nwx -= (p.n_elem + fused_tile((int)p.rk, R, K) - 1) / fused_tile((int)p.rk, R, K);
+    const int form = form_of(p, kern, n_rec);
+    auto tiles = [&](int T) { return (p.n_elem + T - 1) / T; };
+    const int64_t t1 = tiles(tile_of(p, form, L.shape, 1)), t2 = tiles(tile_of(p, form, L.shape, K2));
+    nwf += t1;
+    nwf2 += t2;
+    room1 += std::max(t1, tiles(tile_of(p, form, rs, 1)));
+    room2 += std::max(t2, tiles(tile_of(p, form, rs, RK2)));
+    if (form == FORM_LIN && tables.insert(lin_key(p)).second) L.lin_doubles += lin_tab_size((int)p.degree + 1, S);
     nwa += (p.n_elem + T1 - 1) / T1;
     nwa2 += (p.n_elem + TA2 - 1) / TA2;
     nws += (p.n_elem + kBlock - 1) / kBlock;
     tot += ld_of(p) * (p.degree + 1);
-    if (split && !lin && async_of(p))  // window items of the PE-face split, in the same lists
+    if (split && async_of(p))  // room for the window items of a PE-face split
       for (int K = 1; K <= 2; ++K) {
         const int64_t fw = fused_windows_per_wave((int)p.rk, K);
-        nww[K - 1] += (p.n_elem / p.pe_size + fw - 1) / fw;
+        win[K - 1] += (p.n_elem / p.pe_size + fw - 1) / fw;
       }
     if (async_of(p)) {
       // local DG keeps a second ring of the same shape for u-hat
-      ring += (is_ldg(probs) ? 2 : 1) * (p.n_elem / p.pe_size) * S * depth_of(p, n_rec, kern);
-      if (!lin) at += kRecSlots * (p.n_elem / p.pe_size);
+      ring += (is_ldg(probs) ? 2 : 1) * (p.n_elem / p.pe_size) * S * depth_of(p, n_rec, L.depth_steps);
     }
   }
-  L.at_entries = at;
-  L.n_work_f = (int32_t)(nwf + nww[0]);
-  L.n_work_f2 = (int32_t)(nwf2 + nww[1]);
+  L.n_work_f = (int32_t)nwf;
+  L.n_work_f2 = (int32_t)nwf2;
   L.n_work_s = (int32_t)nws;
   L.n_work_a = n_rec > 0 ? (int32_t)nwa : 0;
   L.n_work_a2 = n_rec > 0 && adj_two_steps(probs) ? (int32_t)nwa2 : 0;
@@ -527,14 +555,12 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   auto take = [&](int64_t bytes) { const int64_t o = off; off = align_up(off + bytes, kAlign); return o; };
   L.probs = take((int64_t)sizeof(DevProblem) * n);
   L.lin = take(8 * L.lin_doubles);
-  L.work_f = take((int64_t)sizeof(WorkItem) * L.n_work_f);
-  L.work_f2 = take((int64_t)sizeof(WorkItem) * L.n_work_f2);
+  L.work_f = take((int64_t)sizeof(WorkItem) * (room1 + win[0]));
+  L.work_f2 = take((int64_t)sizeof(WorkItem) * (room2 + win[1]));
   L.work_s = take((int64_t)sizeof(WorkItem) * nws);
   L.first_s = take((int64_t)sizeof(int32_t) * (n + 1));
   L.ctr = take(8 * sizeof(int64_t));
   L.ring = take(8 * std::max<int64_t>(ring, 1));
-  L.atsum = take(8 * S * std::max<int64_t>(at, 1));
-  L.atk = take((int64_t)sizeof(RecWord) * std::max<int64_t>(at, 1));
   const bool rec = n_rec > 0;
   L.state2 = kern == ADG_KERNEL_FUSED ? take(8 * tot) : -1;
   L.y0 = kern == ADG_KERNEL_STAGE ? take(8 * tot) : -1;
@@ -548,10 +574,7 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   L.n_rec = n_rec;
   L.ckpt_every = (opt && opt->ckpt_every > 0) ? opt->ckpt_every : 64;
   L.n_ckpt = rec ? (n_rec + L.ckpt_every - 1) / L.ckpt_every : 0;
-  L.ckpt = L.useg = L.ybuf = L.lam = L.q = L.adjring = L.cpart = L.ckrec = L.work_a = L.work_a2 = -1;
-  L.rec_atsum_bytes = 8 * S * std::max<int64_t>(at, 1);
-  L.rec_atk_bytes = (int64_t)sizeof(RecWord) * std::max<int64_t>(at, 1);
-  L.rec_bytes = align_up(L.rec_atsum_bytes, kAlign) + align_up(L.rec_atk_bytes, kAlign);
+  L.ckpt = L.useg = L.ybuf = L.lam = L.q = L.adjring = L.cpart = L.work_a = L.work_a2 = -1;
   if (rec) {
     // stage kernels recompute a segment into seg slots; the fused adjoint
     // reads the segment's first state from its checkpoint and needs seg - 1
@@ -565,16 +588,12 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
       L.q = take(8 * tot * (S - 1));
       L.cpart = take(8 * nws);
     } else {
-      L.ckrec = take(L.rec_bytes * (L.n_ckpt + 1));
       L.work_a = take((int64_t)sizeof(WorkItem) * nwa);
       if (L.n_work_a2 > 0) L.work_a2 = take((int64_t)sizeof(WorkItem) * nwa2);
       L.cpart = take(8 * nwa);
     }
   }
   L.total = off;
-  if (L.lin_doubles > 0)
-    L.lin_extra = align_up(8 * L.lin_doubles, kAlign) + (int64_t)sizeof(WorkItem) * std::max<int64_t>(nwx, 0) +
-                  (int64_t)sizeof(int64_t) * n + 3 * kAlign;
   return L;
 }
 
@@ -607,17 +626,15 @@ struct adg_ctx {
   int32_t group[2][kFusedRanges + 1] = {};
   int32_t grid[2][kFusedRanges] = {};
   int32_t single[2][kFusedRanges] = {};
-  LinRange lin_range[2][kFusedRanges] = {};
+  FaceRange faces[2][kFusedRanges] = {};
   int32_t one_launch = 0;  // ADG_OPT_ONE_LAUNCH
-  int32_t mode[2][kFusedRanges] = {};       // fused_mode of each range of those lists
-  bool split = false;                       // PE-face split in use
-  int32_t lane_elems = 2;
-  int32_t fused_steps = 2;
+  int32_t lane_elems = 2, fused_steps = 2;  // of the two-step reverse
   // fused adjoint work list (recording contexts of the fused kernel)
   std::vector<WorkItem> work_a, work_a2;
   int32_t group_a[5] = {0, 0, 0, 0, 0}, group_a2[5] = {0, 0, 0, 0, 0};
   int32_t grid_a[4] = {1, 1, 1, 1}, grid_a2[4] = {1, 1, 1, 1};
 
+  int list_steps(int list) const { return list == 0 ? 1 : std::max(2, L.shape.kmax); }
   StepArgs base_args(int64_t work_off, int32_t n_work, int K = 1) const {
     StepArgs a{};
     const int list = K > 1 ? 1 : 0;  // work list
@@ -626,20 +643,15 @@ struct adg_ctx {
     a.n_work = n_work;
     a.ring = (double*)(ws + L.ring);
     a.ctr = (int64_t*)(ws + L.ctr);
-    a.atsum = (double*)(ws + L.atsum);
-    a.atk = (RecWord*)(ws + L.atk);
     for (int i = 0; i <= kFusedRanges; ++i) a.group[i] = group[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.grid[i] = grid[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[list][i];
-    for (int i = 0; i < kFusedRanges; ++i) a.mode[i] = mode[list][i];
+    for (int i = 0; i < kFusedRanges; ++i) a.faces[i] = faces[list][i];
     a.lin = (const double*)(ws + L.lin);
-    a.lin_elems = L.lin_elems;
-    a.lin_km = list == 0 ? 1 : std::max(2, L.kmax);
-    a.lin_halo = lin_halo(S, L.lin_elems, a.lin_km);
-    for (int i = 0; i < kFusedRanges; ++i) a.lin_range[i] = lin_range[list][i];
-    a.lane_elems = lane_elems;
-    a.one_launch = one_launch;
+    a.elems = L.shape.elems;
     a.steps = K;
+    a.halo = fused_halo(rk, L.shape.elems, list_steps(list));
+    a.one_launch = one_launch;
     a.qbuf = L.qbuf >= 0 ? (double*)(ws + L.qbuf) : nullptr;
     return a;
   }
@@ -657,30 +669,18 @@ struct adg_ctx {
     a.lane_elems = K == 2 ? adj_lane_elems(lane_elems) : 1;
     return a;
   }
-  // copy the fused kernel's PE-face records to / from checkpoint slot k
-  int save_records(int64_t k, bool restore) {
-    if (L.ckrec < 0 || L.at_entries == 0) return ADG_OK;
-    char* rec = ws + L.ckrec + L.rec_bytes * k;
-    char* sum = ws + L.atsum;
-    char* kk = ws + L.atk;
-    char* rk_ = rec + align_up(L.rec_atsum_bytes, kAlign);
-    ADG_HIP(hipMemcpyAsync(restore ? sum : rec, restore ? rec : sum, L.rec_atsum_bytes, hipMemcpyDeviceToDevice,
-                           stream));
-    ADG_HIP(hipMemcpyAsync(restore ? kk : rk_, restore ? rk_ : kk, L.rec_atk_bytes, hipMemcpyDeviceToDevice, stream));
-    return ADG_OK;
-  }
-
   double* state2() const { return (double*)(ws + L.state2); }
 };
 
 namespace {
 
-// K fused steps uin -> uout (with K = 2 also the state after the first step
-// into umid, if not null).
+// K fused steps uin -> uout (with K > 1 also the states after the steps before
+// the last into umid, umid + total_doubles, ..., if not null).
 int launch_fused(const adg_ctx* c, int K, const double* uin, double* uout, double* umid, int32_t step_offset,
                  hipStream_t st) {
   StepArgs a = c->fused_args(K);
   a.umid = umid;
+  a.mid_stride = c->L.total_doubles;
   ADG_HIP(launch_fused_step(c->rk, c->fused_phys, a, uin, uout, step_offset, st));
   return ADG_OK;
 }
@@ -710,7 +710,7 @@ int enqueue_steps(adg_ctx* c, double** cur, double** other, int32_t step_offset,
 
 // Steps of the next launch with `left` steps to go.
 int next_steps(const adg_ctx* c, int64_t left) {
-  int K = c->L.kmax;
+  int K = c->L.shape.kmax;
   while (K > left) K >>= 1;
   return K;
 }
@@ -729,8 +729,6 @@ int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, hipStream
 int reset_device(adg_ctx* c) {
   ADG_HIP(launch_zero(c->ws + c->L.ctr, 8 * sizeof(int64_t), c->stream));
   ADG_HIP(launch_zero(c->ws + c->L.ring, 8 * std::max<int64_t>(c->L.ring_doubles, 1), c->stream));
-  ADG_HIP(launch_zero(c->ws + c->L.atsum, 8 * c->S * std::max<int64_t>(c->L.at_entries, 1), c->stream));
-  ADG_HIP(launch_zero(c->ws + c->L.atk, sizeof(RecWord) * std::max<int64_t>(c->L.at_entries, 1), c->stream));
   c->steps = 0;
   c->rec_steps = 0;
   return ADG_OK;
@@ -780,12 +778,11 @@ int build_graph(adg_ctx* c, double* d_u) {
 // memory: one array per GPU the library runs on, held until the process ends.
 // Host code never uses this name as a device address (on the host it is a
 // stand-in); its per-device address comes from hipGetSymbolAddress.
-// What the linear form adds (mostly its tables, 1.4 KB at most for a problem
-// of 1024 elements or more) comes on top of the documented size, so that what
-// fits it does not depend on the form.
+// The linear form's tables (1.4 KB at most for a problem of 1024 elements or
+// more) come on top of the documented size.
 constexpr int64_t kScratchBytes = ADG_SCRATCH_BYTES;
-constexpr int64_t kScratchExtra = 8ll << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchExtra];
+constexpr int64_t kScratchTables = 8ll << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchTables];
 
 namespace {
 
@@ -912,7 +909,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
 
   // descriptors
   c->dev.resize(n_probs);
-  int64_t uoff = 0, roff = 0, aoff = 0;
+  int64_t uoff = 0, roff = 0;
   std::vector<double> lin_tabs;
   std::map<LinKey, int64_t> lin_at;
   for (int32_t i = 0; i < n_probs; ++i) {
@@ -928,7 +925,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     d.np = (int)p.degree + 1;
     d.q = q_of(p);
     d.n_delays = (int)p.n_delays;
-    d.depth = (int32_t)depth_of(p, n_steps_record, c->kernel);
+    d.depth = (int32_t)depth_of(p, n_steps_record, c->L.depth_steps);
     d.per_stage = p.delay_granularity == ADG_DELAY_PER_STAGE;
     d.caa = p.delay_granularity == ADG_DELAY_CAA;
     d.scheme = (int)p.scheme;
@@ -942,13 +939,10 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
       }
     }
     d.ring_off = roff;
-    d.at_off = aoff * c->S;
-    d.atk_off = aoff;
     if (d.async_faces) {
       const int64_t one_ring = d.n_pe * c->S * (int64_t)d.depth;
       d.ring2_off = roff + one_ring;
       roff += (is_ldg(probs) ? 2 : 1) * one_ring;
-      if (!lin_of(p, c->kernel, n_steps_record)) aoff += kRecSlots * d.n_pe;
     }
     d.seed_mix = splitmix64(p.seed);
     for (int k = 0; k + 1 < kMaxL; ++k) d.thr[k] = k + 1 < d.n_delays ? p.delay_threshold[k] : ~0ull;
@@ -986,9 +980,9 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     for (int k = 0; k < d.n_delays; ++k)
       for (int j = 0; j < d.q; ++j) d.atc[k][j] = at_coefficient(d.q, k, j);
   }
-  if (roff != c->L.ring_doubles || aoff != c->L.at_entries || (int64_t)lin_tabs.size() != c->L.lin_doubles) {
+  if (roff != c->L.ring_doubles || (int64_t)lin_tabs.size() != c->L.lin_doubles) {
     delete c;
-    return fail(ADG_E_INVALID, "internal: ring or record layout does not match the workspace layout");
+    return fail(ADG_E_INVALID, "internal: ring or table layout does not match the workspace layout");
   }
   // work lists: heaviest (highest degree) problems first
   std::vector<int32_t> order(n_probs);
@@ -998,70 +992,38 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   c->fused_steps = fused_steps_of(opt);
   std::vector<WorkItem> wfk[2], ws_;
   std::vector<int32_t> first(n_probs + 1, 0);
-  // PE-face split: in each range the window items of its asynchronous
-  // problems (fused_windows_per_wave faces per item, tile index -(group + 1))
-  // are interleaved with the tiles of every problem in order of their first
-  // element; ranges without asynchronous problems take the kernel with the
-  // PE-face paths compiled out
-  c->split = pe_split_of(probs, n_probs, opt);
   c->one_launch = (opt && (opt->flags & ADG_OPT_ONE_LAUNCH)) ? 1 : 0;
-  for (int K = 1; K <= 2; ++K) {  // the lists of one and of several steps per launch
-    const int KL = K == 1 ? 1 : std::max(2, c->L.kmax);
-    const int fw = fused_windows_per_wave(c->rk, K);
-    std::vector<WorkItem>& wf = wfk[K - 1];
-    wf.reserve(K == 1 ? c->L.n_work_f : c->L.n_work_f2);
+  for (int list = 0; list < 2; ++list) {  // one and several steps per launch
+    const int K = c->list_steps(list);
+    std::vector<WorkItem>& wf = wfk[list];
+    wf.reserve(list == 0 ? c->L.n_work_f : c->L.n_work_f2);
     // ranges per degree, np = 5, 4, 3, 2 (order is sorted by degree,
-    // descending), each split into the a > 0 upwind form and the rest
+    // descending), each split by form
     for (int gi = 0; gi < kFusedRanges; ++gi) {
       const int np = 5 - gi / kForms, form = gi % kForms;
-      auto in_range = [&](int32_t i) {
-        const int f = lin_of(probs[i], c->kernel, n_steps_record) ? FORM_LIN
-                      : c->phys == PHYS_ADV_UPWIND && probs[i].speed > 0.0 ? FORM_POS : FORM_GEN;
-        return (int)probs[i].degree + 1 == np && f == form;
-      };
-      c->group[K - 1][gi] = (int32_t)wf.size();
-      bool range_async = false;
-      for (int32_t i : order)
-        if (in_range(i) && async_of(probs[i])) range_async = true;
+      const int32_t b = c->group[list][gi] = (int32_t)wf.size();
+      FaceRange& fr = c->faces[list][gi];
+      int n_in = 0;
       for (int32_t i : order) {
-        if (!in_range(i)) continue;
-        const bool lin = form == FORM_LIN;
-        const int T = tile_of(probs[i], lin, c->lane_elems, c->L.lin_elems, KL);
-        const int64_t nt = (probs[i].n_elem + T - 1) / T;
-        const bool win = c->split && !lin && async_of(probs[i]);
-        if (lin && async_of(probs[i])) {
-          LinRange& lr = c->lin_range[K - 1][gi];
-          lr.n_faces = std::max(lr.n_faces, std::min(64, lin_faces(c->L.lin_elems, probs[i].pe_size)));
-          lr.lds_words = lin_lds_words(c->S, KL, lr.n_faces);
-        }
-        const int64_t ng = win ? (probs[i].n_elem / probs[i].pe_size + fw - 1) / fw : 0;
-        const int64_t gstride = (int64_t)fw * probs[i].pe_size;  // elements between window groups
-        // merge by first element: window group g at g * fw * pe_size, tile t at t * T
-        for (int64_t t = 0, g = 0; t < nt || g < ng;) {
-          if (g < ng && (t >= nt || g * gstride <= t * T)) {
-            wf.push_back(WorkItem{i, (int32_t)(-g - 1)});
-            ++g;
-          } else {
-            wf.push_back(WorkItem{i, (int32_t)t});
-            ++t;
-          }
+        const adg_problem& p = probs[i];
+        if ((int)p.degree + 1 != np || form_of(p, c->kernel, n_steps_record) != form) continue;
+        ++n_in;
+        const int T = tile_of(p, form, c->L.shape, K);
+        for (int64_t t = 0; t < (p.n_elem + T - 1) / T; ++t) wf.push_back(WorkItem{i, (int32_t)t});
+        if (async_of(p) && c->kernel == ADG_KERNEL_FUSED && !is_ldg(probs)) {
+          fr.n_faces = std::max(fr.n_faces, fused_faces(c->L.shape.elems, p.pe_size));
+          fr.lds_words = fused_lds_words(c->S, K, fr.n_faces);
         }
       }
-      c->mode[K - 1][gi] = form == FORM_LIN || !range_async ? FUSED_NOPE : (c->split ? FUSED_SPLIT : FUSED_FULL);
+      c->grid[list][gi] = fused_grid((int32_t)wf.size() - b);
+      // one problem, whose tiles are listed in order: the kernel forms its
+      // items without loading the list
+      c->single[list][gi] = n_in == 1 ? wf[b].prob : -1;
     }
-    c->group[K - 1][kFusedRanges] = (int32_t)wf.size();
-    if ((int64_t)wf.size() != (K == 1 ? c->L.n_work_f : c->L.n_work_f2)) {
+    c->group[list][kFusedRanges] = (int32_t)wf.size();
+    if ((int64_t)wf.size() != (list == 0 ? c->L.n_work_f : c->L.n_work_f2)) {
       delete c;
       return fail(ADG_E_INVALID, "internal: fused work list does not match the workspace layout");
-    }
-    for (int gi = 0; gi < kFusedRanges; ++gi) {
-      const int32_t b = c->group[K - 1][gi], e = c->group[K - 1][gi + 1];
-      c->grid[K - 1][gi] = fused_grid(e - b);
-      // one problem whose tiles are listed in order: the kernel forms its
-      // items without loading the list (never under the split)
-      bool one = e > b && c->mode[K - 1][gi] != FUSED_SPLIT;
-      for (int32_t w = b; w < e && one; ++w) one = wf[w].prob == wf[b].prob && wf[w].tile == w - b;
-      c->single[K - 1][gi] = one ? wf[b].prob : -1;
     }
   }
   for (int32_t i = 0; i < n_probs; ++i) {  // stage/stats list in problem order (contiguous per problem)
@@ -1127,8 +1089,17 @@ int adg_init_scratch(adg_ctx** out, const adg_problem* probs, int32_t n_probs, c
   int64_t need = 0;
   int rc = adg_workspace_size(probs, n_probs, opt, 0, &need);
   if (rc) return rc;
-  const int64_t extra = make_layout(probs, n_probs, opt, 0).lin_extra;
-  if (need - extra > kScratchBytes || extra > kScratchExtra)
+  // where the library's choice of steps per launch (longer rings and lists)
+  // does not fit, two steps
+  auto beside_tables = [&](const adg_options* o) {
+    const Layout L = make_layout(probs, n_probs, o, 0);
+    return L.total - align_up(8 * L.lin_doubles, kAlign);
+  };
+  adg_options two = opt ? *opt : adg_options{};
+  if (two.fused_steps == 0) two.fused_steps = 2;
+  if (beside_tables(opt) > kScratchBytes) opt = &two;
+  need = make_layout(probs, n_probs, opt, 0).total;
+  if (beside_tables(opt) > kScratchBytes || need - beside_tables(opt) > kScratchTables)
     return fail(ADG_E_WORKSPACE, "adg_init_scratch: these problems need " + std::to_string(need) +
                                      " bytes of workspace; the static scratch array holds " +
                                      std::to_string(kScratchBytes));
@@ -1179,13 +1150,11 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
         const int32_t m = (int32_t)std::min<int64_t>(n_steps - done, kGraphSteps);
         for (int32_t i = 0; i < m;) {
           const int64_t n = done + i;
-          if (c->fused_steps == 2 && i + 1 < m) {
-            if ((rc = launch_fused(c, 2, ck + tot * n, slot(n + 2), slot(n + 1), i, c->stream))) return rc;
-            i += 2;
-          } else {
-            if ((rc = launch_fused(c, 1, ck + tot * n, slot(n + 1), nullptr, i, c->stream))) return rc;
-            i += 1;
-          }
+          // the states before the launch's last lie in consecutive slots
+          const int K = next_steps(c, m - i);
+          if ((rc = launch_fused(c, K, ck + tot * n, slot(n + K), K > 1 ? ck + tot * (n + 1) : nullptr, i, c->stream)))
+            return rc;
+          i += K;
         }
         ADG_HIP(launch_advance((int64_t*)(c->ws + c->L.ctr), m, c->stream));
         done += m;
@@ -1197,7 +1166,6 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
     }
     for (int64_t k = 0; done < n_steps; ++k) {
       ADG_HIP(hipMemcpyAsync(c->ws + c->L.ckpt + 8 * tot * k, d_u, 8 * tot, hipMemcpyDeviceToDevice, c->stream));
-      if ((rc = c->save_records(k, false))) return rc;
       const int64_t m = std::min<int64_t>(C, n_steps - done);
       if ((rc = adg_run(c, d_u, m, flags & ~(ADG_RUN_RECORD | ADG_RUN_CHECK_FINITE)))) return rc;
       done += m;
@@ -1359,7 +1327,6 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   const size_t bytes = 8 * (size_t)tot;
   int rc;
 
-  if ((rc = c->save_records(L.n_ckpt, false))) return rc;
   ADG_HIP(hipMemcpyAsync(lam, d_cot_uT, bytes, hipMemcpyDeviceToDevice, st));
   ADG_HIP(launch_zero(adjring, 8 * std::max<int64_t>(L.ring_doubles, 1), st));
   ADG_HIP(launch_zero(cpart, 8 * (size_t)std::max<int32_t>(L.n_work_a, 1), st));
@@ -1388,15 +1355,13 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
     // u^{n0+i}: the checkpoint itself for i = 0, recomputed into useg[i-1] after
     double* ck = (double*)(ws + L.ckpt) + tot * k;
     auto state = [&](int64_t i) { return i == 0 ? ck : useg + tot * (i - 1); };
-    if (len > 1 && (rc = c->save_records(k, true))) return rc;
     for (int64_t i = 1; i < len;) {
-      if (c->fused_steps == 2 && i + 1 < len) {  // two steps per launch, the first one written too
-        if ((rc = launch_fused(c, 2, state(i - 1), state(i + 1), state(i), (int32_t)(n0 + i - 1), st))) return rc;
-        i += 2;
-      } else {
-        if ((rc = launch_fused(c, 1, state(i - 1), state(i), nullptr, (int32_t)(n0 + i - 1), st))) return rc;
-        i += 1;
-      }
+      // several steps per launch, each one's state written
+      const int K = next_steps(c, len - i);
+      if ((rc = launch_fused(c, K, state(i - 1), state(i + K - 1), K > 1 ? state(i) : nullptr, (int32_t)(n0 + i - 1),
+                             st)))
+        return rc;
+      i += K;
     }
     for (int64_t i = len - 1; i >= 0; --i) {
       ADG_HIP(launch_adj_fused(c->rk, c->phys, aa, state(i), lam, lamu, ring, adjring, cpart, (int32_t)(n0 + i),
@@ -1405,7 +1370,6 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
     }
   }
   ADG_HIP(hipMemcpyAsync(d_grad_u0, lam, bytes, hipMemcpyDeviceToDevice, st));
-  if ((rc = c->save_records(L.n_ckpt, true))) return rc;
   ADG_HIP(launch_set_counter(ctr, c->steps, st));
   if (h_grad_speed) {
     std::vector<double> part(c->work_a.size());

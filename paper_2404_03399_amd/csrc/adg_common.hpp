@@ -10,7 +10,6 @@ constexpr int kMaxNp = 5;     // degree <= 4
 constexpr int kMaxL = 8;      // delays 0..7
 constexpr int kMaxQ = 5;      // AT levels
 constexpr int kBlock = 256;   // threads per workgroup (4 wave64)
-constexpr int kRecSlots = 4;  // fused kernel PE-face record slots, indexed by step mod 4
 
 // PHYS_ADV_UPWIND_POS: upwind advection with a > 0 in the fused kernel, which
 // folds the right-face flux a u_p into the volume operator.
@@ -24,12 +23,6 @@ __host__ __device__ constexpr int rk_stages(int rk) {
   return rk == RK_HEUN ? 2 : (rk == RK_RK4 ? 4 : (rk == RK_LS4 ? 5 : 3));
 }
 constexpr int kMaxStages = 5;
-
-// Packed delays of one PE face and step in the fused kernel's records: byte s
-// holds the clamped delay of stage s (delays < kMaxL <= 255), so that the
-// record jobs of different stages write different bytes of one word.
-using RecWord = uint64_t;
-static_assert(kMaxStages <= (int)sizeof(RecWord), "one byte per stage");
 
 // Division by a run-time invariant 0 < d < 2^31 for dividends n < 2^31 by
 // multiplication (Granlund & Montgomery, PLDI 1994): with l = ceil(log2 d),
@@ -67,8 +60,6 @@ struct DevProblem {
   int64_t u_off;         // offset of the problem in the state vector
   int64_t ring_off;      // offset of the problem's delay ring (doubles)
   int64_t ring2_off;     // local DG: offset of the u-hat ring (same shape as the flux ring)
-  int64_t at_off;        // offset of the problem's AT sums ([kRecSlots][P][S] doubles)
-  int64_t atk_off;       // offset of the problem's delays ([kRecSlots][P] RecWords, byte s = stage s)
   int32_t np;            // degree + 1
   int32_t q;             // AT levels (1 for ADG)
   int32_t n_delays;      // L

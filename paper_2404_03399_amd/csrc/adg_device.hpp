@@ -138,6 +138,15 @@ __host__ __device__ constexpr double ls_b(int rk, int s) {
 }
 __host__ __device__ constexpr bool low_storage(int rk) { return rk == RK_LS3 || rk == RK_LS4; }
 
+// x / 3 correctly rounded: the residual of the product with the rounded
+// reciprocal corrects it (Markstein, IBM J. Res. Dev. 34, 1990); an infinite x
+// gives a NaN residual and keeps the product.  A division instruction sequence
+// in its place is half of an SSP-RK3 update.
+__device__ __forceinline__ double third_of(double x) {
+  const double z = 1.0 / 3.0, q = x * z, r = fma(-3.0, q, x);
+  return r == r ? fma(r, z, q) : q;
+}
+
 // RK update after the stage-s operator value k (oracle's algebraic forms).
 // Every multiply-add is an explicit FMA and nothing else is contracted, so
 // the rounding does not depend on how the compiler schedules the caller
@@ -171,7 +180,7 @@ __device__ __forceinline__ void rk_update(int s, double dt, const double (&u0)[N
       for (int j = 0; j < NP; ++j) y[j] = fma(0.25, fma(dt, k[j], y[j]), 0.75 * u0[j]);
     } else {
 #pragma unroll
-      for (int j = 0; j < NP; ++j) y[j] = fma(2.0 / 3.0, fma(dt, k[j], y[j]), u0[j] / 3.0);
+      for (int j = 0; j < NP; ++j) y[j] = fma(2.0 / 3.0, fma(dt, k[j], y[j]), third_of(u0[j]));
     }
   } else if constexpr (low_storage(RK)) {
     // 2N-storage form, ks holding dU: dU = A_s dU + dt k, y = y + B_s dU
@@ -245,19 +254,6 @@ __device__ __forceinline__ double lane_from_right(double v) {
   return __hiloint2double(hi, lo);
 }
 
-// Per-lane PE-face values.  at[kk][s][lane]: the AT sum of step n + kk
-// (read by the lane itself), then the raw level-(n + kk) flux of an owner
-// lane (read at the end by the lanes that form the next records).  With
-// R <= PE size a lane's R left faces hold at most one PE face.  part / kdj:
-// per record job (a lane of an owner wave), the sum over the levels before
-// the launch and the delay, formed at the start of the launch.
-template <int K, int S>
-struct WaveSmemK {
-  double at[K][kWavesPerBlock][S][kWave];
-  double part[kWavesPerBlock][kWave];
-  int32_t kdj[kWavesPerBlock][kWave];
-};
-
 template <int NP, int PHYS>
 __device__ __forceinline__ void folded_rhs(const DevProblem& P, const double (&y)[NP], double fl, double fr,
                                            double (&k)[NP]) {
@@ -274,12 +270,6 @@ __device__ __forceinline__ void folded_rhs(const DevProblem& P, const double (&y
   }
 }
 
-struct FusedPtrs {
-  double* __restrict__ ring;
-  double* __restrict__ atsum;
-  RecWord* __restrict__ atk;
-};
-
 // Lane of the i-th set bit (from 0) of a wave-uniform mask, 0 if there is none.
 __device__ __forceinline__ int nth_set_lane(uint64_t mask, int i) {
   int lane = 0;
@@ -290,9 +280,6 @@ __device__ __forceinline__ int nth_set_lane(uint64_t mask, int i) {
   }
   return lane;
 }
-
-// Record slot of step m (steps below 2^31).
-__device__ __forceinline__ int64_t rec_slot(int64_t m) { return (int64_t)((uint32_t)m % (uint32_t)kRecSlots); }
 
 // Part of the AT sum of step m = n + ahead (delay kd >= 1) over the levels
 // m - kd - j that precede step n, j = q-1 down to 0, oldest first, one

@@ -16,7 +16,7 @@ enum FusedForm : int { FORM_LIN = 0, FORM_POS = 1, FORM_GEN = 2 };
 constexpr int kForms = 3;
 constexpr int kFusedRanges = 4 * kForms;
 
-struct LinRange {
+struct FaceRange {
   int32_t n_faces;     // most PE faces that a wave of the range holds
   int32_t lds_words;   // doubles of LDS per wave
 };
@@ -27,72 +27,55 @@ struct StepArgs {
   int32_t n_work;
   double* ring;              // delay ring (fluxes), may be null when no PE faces
   int64_t* ctr;              // ctr[0] = steps completed by earlier batches, ctr[2] = non-finite flag
-  double* atsum;             // fused kernel: AT sums of past levels, [kRecSlots][P][S] per problem
-  RecWord* atk;              // fused kernel: clamped delays, [kRecSlots][P] words per problem (byte s = stage s)
-  int32_t group[kFusedRanges + 1];          // fused kernel: work-item ranges per degree and form (below)
-  int32_t grid[kFusedRanges];           // fused kernel: workgroups per range
-  int32_t single[kFusedRanges];         // fused kernel: the only problem of a range, or -1
-  int32_t lane_elems;        // fused kernel: elements per lane (1, 2 or 4)
-  int32_t steps;             // fused kernel: time steps per launch (1 or 2; up to kLinSteps in the linear form)
+  int32_t group[kFusedRanges + 1];   // fused kernel: work-item ranges per degree and form
+  int32_t grid[kFusedRanges];        // fused kernel: workgroups per range
+  int32_t single[kFusedRanges];      // fused kernel: the only problem of a range, or -1
+  FaceRange faces[kFusedRanges];     // fused kernel: PE faces per wave of a range
+  int32_t elems;             // fused kernel: elements per lane (1, 2 or 4)
+  int32_t steps;             // fused kernel: time steps of the launch (a power of two, at most the list's)
+  int32_t halo;              // fused kernel: halo lanes per side (upwind, a > 0: on the left) of the work list
   double* qbuf;              // local DG: q = u_x of the current stage input (state layout)
-  double* umid;              // fused kernel, two steps per launch: also write the state after
-                             // the first step here (state layout), or null
+  double* umid;              // fused kernel, several steps per launch: also write the states after
+                             // the steps before the last here (state layout), or null
+  int64_t mid_stride;        // distance between those states (doubles)
   const double* lin;         // linear form: tables of the problems
-  int32_t lin_elems;         // linear form: elements per lane (1, 2 or 4)
-  int32_t lin_km;            // linear form: steps per launch that the work list's halo holds
-  int32_t lin_halo;          // linear form: halo lanes on the left
-  LinRange lin_range[kFusedRanges];     // linear form, per range
-  int32_t mode[kFusedRanges];           // fused kernel: fused_mode of each range (FUSED_SPLIT ranges mark
-                             // their window items by tile index -(window group + 1))
-  int32_t one_launch;        // fused kernel: one launch over every range (two elements per lane,
-                             // every range FUSED_FULL), else one launch per range
+  int32_t one_launch;        // fused kernel: one launch over every range, else one per range
 };
 
-
 // Fused step kernel geometry: one wave64 per work item, R in {1, 2, 4}
-// consecutive elements per lane, K in {1, 2} time steps per launch, halo of
-// ceil(K S / R) lanes per side; owned elements per work item:
+// consecutive elements per lane, K time steps per launch, a halo of K S
+// elements: on both sides in the general form; on the left for upwind with
+// a > 0, and there one lane more on the right where a problem has PE faces (the
+// element right of the last owned one, whose left face may be one).
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = kBlock / kWave;
+constexpr int kMaxSteps = 8;  // most steps per launch
 __host__ __device__ constexpr int fused_halo(int rk, int R, int K) { return (K * rk_stages(rk) + R - 1) / R; }
 __host__ __device__ constexpr int fused_tile(int rk, int R, int K) { return R * (kWave - 2 * fused_halo(rk, R, K)); }
-
-// Fused kernel modes, per work range: FUSED_FULL handles PE faces in every
-// tile; FUSED_NOPE has every PE-face path compiled out (ranges without
-// asynchronous problems); FUSED_SPLIT (the PE-face split) runs two kinds of
-// wave in one launch: window waves (one element per lane, windows of
-// fused_window elements centred on PE faces, each owning the 2 K S elements
-// that the face's delayed flux reaches in K S stages, with every PE-face
-// path) and tile waves with the PE-face paths compiled out that store only
-// the elements outside those windows.
-enum fused_mode { FUSED_FULL = 0, FUSED_NOPE = 1, FUSED_SPLIT = 2 };
-__host__ __device__ constexpr int fused_window(int rk, int K) { return 4 * K * rk_stages(rk); }
-__host__ __device__ constexpr int fused_windows_per_wave(int rk, int K) { return kWave / fused_window(rk, K); }
-
-// Linear form: halo lanes on the left for K steps, one lane more on the right
-// where a problem has PE faces (the element right of the last owned one, whose
-// left face may be one); owned elements per work item.
-__host__ __device__ constexpr int lin_halo(int S, int R, int K) { return (K * S + R - 1) / R; }
-__host__ __device__ constexpr int lin_tile_elems(int S, int R, int K, bool async) {
-  return R * (kWave - lin_halo(S, R, K) - (async ? 1 : 0));
+__host__ __device__ constexpr int fused_tile_left(int rk, int R, int K, bool async) {
+  return R * (kWave - fused_halo(rk, R, K) - (async ? 1 : 0));
 }
-// PE faces of a wave's 64 R elements at most (R <= PE size, so one per lane)
-__host__ __device__ constexpr int lin_faces(int R, int64_t pe_size) {
+// PE faces of a wave's 64 R elements at most (R divides the PE size, so one per lane)
+__host__ __device__ constexpr int fused_faces(int R, int64_t pe_size) {
   return (int)((kWave * R - 1) / pe_size) + 1;
 }
-// LDS of a wave in doubles (layout in adg_linear.hpp)
-__host__ __device__ constexpr int lin_lds_words(int S, int K, int n_faces) {
+// LDS of a wave in doubles (layout: WaveFaces)
+__host__ __device__ constexpr int fused_lds_words(int S, int K, int n_faces) {
   return n_faces > 0 ? kMaxL * kMaxQ + S + n_faces * (K * S + K + 1) : 0;
 }
-constexpr int kLinSteps = 8;  // most steps per launch
 // One range of the linear form (compiled per stage count).
 template <int S>
 void launch_lin_s(const StepArgs& a, int gi, const double* uin, double* uout, int32_t step_offset, hipStream_t stream);
 
+// Windows of 4 K S elements around a PE face and how many fit a wave: sizes of
+// the room that the workspace keeps for ADG_OPT_PE_SPLIT_ON.
+__host__ __device__ constexpr int fused_window(int rk, int K) { return 4 * K * rk_stages(rk); }
+__host__ __device__ constexpr int fused_windows_per_wave(int rk, int K) { return kWave / fused_window(rk, K); }
+
 // Workgroups of the fused kernel for n_work items (kWavesPerBlock per group).
 inline int fused_grid(int n_work) { return n_work < 1 ? 1 : (n_work + kWavesPerBlock - 1) / kWavesPerBlock; }
 
-// a.steps full RK steps (1 or 2), all stages on chip: state uin -> uout
+// a.steps full RK steps, all stages on chip: state uin -> uout
 // (distinct buffers).  The first step's index is ctr[0] + step_offset.
 hipError_t launch_fused_step(int rk, int phys, const StepArgs& a, const double* uin, double* uout,
                              int32_t step_offset, hipStream_t stream);

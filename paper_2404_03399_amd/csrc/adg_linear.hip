@@ -10,6 +10,8 @@
 
 namespace adg {
 
+extern __shared__ double wave_lds[];
+
 template <int NP, int S, int R>
 __global__ __launch_bounds__(kBlock) void k_lin_step(const DevProblem* __restrict__ probs,
                                                      const double* __restrict__ lin,
@@ -19,7 +21,6 @@ __global__ __launch_bounds__(kBlock) void k_lin_step(const DevProblem* __restric
                                                      double* __restrict__ uout, int32_t step_offset, int32_t K,
                                                      int32_t HL, int32_t n_faces_max, int32_t lds_words,
                                                      int32_t single_prob) {
-  extern __shared__ double lin_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int lane = (int)(threadIdx.x % kWave);
   const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
@@ -28,20 +29,20 @@ __global__ __launch_bounds__(kBlock) void k_lin_step(const DevProblem* __restric
   // a range holding one problem lists its tiles in order: no work-list load
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
   const DevProblem& P = probs[wi.prob];
-  lin_tile<NP, S, R>(P, lin + P.lin_off, wi, ring, n, K, HL, uin, uout, n_faces_max, lin_lds + wv * lds_words, lane);
+  lin_tile<NP, S, R>(P, lin + P.lin_off, wi, ring, n, K, HL, uin, uout, n_faces_max, wave_lds + wv * lds_words, lane);
 }
 
 template <int NP, int S, int R>
 static void lin_go(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
-  const LinRange& lr = a.lin_range[gi];
-  hipLaunchKernelGGL((k_lin_step<NP, S, R>), dim3(a.grid[gi]), dim3(kBlock), 8 * kWavesPerBlock * lr.lds_words, st,
+  const FaceRange& fr = a.faces[gi];
+  hipLaunchKernelGGL((k_lin_step<NP, S, R>), dim3(a.grid[gi]), dim3(kBlock), 8 * kWavesPerBlock * fr.lds_words, st,
                      a.probs, a.lin, a.work, a.ctr, a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.steps,
-                     a.lin_halo, lr.n_faces, lr.lds_words, a.single[gi]);
+                     a.halo, fr.n_faces, fr.lds_words, a.single[gi]);
 }
 
 template <int NP, int S>
 static void lin_r(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
-  switch (a.lin_elems) {
+  switch (a.elems) {
     case 1: lin_go<NP, S, 1>(a, gi, uin, uout, off, st); break;
     case 4: lin_go<NP, S, 4>(a, gi, uin, uout, off, st); break;
     default: lin_go<NP, S, 2>(a, gi, uin, uout, off, st); break;
