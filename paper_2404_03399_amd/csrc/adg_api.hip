@@ -616,6 +616,9 @@ struct adg_ctx {
   // workspace and the generation of that use (-1: caller's workspace)
   int scratch_dev = -1;
   uint64_t scratch_gen = 0;
+  // a call was captured into a caller's graph: its replays advance the device's
+  // step counter alone, so launches count from that one from then on
+  bool device_clock = false;
   // graph cache
   hipGraphExec_t graph = nullptr;
   const double* graph_u = nullptr;
@@ -642,7 +645,8 @@ struct adg_ctx {
     a.work = (const WorkItem*)(ws + work_off);
     a.n_work = n_work;
     a.ring = (double*)(ws + L.ring);
-    a.ctr = (int64_t*)(ws + L.ctr);
+    a.ctr = ctr();
+    a.clock = StepClock{ctr() + CTR_DONE, nullptr, 0};
     for (int i = 0; i <= kFusedRanges; ++i) a.group[i] = group[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.grid[i] = grid[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[list][i];
@@ -669,6 +673,7 @@ struct adg_ctx {
     a.lane_elems = K == 2 ? adj_lane_elems(lane_elems) : 1;
     return a;
   }
+  int64_t* ctr() const { return (int64_t*)(ws + L.ctr); }
   double* state2() const { return (double*)(ws + L.state2); }
 };
 
@@ -676,35 +681,27 @@ namespace {
 
 // K fused steps uin -> uout (with K > 1 also the states after the steps before
 // the last into umid, umid + total_doubles, ..., if not null).
-int launch_fused(const adg_ctx* c, int K, const double* uin, double* uout, double* umid, int32_t step_offset,
-                 hipStream_t st) {
+int launch_fused(const adg_ctx* c, int K, const double* uin, double* uout, double* umid, const StepClock& clock,
+                 int32_t step_offset, hipStream_t st) {
   StepArgs a = c->fused_args(K);
   a.umid = umid;
   a.mid_stride = c->L.total_doubles;
+  a.clock = clock;
   ADG_HIP(launch_fused_step(c->rk, c->fused_phys, a, uin, uout, step_offset, st));
   return ADG_OK;
 }
 
-// Enqueue K steps (K > 1 only for the fused kernel); for the fused kernel the
-// result lands in *cur after a swap with the internal buffer.
-int enqueue_steps(adg_ctx* c, double** cur, double** other, int32_t step_offset, int K, hipStream_t st) {
-  if (c->kernel == ADG_KERNEL_FUSED) {
-    if (int rc = launch_fused(c, K, *cur, *other, nullptr, step_offset, st)) return rc;
-    std::swap(*cur, *other);
-    return ADG_OK;
-  }
-  const StepArgs a = c->stage_args();
-  double* U = *cur;
+// One step with the per-stage kernels, in place on U.
+int launch_stages(adg_ctx* c, const StepArgs& a, double* U, int32_t step_offset, hipStream_t st) {
   double* Y0 = (double*)(c->ws + c->L.y0);
   double* Y1 = (double*)(c->ws + c->L.y1);
   double* A = (double*)(c->ws + c->L.acc);
-  for (int k = 0; k < K; ++k)
-    for (int s = 0; s < c->S; ++s) {
-      const double* yin = s == 0 ? U : ((s & 1) ? Y0 : Y1);
-      double* yout = (s & 1) ? Y1 : Y0;
-      if (c->phys == PHYS_BURGERS_LDG) ADG_HIP(launch_ldg_q(c->rk, s, a, yin, step_offset + k, st));
-      ADG_HIP(launch_stage(c->rk, c->phys, s, a, yin, yout, U, A, step_offset + k, st));
-    }
+  for (int s = 0; s < c->S; ++s) {
+    const double* yin = s == 0 ? U : ((s & 1) ? Y0 : Y1);
+    double* yout = (s & 1) ? Y1 : Y0;
+    if (c->phys == PHYS_BURGERS_LDG) ADG_HIP(launch_ldg_q(c->rk, s, a, yin, step_offset, st));
+    ADG_HIP(launch_stage(c->rk, c->phys, s, a, yin, yout, U, A, step_offset, st));
+  }
   return ADG_OK;
 }
 
@@ -715,15 +712,62 @@ int next_steps(const adg_ctx* c, int64_t left) {
   return K;
 }
 
-// Steps [0, m) of a batch: as many per launch as the kernel allows.
-int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, hipStream_t st) {
+// m steps, as many per launch as the kernel allows, the step counter included.
+// The state goes from *cur through `dst(i)` for each launch's result after i
+// steps of the batch (mid(i): states within a launch, or null).  n0: index of
+// the first step, or -1 to count from the device's counter.
+template <class Dst, class Mid>
+int enqueue_batch(adg_ctx* c, double* cur, int32_t m, int64_t n0, hipStream_t st, Dst dst, Mid mid) {
+  int64_t* ctr = c->ctr();
+  if (c->kernel != ADG_KERNEL_FUSED) {
+    const StepArgs a = c->stage_args();
+    for (int32_t i = 0; i < m; ++i)
+      if (int rc = launch_stages(c, a, cur, i, st)) return rc;
+    ADG_HIP(launch_advance(ctr, m, st));
+    return ADG_OK;
+  }
   for (int32_t i = 0; i < m;) {
     const int K = next_steps(c, m - i);
-    const int rc = enqueue_steps(c, cur, other, i, K, st);
-    if (rc) return rc;
+    const bool first = i == 0, last = i + K >= m;
+    StepClock clock{ctr + (n0 >= 0 ? CTR_ZERO : (first ? CTR_DONE : CTR_BATCH)), nullptr, 0};
+    if (n0 >= 0) {
+      if (last) clock = StepClock{clock.from, ctr + CTR_DONE, n0 + m};
+    } else if (!(first && last)) {  // the word read is never the word written
+      if (first) clock.to = ctr + CTR_BATCH;
+      if (last) clock = StepClock{clock.from, ctr + CTR_DONE, m};
+    }
+    double* out = dst(i + K);
+    if (int rc = launch_fused(c, K, cur, out, K > 1 ? mid(i + 1) : nullptr, clock, (int32_t)((n0 >= 0 ? n0 : 0) + i), st))
+      return rc;
+    if (n0 < 0 && first && last) ADG_HIP(launch_advance(ctr, m, st));
+    cur = out;
     i += K;
   }
   return ADG_OK;
+}
+
+// The same between *cur and *other, which are swapped with every launch.
+int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, int64_t n0, hipStream_t st) {
+  return enqueue_batch(
+      c, *cur, m, n0, st,
+      [&](int32_t) {
+        std::swap(*cur, *other);
+        return *cur;
+      },
+      [](int32_t) { return (double*)nullptr; });
+}
+
+// Whether the context's stream is being captured by the caller (then, and from
+// then on, steps count from the device's counter).
+void note_capture(adg_ctx* c) {
+  if (c->device_clock) return;
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    c->device_clock = true;
+  } else if (s != hipStreamCaptureStatusNone) {
+    c->device_clock = true;
+  }
 }
 
 int reset_device(adg_ctx* c) {
@@ -755,9 +799,7 @@ int build_graph(adg_ctx* c, double* d_u) {
   }
   double* cur = d_u;
   double* other = c->state2();
-  rc = enqueue_batch(c, &cur, &other, kGraphSteps, cap);
-  if (rc == ADG_OK && launch_advance((int64_t*)(c->ws + c->L.ctr), kGraphSteps, cap) != hipSuccess)
-    rc = fail(ADG_E_HIP, "capture of the step-counter advance failed");
+  rc = enqueue_batch(c, &cur, &other, kGraphSteps, -1, cap);
   const hipError_t e1 = hipStreamEndCapture(cap, &g);
   (void)hipStreamDestroy(cap);
   if (rc != ADG_OK) { if (g) (void)hipGraphDestroy(g); return rc; }
@@ -1132,6 +1174,7 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
   if (n_steps < 0) return fail(ADG_E_INVALID, "n_steps < 0");
   if (c->steps + n_steps >= ((int64_t)1 << 31)) return fail(ADG_E_INVALID, "step index would exceed 2^31 - 1");
   if (flags & ~(ADG_RUN_GRAPH | ADG_RUN_RECORD | ADG_RUN_CHECK_FINITE)) return fail(ADG_E_INVALID, "unknown flags");
+  note_capture(c);
   if (flags & ADG_RUN_RECORD) {
     if (c->L.n_rec <= 0) return fail(ADG_E_STATE, "context was created without a recording horizon");
     if (c->steps != 0) return fail(ADG_E_STATE, "ADG_RUN_RECORD must start at step 0 (call adg_reset)");
@@ -1145,18 +1188,14 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
       // launch where the context runs two, the launch writing both states
       double* ck = (double*)(c->ws + c->L.ckpt);
       ADG_HIP(hipMemcpyAsync(ck, d_u, 8 * tot, hipMemcpyDeviceToDevice, c->stream));
-      auto slot = [&](int64_t j) { return j < n_steps ? ck + tot * j : d_u; };
+      // the states before a launch's last lie in consecutive slots
       while (done < n_steps) {
         const int32_t m = (int32_t)std::min<int64_t>(n_steps - done, kGraphSteps);
-        for (int32_t i = 0; i < m;) {
-          const int64_t n = done + i;
-          // the states before the launch's last lie in consecutive slots
-          const int K = next_steps(c, m - i);
-          if ((rc = launch_fused(c, K, ck + tot * n, slot(n + K), K > 1 ? ck + tot * (n + 1) : nullptr, i, c->stream)))
-            return rc;
-          i += K;
-        }
-        ADG_HIP(launch_advance((int64_t*)(c->ws + c->L.ctr), m, c->stream));
+        if ((rc = enqueue_batch(
+                 c, ck + tot * done, m, c->device_clock ? -1 : done, c->stream,
+                 [&](int32_t i) { return done + i < n_steps ? ck + tot * (done + i) : d_u; },
+                 [&](int32_t i) { return ck + tot * (done + i); })))
+          return rc;
         done += m;
       }
       c->steps += n_steps;
@@ -1192,23 +1231,21 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
       left -= c->graph_steps;
     }
   }
-  // remaining steps in batches of at most kGraphSteps, each closed by one
-  // counter advance
+  // remaining steps in batches of at most kGraphSteps
   while (left > 0) {
     const int32_t m = (int32_t)std::min<int64_t>(left, kGraphSteps);
-    if ((rc = enqueue_batch(c, &cur, &other, m, c->stream))) return rc;
-    ADG_HIP(launch_advance((int64_t*)(c->ws + c->L.ctr), m, c->stream));
+    if ((rc = enqueue_batch(c, &cur, &other, m, c->device_clock ? -1 : c->steps + n_steps - left, c->stream))) return rc;
     left -= m;
   }
   if (cur != d_u)
     ADG_HIP(hipMemcpyAsync(d_u, cur, 8 * c->L.total_doubles, hipMemcpyDeviceToDevice, c->stream));
   c->steps += n_steps;
   if (flags & ADG_RUN_CHECK_FINITE) {
-    int64_t* ctr = (int64_t*)(c->ws + c->L.ctr);
-    ADG_HIP(launch_zero(ctr + 2, sizeof(int64_t), c->stream));
+    int64_t* ctr = c->ctr();
+    ADG_HIP(launch_zero(ctr + CTR_FLAG, sizeof(int64_t), c->stream));
     ADG_HIP(launch_check_finite(c->stage_args(), d_u, c->stream));
     int64_t flag = 0;
-    ADG_HIP(hipMemcpyAsync(&flag, ctr + 2, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
+    ADG_HIP(hipMemcpyAsync(&flag, ctr + CTR_FLAG, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
     ADG_HIP(hipStreamSynchronize(c->stream));
     if (flag) return fail(ADG_E_NONFINITE, "state contains NaN or Inf");
   }
@@ -1236,7 +1273,8 @@ int adjoint_stage(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   const int S = c->S;
   char* ws = c->ws;
   hipStream_t st = c->stream;
-  const StepArgs sa = c->stage_args();
+  StepArgs sa = c->stage_args();
+  sa.ctr = c->ctr() + CTR_ZERO;  // launches below pass absolute step indices
   double* lam = (double*)(ws + L.lam);
   double* lamu = lam + tot;
   double* Q = (double*)(ws + L.q);
@@ -1248,13 +1286,11 @@ int adjoint_stage(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   double* abuf = (double*)(ws + L.acc);
   double* y0 = (double*)(ws + L.y0);
   double* y1 = (double*)(ws + L.y1);
-  int64_t* ctr = (int64_t*)(ws + L.ctr);
   const size_t bytes = 8 * (size_t)tot;
 
   ADG_HIP(hipMemcpyAsync(lam, d_cot_uT, bytes, hipMemcpyDeviceToDevice, st));
   ADG_HIP(launch_zero(adjring, 8 * std::max<int64_t>(L.ring_doubles, 1), st));
   ADG_HIP(launch_zero(cpart, 8 * (size_t)L.n_work_s, st));
-  ADG_HIP(launch_set_counter(ctr, 0, st));  // launches below pass absolute step indices
 
   for (int64_t k = L.n_ckpt - 1; k >= 0; --k) {
     const int64_t n0 = k * C;
@@ -1289,7 +1325,6 @@ int adjoint_stage(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
     }
   }
   ADG_HIP(hipMemcpyAsync(d_grad_u0, lam, bytes, hipMemcpyDeviceToDevice, st));
-  ADG_HIP(launch_set_counter(ctr, c->steps, st));
   if (h_grad_speed) {
     std::vector<double> part(L.n_work_s);
     ADG_HIP(hipMemcpyAsync(part.data(), cpart, 8 * part.size(), hipMemcpyDeviceToHost, st));
@@ -1323,14 +1358,12 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   double* cpart = (double*)(ws + L.cpart);
   const double* ring = (const double*)(ws + L.ring);
   double* useg = (double*)(ws + L.useg);
-  int64_t* ctr = (int64_t*)(ws + L.ctr);
   const size_t bytes = 8 * (size_t)tot;
   int rc;
 
   ADG_HIP(hipMemcpyAsync(lam, d_cot_uT, bytes, hipMemcpyDeviceToDevice, st));
   ADG_HIP(launch_zero(adjring, 8 * std::max<int64_t>(L.ring_doubles, 1), st));
   ADG_HIP(launch_zero(cpart, 8 * (size_t)std::max<int32_t>(L.n_work_a, 1), st));
-  ADG_HIP(launch_set_counter(ctr, 0, st));  // launches below pass absolute step indices
 
   // linear advection: the reverse sweep does not depend on the forward states;
   // they are recomputed only for dJ/da
@@ -1358,8 +1391,8 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
     for (int64_t i = 1; i < len;) {
       // several steps per launch, each one's state written
       const int K = next_steps(c, len - i);
-      if ((rc = launch_fused(c, K, state(i - 1), state(i + K - 1), K > 1 ? state(i) : nullptr, (int32_t)(n0 + i - 1),
-                             st)))
+      if ((rc = launch_fused(c, K, state(i - 1), state(i + K - 1), K > 1 ? state(i) : nullptr,
+                             StepClock{c->ctr() + CTR_ZERO, nullptr, 0}, (int32_t)(n0 + i - 1), st)))
         return rc;
       i += K;
     }
@@ -1370,7 +1403,6 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
     }
   }
   ADG_HIP(hipMemcpyAsync(d_grad_u0, lam, bytes, hipMemcpyDeviceToDevice, st));
-  ADG_HIP(launch_set_counter(ctr, c->steps, st));
   if (h_grad_speed) {
     std::vector<double> part(c->work_a.size());
     ADG_HIP(hipMemcpyAsync(part.data(), cpart, 8 * part.size(), hipMemcpyDeviceToHost, st));

@@ -15,7 +15,7 @@ extern __shared__ double wave_lds[];
 template <int NP, int RK, int PHYS, int R>
 __global__ __launch_bounds__(kBlock) void k_fused_step(const DevProblem* __restrict__ probs,
                                                        const WorkItem* __restrict__ work,
-                                                       const int64_t* __restrict__ ctr, double* __restrict__ ring,
+                                                       const StepClock clock, double* __restrict__ ring,
                                                        int32_t w_begin, int32_t w_end,
                                                        const double* __restrict__ uin, double* __restrict__ uout,
                                                        double* __restrict__ umid, int64_t mid_stride,
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(const DevProblem* __restr
   const int lane = (int)(threadIdx.x % kWave);
   const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
   if (w >= w_end) return;  // whole wave
-  const int64_t n = ctr[0] + step_offset;
+  const int64_t n = clock.tick(w == w_begin) + step_offset;
   // a range holding one problem lists its tiles in order: no work-list load
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
   stage_tile<NP, RK, PHYS, R>(probs[wi.prob], wi, ring, n, K, HL, uin, uout, umid, mid_stride, n_faces_max,
@@ -48,7 +48,7 @@ template <int RK, int PHYS, int R>
 __global__ __launch_bounds__(kBlock) void k_fused_all(const DevProblem* __restrict__ probs,
                                                       const double* __restrict__ lin,
                                                       const WorkItem* __restrict__ work,
-                                                      const int64_t* __restrict__ ctr, double* __restrict__ ring,
+                                                      const StepClock clock, double* __restrict__ ring,
                                                       const FusedRangeTable rt, const double* __restrict__ uin,
                                                       double* __restrict__ uout, double* __restrict__ umid,
                                                       int64_t mid_stride, int32_t step_offset, int32_t K, int32_t HL) {
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_all(const DevProblem* __restri
   const int lane = (int)(threadIdx.x % kWave);
   const int w = xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
   if (w >= rt.group[kFusedRanges]) return;  // whole wave
-  const int64_t n = ctr[0] + step_offset;
+  const int64_t n = clock.tick(w == 0) + step_offset;
   const WorkItem wi = work[w];
   const DevProblem& P = probs[wi.prob];
   double* lds = wave_lds + wv * rt.lds_words;
@@ -332,7 +332,7 @@ __device__ __forceinline__ void wave_tile_ldg(const DevProblem& P, const WorkIte
 template <int NP, int RK, int K, int R>
 __global__ __launch_bounds__(kBlock) void k_fused_ldg(const DevProblem* __restrict__ probs,
                                                       const WorkItem* __restrict__ work,
-                                                      const int64_t* __restrict__ ctr, double* __restrict__ ring,
+                                                      const StepClock clock, double* __restrict__ ring,
                                                       int32_t w_begin, int32_t w_end, const double* __restrict__ uin,
                                                       double* __restrict__ uout, int32_t step_offset,
                                                       int32_t single_prob) {
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_ldg(const DevProblem* __restri
   const int lane = (int)(threadIdx.x % kWave);
   const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
   if (w >= w_end) return;  // whole wave
-  const int64_t n = ctr[0] + step_offset;
+  const int64_t n = clock.tick(w == w_begin) + step_offset;
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
   wave_tile_ldg<NP, RK, K, R>(probs[wi.prob], wi, ring, n, uin, uout, sm, wv, lane);
 }
@@ -349,10 +349,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_ldg(const DevProblem* __restri
 template <int NP, int RK, int R>
 static void fused_ldg_go_r(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   if (a.steps == 2)
-    hipLaunchKernelGGL((k_fused_ldg<NP, RK, 2, R>), dim3(a.grid[gi]), dim3(kBlock), 0, st, a.probs, a.work, a.ctr,
+    hipLaunchKernelGGL((k_fused_ldg<NP, RK, 2, R>), dim3(a.grid[gi]), dim3(kBlock), 0, st, a.probs, a.work, a.clock,
                        a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.single[gi]);
   else
-    hipLaunchKernelGGL((k_fused_ldg<NP, RK, 1, R>), dim3(a.grid[gi]), dim3(kBlock), 0, st, a.probs, a.work, a.ctr,
+    hipLaunchKernelGGL((k_fused_ldg<NP, RK, 1, R>), dim3(a.grid[gi]), dim3(kBlock), 0, st, a.probs, a.work, a.clock,
                        a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.single[gi]);
 }
 
@@ -382,7 +382,7 @@ template <int NP, int RK, int PHYS, int R>
 static void fused_go_r(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   const FaceRange& fr = a.faces[gi];
   hipLaunchKernelGGL((k_fused_step<NP, RK, PHYS, R>), dim3(a.grid[gi]), dim3(kBlock),
-                     8 * kWavesPerBlock * fr.lds_words, st, a.probs, a.work, a.ctr, a.ring, a.group[gi],
+                     8 * kWavesPerBlock * fr.lds_words, st, a.probs, a.work, a.clock, a.ring, a.group[gi],
                      a.group[gi + 1], uin, uout, a.umid, a.mid_stride, off, a.steps, a.halo, fr.n_faces, fr.lds_words,
                      a.single[gi]);
 }
@@ -442,10 +442,10 @@ static void fused_all_go(const StepArgs& a, const double* uin, double* uout, int
   const dim3 g(fused_grid(a.group[kFusedRanges])), b(kBlock);
   const size_t lds = 8 * (size_t)(kWavesPerBlock * rt.lds_words);
   if (a.elems == 2)
-    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2>), g, b, lds, st, a.probs, a.lin, a.work, a.ctr, a.ring, rt, uin, uout,
+    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 2>), g, b, lds, st, a.probs, a.lin, a.work, a.clock, a.ring, rt, uin, uout,
                        a.umid, a.mid_stride, off, a.steps, a.halo);
   else
-    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 1>), g, b, lds, st, a.probs, a.lin, a.work, a.ctr, a.ring, rt, uin, uout,
+    hipLaunchKernelGGL((k_fused_all<RK, PHYS, 1>), g, b, lds, st, a.probs, a.lin, a.work, a.clock, a.ring, rt, uin, uout,
                        a.umid, a.mid_stride, off, a.steps, a.halo);
 }
 

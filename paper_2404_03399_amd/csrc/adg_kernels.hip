@@ -7,8 +7,8 @@
 
 namespace adg {
 
-// The absolute step index of a launch is ctr[0] + step_offset: launches of
-// one batch (or one captured graph) carry offsets 0, 1, 2, ... and a single
+// The absolute step index of a stage kernel is ctr[0] + step_offset: launches
+// of one batch (or one captured graph) carry offsets 0, 1, 2, ... and a single
 // k_advance at the end of the batch adds the batch length to ctr[0].  No
 // workgroup ever writes the counter while others read it.
 __global__ void k_advance(int64_t* __restrict__ ctr, int64_t n_steps) {
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void k_check_finite(const DevProblem* __res
   if (e >= P.n_elem) return;
   bool bad = false;
   for (int j = 0; j < P.np; ++j) bad |= !isfinite(u[P.u_off + j * P.ld + e]);
-  if (bad) ctr[2] = 1;
+  if (bad) ctr[CTR_FLAG] = 1;
 }
 
 // ---------------------------------------------------------------- launch ---
@@ -455,15 +455,6 @@ hipError_t launch_zero(void* p, int64_t bytes, hipStream_t stream) {
   const int64_t n = bytes / 8;
   const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 2048);
   hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(kBlock), 0, stream, (uint64_t*)p, n);
-  return hipGetLastError();
-}
-
-__global__ void k_set_counter(int64_t* __restrict__ ctr, int64_t v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) ctr[0] = v;
-}
-
-hipError_t launch_set_counter(int64_t* ctr, int64_t value, hipStream_t stream) {
-  hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(64), 0, stream, ctr, value);
   return hipGetLastError();
 }
 

@@ -16,6 +16,31 @@ enum FusedForm : int { FORM_LIN = 0, FORM_POS = 1, FORM_GEN = 2 };
 constexpr int kForms = 3;
 constexpr int kFusedRanges = 4 * kForms;
 
+// The context's counter words: steps completed, the same while a batch of
+// launches is under way, non-finite flag, and a word that stays 0.
+enum CtrWord : int { CTR_DONE = 0, CTR_BATCH = 1, CTR_FLAG = 2, CTR_ZERO = 3 };
+
+// Step index of a fused launch: *from + step_offset; one wave also leaves
+// *from + add in *to (null: nothing), a word that no wave of the launch reads.
+// A batch of launches closes itself: with the first step's index known on the
+// host, its launches count from CTR_ZERO and the last one writes CTR_DONE; one
+// that is replayed from a graph counts from CTR_DONE in its first launch, which
+// copies it to CTR_BATCH, and from there in the others, the last of which
+// writes CTR_DONE (as a kernel of its own after every batch the advance cost
+// 4 us of the 30 that 16 steps of a small mesh take).
+struct StepClock {
+  const int64_t* from;
+  int64_t* to;
+  int64_t add;
+#ifdef __HIPCC__
+  __device__ __forceinline__ int64_t tick(bool first_wave) const {
+    const int64_t base = *from;
+    if (first_wave && to != nullptr && threadIdx.x == 0) *to = base + add;
+    return base;
+  }
+#endif
+};
+
 struct FaceRange {
   int32_t n_faces;     // most PE faces that a wave of the range holds
   int32_t lds_words;   // doubles of LDS per wave
@@ -26,7 +51,8 @@ struct StepArgs {
   const WorkItem* work;      // device work list, one item per workgroup
   int32_t n_work;
   double* ring;              // delay ring (fluxes), may be null when no PE faces
-  int64_t* ctr;              // ctr[0] = steps completed by earlier batches, ctr[2] = non-finite flag
+  int64_t* ctr;              // stage kernels: the word that step_offset counts from; statistics: the context's words
+  StepClock clock;           // fused kernel
   int32_t group[kFusedRanges + 1];   // fused kernel: work-item ranges per degree and form
   int32_t grid[kFusedRanges];        // fused kernel: workgroups per range
   int32_t single[kFusedRanges];      // fused kernel: the only problem of a range, or -1
@@ -76,7 +102,7 @@ __host__ __device__ constexpr int fused_windows_per_wave(int rk, int K) { return
 inline int fused_grid(int n_work) { return n_work < 1 ? 1 : (n_work + kWavesPerBlock - 1) / kWavesPerBlock; }
 
 // a.steps full RK steps, all stages on chip: state uin -> uout
-// (distinct buffers).  The first step's index is ctr[0] + step_offset.
+// (distinct buffers).  The first step's index is *a.clock.from + step_offset.
 hipError_t launch_fused_step(int rk, int phys, const StepArgs& a, const double* uin, double* uout,
                              int32_t step_offset, hipStream_t stream);
 // Its per-integrator part (one translation unit per RK scheme).
@@ -137,10 +163,7 @@ __host__ __device__ constexpr int adj_tile_elems2(int rk, int R) { return R * (k
 // Zero fill of `bytes` bytes at p (8-byte aligned, a multiple of 8).
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t stream);
 
-// ctr[0] := value (one lane).
-hipError_t launch_set_counter(int64_t* ctr, int64_t value, hipStream_t stream);
-
-// ctr[0] += n_steps (one lane), closing a batch of launches.
+// ctr[CTR_DONE] += n_steps (one lane), closing a batch of stage kernels or of one fused launch.
 hipError_t launch_advance(int64_t* ctr, int64_t n_steps, hipStream_t stream);
 
 // Per-workgroup partial error sums (work list with kBlock elements per item),

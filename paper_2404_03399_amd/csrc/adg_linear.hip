@@ -16,7 +16,7 @@ template <int NP, int S, int R>
 __global__ __launch_bounds__(kBlock) void k_lin_step(const DevProblem* __restrict__ probs,
                                                      const double* __restrict__ lin,
                                                      const WorkItem* __restrict__ work,
-                                                     const int64_t* __restrict__ ctr, double* __restrict__ ring,
+                                                     const StepClock clock, double* __restrict__ ring,
                                                      int32_t w_begin, int32_t w_end, const double* __restrict__ uin,
                                                      double* __restrict__ uout, int32_t step_offset, int32_t K,
                                                      int32_t HL, int32_t n_faces_max, int32_t lds_words,
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBlock) void k_lin_step(const DevProblem* __restric
   const int lane = (int)(threadIdx.x % kWave);
   const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
   if (w >= w_end) return;  // whole wave
-  const int64_t n = ctr[0] + step_offset;
+  const int64_t n = clock.tick(w == w_begin) + step_offset;
   // a range holding one problem lists its tiles in order: no work-list load
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
   const DevProblem& P = probs[wi.prob];
@@ -36,7 +36,7 @@ template <int NP, int S, int R>
 static void lin_go(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   const FaceRange& fr = a.faces[gi];
   hipLaunchKernelGGL((k_lin_step<NP, S, R>), dim3(a.grid[gi]), dim3(kBlock), 8 * kWavesPerBlock * fr.lds_words, st,
-                     a.probs, a.lin, a.work, a.ctr, a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.steps,
+                     a.probs, a.lin, a.work, a.clock, a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.steps,
                      a.halo, fr.n_faces, fr.lds_words, a.single[gi]);
 }
 

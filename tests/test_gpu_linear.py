@@ -97,3 +97,40 @@ def test_linear_form_in_a_batch(torch_cuda):
     for kw in ({}, dict(one_launch=True)):
         for w, a, b in zip(ws, alone, _run(ws, u0s, 7, **kw)):
             assert np.array_equal(a, b), (w.name, kw)
+
+
+@pytest.mark.parametrize("ne,n", [(1280, 3), (1280, 1), (320, 11)])
+def test_steps_in_a_callers_graph(torch_cuda, ne, n):
+    """A caller's capture of adg_run: its replays, the library's own graph and
+    direct steps in any order advance one step counter."""
+    from paper_2404_03399_amd.solver import Solver
+    torch = torch_cuda
+    w = _w(ne, 64)
+    print(f"[gpu-case] captured run of {n} steps, N={ne}", flush=True)
+    u0 = stepper.initial_state(w)
+    st = torch.cuda.Stream()
+    s = Solver(w, stream=st)
+    total = 2 + 4 * n + 16 + 5
+    ref = Solver(w)
+    v = ref.pack(u0)
+    ref.run(v, total, graph=False)
+    with torch.cuda.stream(st):
+        u = s.pack(u0)
+        s.run(u, 2, graph=False)
+        s.capture_graph(u)
+        st.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s.run(u, n, graph=False)
+        for i in range(4):
+            g.replay()
+            if i == 1:
+                s.run(u, 16)
+                float(u.sum())
+            if i == 2:
+                s.run(u, 5, graph=False)
+                float(u.sum())
+    st.synchronize()
+    assert np.array_equal(s.unpack(u)[0], ref.unpack(v)[0])
+    s.close()
+    ref.close()
