@@ -430,13 +430,14 @@ int form_of(const adg_problem& p, int kernel, int64_t n_rec) {
 
 // Owned elements of a work item of the list for K steps.
 int tile_of(const adg_problem& p, int form, const Shape& s, int K) {
+  if (p.equation == ADG_EQ_VISCOUS_BURGERS) return ldg_tile_elems((int)p.rk, s.elems, K);
   if (form == FORM_GEN) return fused_tile((int)p.rk, s.elems, K);
   return fused_tile_left((int)p.rk, s.elems, K, async_of(p));
 }
 
 // Doubles of LDS per wave for problem p in launches of K steps.
 int lds_of(const adg_problem& p, int elems, int K) {
-  return async_of(p) ? fused_lds_words(rk_stages((int)p.rk), K, fused_faces(elems, p.pe_size)) : 0;
+  return async_of(p) ? fused_lds_words(rk_stages((int)p.rk), K, fused_faces(elems, p.pe_size), is_ldg(&p) ? 2 : 1) : 0;
 }
 
 // Elements per lane R: the option's or the library's choice, halved until it
@@ -460,11 +461,16 @@ int lds_of(const adg_problem& p, int elems, int K) {
 //                 (4,8) 31.0; five stages (lsrk4, p = 2) 2^22 (4,4) 27.0, (4,8)
 //                 30.6; 10^5, p = 4, lsrk4, PE 30 (2,2) 4.2, (2,4) 4.5, (2,8) 5.4
 //   general, Burgers, SSP-RK3, p = 2   2^22 (2,4) 26.2, (4,4) 24.0, (4,8) 23.7
+//   local DG, p = 2   Heun 2^14 (1,4) 2.02, (1,8) 1.79, (2,8) 1.85; 2^16 2.35, 2.10,
+//                 1.92; 2^18 (2,8) 3.16, (4,8) 3.53; 2^20 8.11, 7.43; SSP-RK3 2^14
+//                 (1,4) 2.25, (1,8) 2.14; 2^18 (2,4) 4.81, (2,8) 5.07; 2^20 (4,4)
+//                 11.75, (4,8) 11.96; RK4, p = 3 2^14 (1,4) 2.63, (2,8) 2.87; 2^20
+//                 (4,4) 17.8, (4,8) 18.7
 constexpr int kFaceLdsBytes = 48 * 1024;
 Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
   const int kern = kernel_of(probs, opt);
   Shape s{std::max(1, lane_elems_of(probs, n, opt)), kern == ADG_KERNEL_FUSED ? std::max(1, fused_steps_of(opt)) : 1};
-  if (kern != ADG_KERNEL_FUSED || is_ldg(probs)) return s;
+  if (kern != ADG_KERNEL_FUSED) return s;
   const int64_t elems = total_elems(probs, n);
   const bool one_launch = opt && (opt->flags & ADG_OPT_ONE_LAUNCH);
   bool all_lin = true, gen = false;
@@ -476,15 +482,17 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   if (one_launch)
     s.elems = 2;
   else if (!opt || opt->lane_elems == 0) {
-    const int64_t two = all_lin ? (int64_t)1 << 16 : (gen ? 0 : (int64_t)1 << 17);
-    const int64_t four = all_lin ? (int64_t)1 << 19 : (int64_t)1 << 18;
+    const bool ldg = is_ldg(probs);
+    const int64_t two = all_lin || ldg ? (int64_t)1 << 16 : (gen ? 0 : (int64_t)1 << 17);
+    const int64_t four = all_lin || ldg ? (int64_t)1 << 19 : (int64_t)1 << 18;
     s.elems = elems >= four ? 4 : (elems >= two ? 2 : 1);
   }
   for (int32_t i = 0; i < n; ++i)
     if (async_of(probs[i]))
       while (probs[i].pe_size % s.elems) s.elems >>= 1;
   if ((opt && opt->fused_steps != 0) || one_launch) return s;
-  const int most_halo = gen ? (elems <= (int64_t)1 << 16 ? 21 : 8)
+  const int most_halo = is_ldg(probs) ? (elems <= (int64_t)1 << 16 ? 24 : 16) / s.elems
+                        : gen ? (elems <= (int64_t)1 << 16 ? 21 : 8)
                         : all_lin ? (elems <= (int64_t)1 << 18 ? 40 : 20) : (elems <= (int64_t)1 << 17 ? 40 : 16);
   auto fits = [&](int K) {
     if (fused_halo((int)probs[0].rk, s.elems, K) > most_halo) return false;
@@ -655,6 +663,7 @@ struct adg_ctx {
     a.elems = L.shape.elems;
     a.steps = K;
     a.halo = fused_halo(rk, L.shape.elems, list_steps(list));
+    a.halo_right = ldg_halo_right(rk, L.shape.elems, list_steps(list));
     a.one_launch = one_launch;
     a.qbuf = L.qbuf >= 0 ? (double*)(ws + L.qbuf) : nullptr;
     return a;
@@ -1052,9 +1061,9 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
         ++n_in;
         const int T = tile_of(p, form, c->L.shape, K);
         for (int64_t t = 0; t < (p.n_elem + T - 1) / T; ++t) wf.push_back(WorkItem{i, (int32_t)t});
-        if (async_of(p) && c->kernel == ADG_KERNEL_FUSED && !is_ldg(probs)) {
+        if (async_of(p)) {
           fr.n_faces = std::max(fr.n_faces, fused_faces(c->L.shape.elems, p.pe_size));
-          fr.lds_words = fused_lds_words(c->S, K, fr.n_faces);
+          fr.lds_words = std::max(fr.lds_words, lds_of(p, c->L.shape.elems, K));
         }
       }
       c->grid[list][gi] = fused_grid((int32_t)wf.size() - b);

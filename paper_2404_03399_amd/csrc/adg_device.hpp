@@ -316,14 +316,6 @@ __device__ __forceinline__ double at_old_levels_sum(const AtLevels& L) {
   return acc;
 }
 
-__device__ __forceinline__ double at_old_levels(const DevProblem& P, const double* __restrict__ rb, int ahead,
-                                                int kd, int slot_n, int depth) {
-  AtLevels L;
-  at_old_levels_load(P, rb, ahead, kd, slot_n, depth, L);
-  return at_old_levels_sum(L);
-}
-
-
 // --------------------------------------------------------------- adjoint ---
 // Butcher form of a 2N scheme: U_s = U + dt sum_{j<=s} beta_{s,j} K_j with
 // beta_{s,j} = sum_{l=j..s} B_l prod_{m=j+1..l} A_m (K_j the operator at

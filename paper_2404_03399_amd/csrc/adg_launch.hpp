@@ -60,6 +60,7 @@ struct StepArgs {
   int32_t elems;             // fused kernel: elements per lane (1, 2 or 4)
   int32_t steps;             // fused kernel: time steps of the launch (a power of two, at most the list's)
   int32_t halo;              // fused kernel: halo lanes per side (upwind, a > 0: on the left) of the work list
+  int32_t halo_right;        // local DG: halo lanes on the right
   double* qbuf;              // local DG: q = u_x of the current stage input (state layout)
   double* umid;              // fused kernel, several steps per launch: also write the states after
                              // the steps before the last here (state layout), or null
@@ -81,13 +82,18 @@ __host__ __device__ constexpr int fused_tile(int rk, int R, int K) { return R * 
 __host__ __device__ constexpr int fused_tile_left(int rk, int R, int K, bool async) {
   return R * (kWave - fused_halo(rk, R, K) - (async ? 1 : 0));
 }
+// Local DG: one halo element more on the right.
+__host__ __device__ constexpr int ldg_halo_right(int rk, int R, int K) { return (K * rk_stages(rk) + R) / R; }
+__host__ __device__ constexpr int ldg_tile_elems(int rk, int R, int K) {
+  return R * (kWave - fused_halo(rk, R, K) - ldg_halo_right(rk, R, K));
+}
 // PE faces of a wave's 64 R elements at most (R divides the PE size, so one per lane)
 __host__ __device__ constexpr int fused_faces(int R, int64_t pe_size) {
   return (int)((kWave * R - 1) / pe_size) + 1;
 }
-// LDS of a wave in doubles (layout: WaveFaces)
-__host__ __device__ constexpr int fused_lds_words(int S, int K, int n_faces) {
-  return n_faces > 0 ? kMaxL * kMaxQ + S + n_faces * (K * S + K + 1) : 0;
+// LDS of a wave in doubles (layout: WaveFaces; V values per face)
+__host__ __device__ constexpr int fused_lds_words(int S, int K, int n_faces, int V) {
+  return n_faces > 0 ? kMaxL * kMaxQ + V * (S + n_faces * K * S) + n_faces * (K + 1) : 0;
 }
 // One range of the linear form (compiled per stage count).
 template <int S>

@@ -91,12 +91,13 @@ struct WaveElems {
 // step from the raw fluxes kept in LDS, the oldest level first in either part.
 // The ring is written once, at the end, by the owner waves: with a depth of at
 // least L + q + K - 2 no level that a wave of the launch reads shares a slot
-// with one written in it.
+// with one written in it.  V values per face share its delays: the flux, and
+// for local DG (V = 2) u-hat, whose ring follows the flux ring.
 //
 // LDS of a wave with up to n_faces PE faces; a job is g = (face K + step) S + stage:
 //   atc [kMaxL][kMaxQ]     the problem's AT weights
-//   at  [job]              sum over the levels before the launch, then with the
-//                          launch's levels, then the raw flux of that step;
+//   at  [value][job]       sum over the levels before the launch, then with the
+//                          launch's levels, then the raw value of that step;
 //                          S doubles more that lanes without a face write to
 //   kd  [face][step] word  delays, byte s = stage s
 //   own [face] word        1 if the wave owns the element right of it
@@ -107,7 +108,7 @@ __device__ __forceinline__ int lane_rank(uint64_t mask) {  // set bits below thi
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-template <int S>
+template <int S, int V = 1>
 struct WaveFaces {
   double* atc;
   double* at;
@@ -115,14 +116,15 @@ struct WaveFaces {
   KdWord* own;
   uint64_t m_pe = 0;  // lanes with a PE face
   bool pe = false;
-  int n_faces_max, n_jobs = 0, depth = 1, slot_n = 0, slot = 0;
+  int n_faces_max, vstride, n_jobs = 0, depth = 1, slot_n = 0, slot = 0;
   uint32_t b0 = 0;  // the wave's first face; its faces are consecutive, as its elements are
 
   // atc_lane: P.atc[0][lane], loaded ahead of the state
   __device__ __forceinline__ WaveFaces(const DevProblem& P, int e_first, bool owns, double atc_lane, int64_t n, int K,
                                        int n_faces_max_, double* lds, int lane)
       : atc(lds), at(lds + kMaxL * kMaxQ), n_faces_max(n_faces_max_) {
-    kd = reinterpret_cast<KdWord*>(at + n_faces_max * K * S + S);
+    vstride = n_faces_max * K * S + S;
+    kd = reinterpret_cast<KdWord*>(at + V * vstride);
     own = kd + n_faces_max * K;
     if (!P.async_faces) return;
     depth = P.depth;
@@ -155,22 +157,29 @@ struct WaveFaces {
         const int ik = g / S, s = g - ik * S, i = ik >> kshift, kk = ik - (i << kshift);
         const uint32_t b = face(P, i);
         const int k = pe_delay(P, n + kk, s, b);
-        const double* __restrict__ rb = ring + P.ring_off + ((int64_t)b * S + s) * depth;
-        double lv[kMaxQ];
+        const int64_t rb = ((int64_t)b * S + s) * depth;
+        double lv[V][kMaxQ];
 #pragma unroll
         for (int j = 0; j < kMaxQ; ++j) {
-          lv[j] = 0.0;
+#pragma unroll
+          for (int v = 0; v < V; ++v) lv[v][j] = 0.0;
           if (j < P.q) {  // uniform
             const int back = k + j - kk;  // level n - back
-            if (k > 0 && back > 0) lv[j] = rb[ring_slot(slot_n, back, depth)];
+            if (k > 0 && back > 0)
+#pragma unroll
+              for (int v = 0; v < V; ++v)
+                lv[v][j] = ring[(v == 0 ? P.ring_off : P.ring2_off) + rb + ring_slot(slot_n, back, depth)];
           }
         }
         reinterpret_cast<uint8_t*>(kd + ik)[s] = (uint8_t)k;
-        double v = 0.0;
+        double sum[V] = {};
 #pragma unroll
         for (int j = kMaxQ - 1; j >= 0; --j)
-          if (j < P.q && k > 0 && k + j > kk) v = fma(atc[k * kMaxQ + j], lv[j], v);
-        at[g] = v;
+          if (j < P.q && k > 0 && k + j > kk)
+#pragma unroll
+            for (int v = 0; v < V; ++v) sum[v] = fma(atc[k * kMaxQ + j], lv[v][j], sum[v]);
+#pragma unroll
+        for (int v = 0; v < V; ++v) at[v * vstride + g] = sum[v];
       }
     }
   }
@@ -179,8 +188,8 @@ struct WaveFaces {
   // (lanes without a face have a place of their own, so that no branch cuts the
   // stages into blocks: with one the linear form took 167 registers instead of
   // 137), and its delays (0 without a face).
-  __device__ __forceinline__ double* sums(int K, int kk) const {
-    return at + ((pe ? slot : n_faces_max) * K + (pe ? kk : 0)) * S;
+  __device__ __forceinline__ double* sums(int K, int kk, int v = 0) const {
+    return at + v * vstride + ((pe ? slot : n_faces_max) * K + (pe ? kk : 0)) * S;
   }
   __device__ __forceinline__ KdWord delays(int K, int kk) const {
     const KdWord w = kd[pe ? slot * K + kk : 0];
@@ -194,7 +203,12 @@ struct WaveFaces {
       const int g = g0 + lane, ik = g / S, later = (ik & (K - 1)) - kk;  // steps to the job's own
       if (g < n_jobs && later > 0) {
         const int k = reinterpret_cast<const uint8_t*>(kd + ik)[g - ik * S], j = later - k;
-        if (k > 0 && j >= 0 && j < P.q) at[g] = fma(atc[k * kMaxQ + j], at[g - later * S], at[g]);
+        if (k > 0 && j >= 0 && j < P.q)
+#pragma unroll
+          for (int v = 0; v < V; ++v) {
+            double* const x = at + v * vstride + g;
+            *x = fma(atc[k * kMaxQ + j], x[-later * S], *x);
+          }
       }
     }
   }
@@ -209,7 +223,9 @@ struct WaveFaces {
         if (own[i]) {
           int sl = slot_n + kk;
           while (sl >= depth) sl -= depth;
-          ring[P.ring_off + ((int64_t)face(P, i) * S + s) * depth + sl] = at[g];
+#pragma unroll
+          for (int v = 0; v < V; ++v)
+            ring[(v == 0 ? P.ring_off : P.ring2_off) + ((int64_t)face(P, i) * S + s) * depth + sl] = at[v * vstride + g];
         }
       }
     }

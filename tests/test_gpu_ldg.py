@@ -204,3 +204,33 @@ def test_two_step_launch_reads_no_level_written_in_it(torch_cuda, scheme, q, pro
         s.close()
     assert np.array_equal(outs[0], outs[1])
     assert stats.rel_l2(outs[1], ref) <= 1e-12, stats.rel_l2(outs[1], ref)
+
+
+@pytest.mark.parametrize("p,rk,scheme,q,per_stage,ne,pe", [
+    (2, "heun", "adg_at", 2, False, 1000, 20), (1, "rk4", "adg_at", 0, True, 260, 4),
+    (3, "ssprk3", "adg", 0, True, 97, 1), (2, "lsrk3", "adg_at", 3, False, 66, 2), (2, "heun", "adg_at", 2, True, 3, 3),
+    (3, "heun", "dg", 0, False, 513, 27)])
+def test_ldg_eight_steps_per_launch_bitwise(torch_cuda, p, rk, scheme, q, per_stage, ne, pe):
+    """The library's own number of steps per launch (up to eight: a halo of
+    several lanes, AT sums that gain up to seven of the launch's own levels,
+    meshes shorter than the halo) and its remainders give bitwise the results
+    of one step per launch for every number of elements per lane."""
+    from paper_2404_03399_amd.solver import Solver
+    w = _w(p, rk, scheme, q, per_stage, ne=ne, pe=pe, seed=ne + 3 * p)
+    u0 = stepper.initial_state(w)
+    n = 47  # 5 x 8 + 4 + 2 + 1
+    _say(f"viscous Burgers LDG launches of up to eight steps p={p} {rk} {scheme} q={q} N={ne} pe={pe} steps={n}")
+    out = {}
+    for R in (1, 2, 4):
+        if scheme != "dg" and R > pe:
+            continue
+        for K in (1, 0):
+            s = Solver(w, kernel="fused", lane_elems=R, fused_steps=K)
+            u = s.pack(u0)
+            s.run(u, n, graph=R == 2)
+            torch_cuda.cuda.synchronize()
+            out[R, K] = s.unpack(u)[0]
+            s.close()
+    for key, v in out.items():
+        assert np.array_equal(v, out[1, 1]), key
+    assert stats.rel_l2(out[1, 0], stepper.Stepper(w).run(u0, n)) <= 1e-12
