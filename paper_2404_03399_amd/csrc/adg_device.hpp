@@ -40,7 +40,7 @@ struct Physics<PHYS_ADV_UPWIND_POS> {
 template <>
 struct Physics<PHYS_ADV_CENTRAL> {
   __device__ static double f(double u, double a) { return a * u; }
-  __device__ static double fhat(double um, double up, double a) { return a * (0.5 * um + 0.5 * up); }
+  __device__ static double fhat(double um, double up, double a) { return (0.5 * a) * (um + up); }
 };
 
 template <>
@@ -52,8 +52,7 @@ struct Physics<PHYS_BURGERS_LLF> {
   __device__ static double fhat(double um, double up, double) {
 #pragma clang fp contract(off)
     const double lam = fmax(fabs(um), fabs(up));
-    const double avg = 0.5 * (fma(0.5 * um, um, (0.5 * up) * up));
-    return fma(-0.5 * lam, up - um, avg);
+    return 0.5 * fma(lam, um - up, 0.5 * fma(um, um, up * up));  // factors of 0.5 where they cost least
   }
 };
 

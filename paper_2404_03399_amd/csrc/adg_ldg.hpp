@@ -49,7 +49,7 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
   WaveFaces<S, 2> wf(P, we.e[0], we.own_n > 0, atc, n, K, n_faces_max, lds, lane);
   wf.draw(P, ring, n, K, lane);
 
-  const double nu = P.nu, dt = P.dt;
+  const double nu2 = 2.0 * P.nu, dt2 = 0.5 * P.dt;
   bool rpe = false;  // the right face of the last element is a PE face
   if (P.async_faces) {
     const uint32_t e1 = (we.e[R - 1] + 1 == (int)P.n_elem) ? 0u : (uint32_t)(we.e[R - 1] + 1);
@@ -70,7 +70,7 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
         for (int j = 0; j < NP; ++j) u0[r][j] = y[r][j];
 #pragma unroll
       for (int s = 0; s < S; ++s) {
-        double um[R], G[R], q[R][NP];
+        double um[R], G[R], v[R][NP];  // G and v = -nu q doubled: no factors of 1/2
         um[0] = lane_from_left(y[R - 1][NP - 1]);  // u- at the left face, and its u-hat
 #pragma unroll
         for (int r = 1; r < R; ++r) um[r] = y[r - 1][NP - 1];
@@ -88,19 +88,18 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const double hl = r == 0 ? hl0 : um[r], hr = r + 1 < R ? y[r][NP - 1] : hr_last;
-          double g[NP];
 #pragma unroll
-          for (int i = 0; i < NP; ++i) {
-            q[r][i] = fma(-kl[i], hl, kr[i] * hr);
-            g[i] = -y[r][i];
-          }
-          fmac_operator<NP>(op, g, q[r]);
-          G[r] = fma(-nu, q[r][0], Physics<PHYS_BURGERS_LLF>::fhat(um[r], y[r][0], 1.0));
+          for (int i = 0; i < NP; ++i) v[r][i] = fma(kl[i], hl, -kr[i] * hr);
+          fmac_operator<NP>(op, y[r], v[r]);  // -q
+#pragma unroll
+          for (int i = 0; i < NP; ++i) v[r][i] *= nu2;
+          const double up = y[r][0], lam = fmax(fabs(um[r]), fabs(up));
+          G[r] = fma(0.5, fma(um[r], um[r], up * up), fma(lam, um[r] - up, v[r][0]));
           __builtin_amdgcn_sched_barrier(0);  // one element after the other
         }
         if constexpr (PE) {
-          mine_g[s] = G[0];
-          G[0] = late ? at_g : G[0];
+          mine_g[s] = 0.5 * G[0];
+          G[0] = late ? 2.0 * at_g : G[0];
         }
         const double g_last = lane_from_right(G[0]);
 #pragma unroll
@@ -109,11 +108,11 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
           double k[NP], g[NP];
 #pragma unroll
           for (int j = 0; j < NP; ++j) {
-            g[j] = fma(0.5 * y[r][j], y[r][j], -nu * q[r][j]);
+            g[j] = fma(y[r][j], y[r][j], v[r][j]);
             k[j] = fma(-kr[j], gr, kl[j] * G[r]);
           }
           fmac_operator<NP>(op, g, k);
-          rk_update<NP, RK>(s, dt, u0[r], y[r], ks[r], k);
+          rk_update<NP, RK>(s, dt2, u0[r], y[r], ks[r], k);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
