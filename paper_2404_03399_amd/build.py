@@ -27,6 +27,9 @@ UNITS = [("adg_fused.hip", ["-DADG_RK=0"] + PRELOAD), ("adg_fused.hip", ["-DADG_
          ("adg_fused.hip", ["-DADG_RK=4"] + PRELOAD),
          ("adg_linear.hip", ["-DADG_S=2"] + PRELOAD), ("adg_linear.hip", ["-DADG_S=3"] + PRELOAD),
          ("adg_linear.hip", ["-DADG_S=4"] + PRELOAD), ("adg_linear.hip", ["-DADG_S=5"] + PRELOAD),
+         ("adg_reverse.hip", ["-DADG_RK=0"] + PRELOAD), ("adg_reverse.hip", ["-DADG_RK=1"] + PRELOAD),
+         ("adg_reverse.hip", ["-DADG_RK=2"] + PRELOAD), ("adg_reverse.hip", ["-DADG_RK=3"] + PRELOAD),
+         ("adg_reverse.hip", ["-DADG_RK=4"] + PRELOAD),
          ("adg_adjoint.hip", []), ("adg_kernels.hip", []), ("adg_api.hip", [])]
 ARCH = "gfx950"
 

@@ -1,6 +1,5 @@
-// Discrete adjoint kernels: one launch per reverse RK stage (RK registers in
-// HBM), the fused reverse step (one launch per step and degree group), and
-// for linear advection without dJ/da two fused reverse steps per launch.
+// Discrete adjoint, stage by stage: one launch per reverse RK stage (RK
+// registers in HBM).
 #include "adg_device.hpp"
 
 namespace adg {
@@ -143,527 +142,6 @@ __global__ __launch_bounds__(kBlock) void k_adj_stage(const DevProblem* __restri
   }
 }
 
-// One reverse RK step of a lane's R consecutive elements in Butcher form:
-// lamp = lambda^{m+1} in, lu = lambda^m out, keep = the forward stage values
-// (FWD, one element per lane).  pe[r]: the left face of element r is a PE
-// face (at most one r per lane); for it kd(s) and adjn(s) give the face's
-// delay at (m, s) and the adjoint already collected for its level-m raw flux,
-// and on_lf(s, lf) receives the face sensitivity to scatter.  Returns the
-// lane's dJ/da share (FWD, advection, owned lanes).  Each element takes the
-// same operations in the same order whatever R (a neighbour's face term comes
-// from the lane's own registers or by a lane shift), and explicit FMAs with
-// contraction off give every kernel that reverses a step the same roundings.
-//
-// PHYS_ADV_UPWIND_POS (upwind, a > 0) transposes the folded forward operator:
-// the interior flux a u_p of an element's right face sits in Kdu, so an
-// element's sensitivity is Kdu^T lambda_K plus a (l_l . lambda_K of the right
-// neighbour) at its last node, and the right lift (l_r . lambda_K) is formed
-// only in waves that hold a PE face, where the applied flux replaces a u_p.
-template <int NP, int RK, int PHYS, bool FWD, int R, class KdF, class AdjF, class LfF>
-__device__ __forceinline__ double adj_reverse(const DevProblem& P, const double (&lamp)[R][NP], double (&lu)[R][NP],
-                                              const double (&keep)[rk_stages(RK)][NP], const bool (&pe)[R],
-                                              bool owned, KdF kd_of, AdjF adjn_of, LfF on_lf) {
-#pragma clang fp contract(off)
-  static_assert(R == 1 || (!FWD && PHYS != PHYS_BURGERS_LLF), "several elements per lane: constant Jacobian only");
-  constexpr int S = rk_stages(RK);
-  constexpr bool POS = PHYS == PHYS_ADV_UPWIND_POS;
-  const double a = P.speed, dt = P.dt;
-  bool any_pe = false;
-#pragma unroll
-  for (int r = 0; r < R; ++r) any_pe = any_pe || pe[r];
-  // POS: the right lifts are needed only where some lane holds a PE face
-  const bool with_cr = !POS || __ballot(any_pe) != 0;  // uniform
-  // Q[r][i] = dt sum_{j>i} a_ji mu_j (dt folded into the stage weights)
-  double Q[R][S][NP];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int j = 0; j < NP; ++j) lu[r][j] = lamp[r][j];
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int s = 0; s < S; ++s)
-#pragma unroll
-      for (int j = 0; j < NP; ++j) Q[r][s][j] = 0.0;
-  double ca = 0.0;
-#pragma unroll
-  for (int s = S - 1; s >= 0; --s) {
-    double lk[R][NP], cl[R], cr[R];
-    const double bs = dt * bt_b<RK>(s);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int i = 0; i < NP; ++i) lk[r][i] = s < S - 1 ? fma(bs, lamp[r][i], Q[r][s][i]) : bs * lamp[r][i];
-      cl[r] = 0.0;
-      cr[r] = 0.0;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) cl[r] = fma(P.Kl[i], lk[r][i], cl[r]);
-      if (with_cr)
-#pragma unroll
-        for (int i = 0; i < NP; ++i) cr[r] = fma(P.Kr[i], lk[r][i], cr[r]);
-    }
-    // raw[r]: sensitivity of the flux applied at element r's left face (both
-    // neighbours' lifts); POS: g[r], what that face gives its left element's
-    // last node, over a
-    double crl[R], raw[R], g[R];  // crl[r]: the right lift of element r's left neighbour
-    if (with_cr) {
-      crl[0] = lane_from_left(cr[R - 1]);
-#pragma unroll
-      for (int r = 1; r < R; ++r) crl[r] = cr[r - 1];
-#pragma unroll
-      for (int r = 0; r < R; ++r) raw[r] = cl[r] - crl[r];
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) g[r] = cl[r];
-    double dm = 0.0, dp = 0.0;
-    if constexpr (PHYS == PHYS_BURGERS_LLF)
-      flux_partials<PHYS>(lane_from_left(keep[s][NP - 1]), keep[s][0], a, dm, dp);
-    else if constexpr (!POS)
-      flux_partials<PHYS>(0.0, 0.0, a, dm, dp);
-    if (any_pe) {  // with_cr holds here
-      double lf = raw[0];
-#pragma unroll
-      for (int r = 1; r < R; ++r) lf = pe[r] ? raw[r] : lf;
-      const int kk = kd_of(s);
-      const double rp = (kk == 0 ? lf : 0.0) + adjn_of(s);
-      on_lf(s, lf);
-      if constexpr (POS) {
-        // the left element's right lift, which Kdu^T took off, comes back
-        // with the raw flux's sensitivity
-#pragma unroll
-        for (int r = 0; r < R; ++r) g[r] = pe[r] ? crl[r] + rp : g[r];
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) raw[r] = pe[r] ? rp : raw[r];
-      }
-    }
-    // the right face of element R-1 is the next lane's first
-    double rdm;
-    if constexpr (POS)
-      rdm = lane_from_right(g[0]);
-    else
-      rdm = lane_from_right(raw[0] * dm);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      double mu[NP];
-#pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        double v = 0.0;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) v = fma((POS ? P.Kdu : P.Kd)[i * kMaxNp + j], lk[r][i], v);
-        if constexpr (PHYS == PHYS_BURGERS_LLF)
-          mu[j] = (2.0 * keep[s][j]) * v;
-        else
-          mu[j] = v;
-      }
-      if constexpr (POS) {
-        mu[NP - 1] = fma(a, r + 1 < R ? g[r + 1] : rdm, mu[NP - 1]);
-      } else {
-        mu[0] = fma(raw[r], dp, mu[0]);
-        mu[NP - 1] += r + 1 < R ? raw[r + 1] * dm : rdm;
-      }
-#pragma unroll
-      for (int j = 0; j < NP; ++j) lu[r][j] += mu[j];
-#pragma unroll
-      for (int i = 0; i < s; ++i) {
-        const double c = bt_a<RK>(s, i);
-        if (c != 0.0) {
-          const double dc = dt * c;
-#pragma unroll
-          for (int j = 0; j < NP; ++j) Q[r][i][j] = fma(dc, mu[j], Q[r][i][j]);
-        }
-      }
-      if constexpr (FWD && PHYS != PHYS_BURGERS_LLF) {
-        if (owned)
-#pragma unroll
-          for (int i = 0; i < NP; ++i) ca = fma(lk[r][i], keep[s][i], ca);
-      }
-    }
-  }
-  return ca;
-}
-
-// adj_reverse in the a > 0 upwind form where the problem has one (a
-// wave-uniform choice), else in the general form of PHYS
-template <int NP, int RK, int PHYS, bool FWD, int R, class KdF, class AdjF, class LfF>
-__device__ __forceinline__ double adj_reverse_form(const DevProblem& P, const double (&lamp)[R][NP],
-                                                   double (&lu)[R][NP], const double (&keep)[rk_stages(RK)][NP],
-                                                   const bool (&pe)[R], bool owned, KdF kd_of, AdjF adjn_of,
-                                                   LfF on_lf) {
-  if constexpr (PHYS == PHYS_ADV_UPWIND) {
-    if (P.speed > 0.0)
-      return adj_reverse<NP, RK, PHYS_ADV_UPWIND_POS, FWD, R>(P, lamp, lu, keep, pe, owned, kd_of, adjn_of, on_lf);
-  }
-  return adj_reverse<NP, RK, PHYS, FWD, R>(P, lamp, lu, keep, pe, owned, kd_of, adjn_of, on_lf);
-}
-
-// Per-lane PE-face values of a reverse step (lane = the PE lane they belong
-// to): delay, AT sum of past levels (forward recompute), and the adjoint
-// already collected for the level-n raw flux, replaced once read by the flux
-// sensitivity to scatter.
-template <int S>
-struct AdjSmem {
-  uint8_t kd[kWavesPerBlock][S][kWave];
-  double atf[kWavesPerBlock][S][kWave];
-  double adjn[kWavesPerBlock][S][kWave];
-};
-
-// ------------------------------------------------------ fused adjoint step ---
-// Reverse of one whole RK step n in one launch: one wave64 per tile of
-// T = 64 - 2H owned elements with H halo lanes per side, one element per lane.
-// The forward stages are recomputed on chip from u^n (keeping what the reverse
-// needs: the stage operator values K_i for the speed gradient of advection,
-// the stage inputs Y_i for the Burgers Jacobian), then the stages are reversed
-// in Butcher form with the face terms exchanged between lanes:
-//   lambda_K,i = dt (b_i lambda^{n+1} + sum_{j>i} a_ji mu_j),
-//   mu_i = (dK_i/dY_i)^T lambda_K,i,   lambda^n = lambda^{n+1} + sum_i mu_i.
-// Each reverse stage widens the dependence by one element per side, so after
-// S stages the owned lanes are exact when the Jacobian is constant (linear
-// advection, H = S).  For Burgers reverse stage s also reads the stage input
-// Y_s one lane further out, which is exact only s lanes in from the wave's
-// edge: H = 2S - 1.  PE faces take the transposed AT
-// combination: the delayed levels' weights go to the adjoint ring (levels
-// below n, deposited by the owner lane only), the raw level-n flux collects
-// its synchronous share plus what later steps deposited at level n.
-template <int NP, int RK, int PHYS, bool FWD>
-__device__ __forceinline__ void adj_tile(const DevProblem& P, const WorkItem wi, int w, int lane, int32_t n,
-                                         const double* __restrict__ uin, const double* __restrict__ lam,
-                                         double* __restrict__ lamo, const double* __restrict__ ring,
-                                         double* __restrict__ adjring, double* __restrict__ cpart,
-                                         AdjSmem<rk_stages(RK)>& sm, int wv) {
-  constexpr int S = rk_stages(RK);
-  constexpr int HL = adj_halo(RK, PHYS == PHYS_BURGERS_LLF);
-  constexpr int T = kWave - 2 * HL;
-  const int N = (int)P.n_elem;
-  const int e0 = wi.tile * T;
-  const int teff = (N - e0) < T ? (N - e0) : T;
-  const int x = e0 - HL + lane;
-  const int e = N < kWave ? wrap_elem(x, N) : wrap_once(x, N);
-  const bool owned = lane >= HL && lane < kWave - HL && (x - e0) < teff;
-  const int64_t ld = P.ld;
-  const double* __restrict__ lp = lam + P.u_off;
-  double u0[NP], lamp[1][NP];
-  // plane accesses through buffer resources (lane byte offset in a VGPR, the
-  // plane's in an SGPR) where the problem's planes span less than 2 GiB
-  const bool buffered = (int64_t)P.np * ld < (int64_t)1 << 28;
-  const int voff = e * 8;
-  if (buffered) {
-    const __amdgpu_buffer_rsrc_t rl = plane_rsrc(lp);
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      if constexpr (FWD)
-        u0[j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(plane_rsrc(uin + P.u_off), voff,
-                                                                                (int)(8 * j * ld), 0));
-      lamp[0][j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rl, voff, (int)(8 * j * ld), 0));
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      if constexpr (FWD) u0[j] = uin[P.u_off + j * ld + e];
-      lamp[0][j] = lp[j * ld + e];
-    }
-  }
-
-  // PE face on this lane's left face.  Its delays of step n, the applied AT
-  // sums of past levels and the adjoint already collected for the level-n raw
-  // fluxes are formed by job lanes, one per (PE lane, stage), with one memory
-  // round trip for the whole wave.
-  bool pe = false;
-  uint32_t b = 0;
-  int depth = 1, slot_n = 0;
-  if (P.async_faces) {
-    depth = P.depth;
-    slot_n = (int)((uint32_t)n - fast_div((uint32_t)n, P.depth_div) * (uint32_t)depth);
-    b = fast_div((uint32_t)e, P.pe_div);
-    pe = (uint32_t)e == b * P.pe_div.d;
-  }
-  const uint64_t m_pe = __ballot(pe);
-  const int n_jobs = S * __builtin_popcountll(m_pe);
-  for (int g0 = 0; g0 < n_jobs; g0 += kWave) {  // uniform
-    const int g = g0 + lane;
-    const int i = g / S, s = g - i * S;
-    const int tgt = nth_set_lane(m_pe, i);
-    const uint32_t face = (uint32_t)__shfl((int)b, tgt);  // every lane active
-    if (g < n_jobs) {
-      const int kd = pe_delay(P, n, s, face);
-      const int64_t rb = P.ring_off + ((int64_t)face * S + s) * depth;
-      // every load of the job before the first LDS write waits for one
-      const double adjn = adjring[rb + slot_n];
-      AtLevels lv;
-      if constexpr (FWD) at_old_levels_load(P, ring + rb, 0, kd, slot_n, depth, lv);
-      sm.kd[wv][s][tgt] = (uint8_t)kd;
-      sm.adjn[wv][s][tgt] = adjn;
-      if constexpr (FWD) sm.atf[wv][s][tgt] = at_old_levels_sum(lv);
-    }
-  }
-
-  // forward stages, keeping K_s (advection) or Y_s (Burgers) in registers
-  // (a per-lane LDS copy lowers the occupancy further and measured slower)
-  const double a = P.speed, dt = P.dt;
-  double keep[S][NP];
-  auto kept = [&](int s, int j) -> double& { return keep[s][j]; };
-  if constexpr (FWD) {
-    double y[NP], ks[NP], k[NP];
-#pragma unroll
-    for (int j = 0; j < NP; ++j) y[j] = u0[j];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-      double F = Physics<PHYS>::fhat(lane_from_left(y[NP - 1]), y[0], a);
-      if (pe && sm.kd[wv][s][lane] > 0) F = sm.atf[wv][s][lane];
-      folded_rhs<NP, PHYS>(P, y, F, lane_from_right(F), k);
-#pragma unroll
-      for (int j = 0; j < NP; ++j) kept(s, j) = PHYS == PHYS_BURGERS_LLF ? y[j] : k[j];
-      if (s + 1 < S) rk_update<NP, RK>(s, dt, u0, y, ks, k);
-    }
-  }
-
-  // reverse stages
-  double lu[1][NP];
-  const bool pe1[1] = {pe};
-  const double ca = adj_reverse_form<NP, RK, PHYS, FWD, 1>(
-      P, lamp, lu, keep, pe1, owned, [&](int s) { return (int)sm.kd[wv][s][lane]; },
-      [&](int s) { return sm.adjn[wv][s][lane]; }, [&](int s, double lf) { sm.adjn[wv][s][lane] = lf; });
-
-  double* __restrict__ lo = lamo + P.u_off;
-  if (owned) {
-    if (buffered) {
-      const __amdgpu_buffer_rsrc_t ro = plane_rsrc(lo);
-#pragma unroll
-      for (int j = 0; j < NP; ++j)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(BufWord2, lu[0][j]), ro, voff, (int)(8 * j * ld), 0);
-    } else {
-#pragma unroll
-      for (int j = 0; j < NP; ++j) lo[j * ld + e] = lu[0][j];
-    }
-  }
-
-  // the delayed levels' share of the AT sensitivities into the adjoint ring
-  // (levels below n, which nothing in this launch reads), one job lane per
-  // (owned PE lane, stage, level); each ring entry is touched once
-  const uint64_t m_own = __ballot(pe && owned);
-  const int n_sc = S * kMaxQ * __builtin_popcountll(m_own);
-  for (int g0 = 0; g0 < n_sc; g0 += kWave) {  // uniform
-    const int g = g0 + lane;
-    const int i = g / (S * kMaxQ), r = g - i * (S * kMaxQ), s = r / kMaxQ, j = r - s * kMaxQ;
-    const int tgt = nth_set_lane(m_own, i);
-    const uint32_t face = (uint32_t)__shfl((int)b, tgt);  // every lane active
-    if (g < n_sc) {
-      const int kk = sm.kd[wv][s][tgt];
-      if (kk > 0 && j < P.q) {
-        double* __restrict__ at = adjring + P.ring_off + ((int64_t)face * S + s) * depth + ring_slot(slot_n, kk + j, depth);
-        *at = fma(P.atc[kk][j], sm.adjn[wv][s][tgt], *at);
-      }
-    }
-  }
-
-  // dJ/da share of this tile: every term of K is proportional to a for linear
-  // advection, so dK/da = K / a with the stage inputs held fixed.  Fixed
-  // butterfly order: deterministic.
-  if constexpr (FWD && PHYS != PHYS_BURGERS_LLF) {
-    double cs = ca;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) cs += __shfl_xor(cs, o, kWave);
-    if (lane == 0) cpart[w] += cs / a;
-  }
-}
-
-// Two reverse steps per launch without the forward stages (linear
-// advection, dJ/du0 only): lambda^n from lambda^{n+2}, a halo of 2S elements
-// per side, R consecutive elements per lane as in the fused step.  Step n+1
-// is reversed first.  Its PE-face sensitivity with delay 1 lands at level n,
-// which step n reads in the same launch: every lane holding that face adds it
-// to its own copy of step n's collected adjoint (the same FMA the adjoint
-// ring would take) instead of waiting for the ring.  At the end one job lane
-// per (owned PE element, stage, level below n) adds both steps' shares to the
-// adjoint ring, step n+1's first, so each entry is touched once per launch
-// and sums in the order of one step per launch.  A PE size of at least R puts
-// at most one PE face on a lane.
-template <int S>
-struct AdjSmem2 {
-  uint8_t kd[2][kWavesPerBlock][S][kWave];
-  double adjn[2][kWavesPerBlock][S][kWave];  // collected adjoint, then (once read) the sensitivity lf
-};
-
-template <int NP, int RK, int PHYS, int R>
-__device__ __forceinline__ void adj_tile2(const DevProblem& P, const WorkItem wi, int lane, int32_t n,
-                                          const double* __restrict__ lam, double* __restrict__ lamo,
-                                          double* __restrict__ adjring, AdjSmem2<rk_stages(RK)>& sm, int wv) {
-  constexpr int S = rk_stages(RK);
-  constexpr int HL = adj_halo2(RK, R);
-  constexpr int T = adj_tile_elems2(RK, R);
-  const int N = (int)P.n_elem;
-  const int e0 = wi.tile * T;
-  const int teff = (N - e0) < T ? (N - e0) : T;
-  const int xb = e0 - R * HL;  // element position of lane 0, element 0
-  const bool lane_owned = lane >= HL && lane < kWave - HL;
-  const bool tiny = N < kWave * R;  // the wave's extent may wrap more than once
-  int e[R];
-  bool owned[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int x = xb + R * lane + r;
-    e[r] = tiny ? wrap_elem(x, N) : wrap_once(x, N);
-    owned[r] = lane_owned && (x - e0) < teff;
-  }
-  // with N a multiple of R a lane's elements never straddle the periodic wrap
-  const bool grouped = R > 1 && (N % R) == 0;
-  const int64_t ld = P.ld;
-  const double* __restrict__ lp = lam + P.u_off;
-  double lamp[R][NP];
-  // a grouped lane's planes as 16-byte pieces through a buffer resource (the
-  // problem's planes must span less than 2 GiB)
-  const bool buffered = grouped && (int64_t)P.np * ld < (int64_t)1 << 28;
-  const int voff = e[0] * 8;
-  if (buffered) {
-    const __amdgpu_buffer_rsrc_t rl = plane_rsrc(lp);
-#pragma unroll
-    for (int j = 0; j < NP; ++j)
-#pragma unroll
-      for (int r = 0; r < R; r += 2) {
-        const double2 v = __builtin_bit_cast(double2,
-                                             __builtin_amdgcn_raw_buffer_load_b128(rl, voff + 8 * r, (int)(8 * j * ld), 0));
-        lamp[r][j] = v.x;
-        lamp[r + 1 < R ? r + 1 : r][j] = v.y;  // R >= 2 here
-      }
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int j = 0; j < NP; ++j) lamp[r][j] = lp[j * ld + e[r]];
-  }
-
-  bool pe[R];
-  bool own_pe = false;  // the lane owns the element right of its PE face
-  uint32_t b = 0;
-  int depth = 1, slot_n = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) pe[r] = false;
-  if (P.async_faces) {
-    depth = P.depth;
-    slot_n = (int)((uint32_t)n - fast_div((uint32_t)n, P.depth_div) * (uint32_t)depth);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const uint32_t br = fast_div((uint32_t)e[r], P.pe_div);
-      pe[r] = (uint32_t)e[r] == br * P.pe_div.d;
-      if (pe[r]) b = br;
-      own_pe = own_pe || (pe[r] && owned[r]);
-    }
-  }
-  bool any_pe = false;
-#pragma unroll
-  for (int r = 0; r < R; ++r) any_pe = any_pe || pe[r];
-  // delays and collected adjoint of levels n+1 (t = 0) and n (t = 1), one job
-  // lane per (PE lane, step, stage)
-  const uint64_t m_pe = __ballot(any_pe);
-  const int n_jobs = 2 * S * __builtin_popcountll(m_pe);
-  for (int g0 = 0; g0 < n_jobs; g0 += kWave) {  // uniform
-    const int g = g0 + lane;
-    const int i = g / (2 * S), r = g - i * (2 * S), t = r / S, s = r - t * S;
-    const int tgt = nth_set_lane(m_pe, i);
-    const uint32_t face = (uint32_t)__shfl((int)b, tgt);  // every lane active
-    if (g < n_jobs) {
-      const int32_t m = n + 1 - t;
-      const int kd = pe_delay(P, m, s, face);
-      const int slot_m = t == 0 ? (slot_n + 1 == depth ? 0 : slot_n + 1) : slot_n;
-      sm.kd[t][wv][s][tgt] = (uint8_t)kd;
-      sm.adjn[t][wv][s][tgt] = adjring[P.ring_off + ((int64_t)face * S + s) * depth + slot_m];
-    }
-  }
-
-  const double keep[S][NP] = {};  // no forward stages: the Jacobian is constant
-  double l1[R][NP], l0[R][NP];
-  // step n + 1: a delay of 1 deposits c_0(1) lf at level n, which step n reads
-  adj_reverse_form<NP, RK, PHYS, false, R>(
-      P, lamp, l1, keep, pe, false, [&](int s) { return (int)sm.kd[0][wv][s][lane]; },
-      [&](int s) { return sm.adjn[0][wv][s][lane]; },
-      [&](int s, double lf) {
-        sm.adjn[0][wv][s][lane] = lf;
-        if (sm.kd[0][wv][s][lane] == 1) sm.adjn[1][wv][s][lane] = fma(P.atc[1][0], lf, sm.adjn[1][wv][s][lane]);
-      });
-  adj_reverse_form<NP, RK, PHYS, false, R>(
-      P, l1, l0, keep, pe, false, [&](int s) { return (int)sm.kd[1][wv][s][lane]; },
-      [&](int s) { return sm.adjn[1][wv][s][lane]; }, [&](int s, double lf) { sm.adjn[1][wv][s][lane] = lf; });
-
-  double* __restrict__ lo = lamo + P.u_off;
-  bool all_owned = true;
-#pragma unroll
-  for (int r = 0; r < R; ++r) all_owned = all_owned && owned[r];
-  if (buffered && all_owned) {
-    const __amdgpu_buffer_rsrc_t ro = plane_rsrc(lo);
-#pragma unroll
-    for (int j = 0; j < NP; ++j)
-#pragma unroll
-      for (int r = 0; r < R; r += 2) {
-        double2 v;
-        v.x = l0[r][j];
-        v.y = l0[r + 1 < R ? r + 1 : r][j];
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(BufWord4, v), ro, voff + 8 * r, (int)(8 * j * ld), 0);
-      }
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (owned[r])
-#pragma unroll
-        for (int j = 0; j < NP; ++j) lo[j * ld + e[r]] = l0[r][j];
-  }
-
-  // levels n - d of each owned PE face and stage that either step reaches:
-  // d >= 1 up to (L - 1) + (q - 1), taken at the largest L and q
-  constexpr int W = (kMaxL - 1) + (kMaxQ - 1);
-  const uint64_t m_own = __ballot(own_pe);
-  const int n_sc = S * W * __builtin_popcountll(m_own);
-  for (int g0 = 0; g0 < n_sc; g0 += kWave) {  // uniform
-    const int g = g0 + lane;
-    const int i = g / (S * W), r = g - i * (S * W), s = r / W, d = 1 + (r - s * W);
-    const int tgt = nth_set_lane(m_own, i);
-    const uint32_t face = (uint32_t)__shfl((int)b, tgt);  // every lane active
-    if (g < n_sc) {
-      const int k1 = sm.kd[0][wv][s][tgt], k0 = sm.kd[1][wv][s][tgt];
-      const int j1 = 1 + d - k1, j0 = d - k0;  // level n - d from step n+1 and from step n
-      const bool u1 = k1 > 0 && j1 >= 0 && j1 < P.q, u0 = k0 > 0 && j0 >= 0 && j0 < P.q;
-      if ((u1 || u0) && d < depth) {
-        double* __restrict__ at = adjring + P.ring_off + ((int64_t)face * S + s) * depth + ring_slot(slot_n, d, depth);
-        double v = *at;
-        if (u1) v = fma(P.atc[k1][j1], sm.adjn[0][wv][s][tgt], v);
-        if (u0) v = fma(P.atc[k0][j0], sm.adjn[1][wv][s][tgt], v);
-        *at = v;
-      }
-    }
-  }
-}
-
-template <int NP, int RK, int PHYS, int R>
-__global__ __launch_bounds__(kBlock) void k_adj_fused2(const DevProblem* __restrict__ probs,
-                                                       const WorkItem* __restrict__ work, int32_t w_begin,
-                                                       int32_t w_end, const double* __restrict__ lam,
-                                                       double* __restrict__ lamo, double* __restrict__ adjring,
-                                                       int32_t n) {
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int lane = (int)(threadIdx.x % kWave);
-  const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
-  if (w >= w_end) return;  // whole wave
-  __shared__ AdjSmem2<rk_stages(RK)> sm;
-  const WorkItem wi = work[w];
-  adj_tile2<NP, RK, PHYS, R>(probs[wi.prob], wi, lane, n, lam, lamo, adjring, sm, wv);
-}
-
-template <int NP, int RK, int PHYS, bool FWD>
-__global__ __launch_bounds__(kBlock) void k_adj_fused(const DevProblem* __restrict__ probs,
-                                                      const WorkItem* __restrict__ work, int32_t w_begin,
-                                                      int32_t w_end, const double* __restrict__ u,
-                                                      const double* __restrict__ lam, double* __restrict__ lamo,
-                                                      const double* __restrict__ ring,
-                                                      double* __restrict__ adjring, double* __restrict__ cpart,
-                                                      int32_t n) {
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int lane = (int)(threadIdx.x % kWave);
-  const int w = w_begin + xcd_block((int)blockIdx.x, (int)gridDim.x) * kWavesPerBlock + wv;
-  if (w >= w_end) return;  // whole wave
-  __shared__ AdjSmem<rk_stages(RK)> sm;
-  const WorkItem wi = work[w];
-  adj_tile<NP, RK, PHYS, FWD>(probs[wi.prob], wi, w, lane, n, u, lam, lamo, ring, adjring, cpart, sm, wv);
-}
-
 template <int RK, int PHYS, int SI>
 static void adj_go(const StepArgs& a, const AdjPtrs& p, int32_t n, hipStream_t st) {
   hipLaunchKernelGGL((k_adj_stage<RK, PHYS, SI>), dim3(a.n_work), dim3(kBlock), 0, st, a.probs, a.work, p, n);
@@ -699,105 +177,6 @@ hipError_t launch_adj_stage(int rk, int phys, int stage, const StepArgs& a, cons
     case RK_LS3: adj_phys<RK_LS3>(phys, stage, a, p, n, stream); break;
     case RK_LS4: adj_phys<RK_LS4>(phys, stage, a, p, n, stream); break;
     default: adj_phys<RK_RK4>(phys, stage, a, p, n, stream); break;
-  }
-  return hipGetLastError();
-}
-
-template <int RK, int PHYS, bool FWD>
-static void adj_fused_go(const AdjArgs& a, const double* u, const double* lam, double* lamo, const double* ring,
-                         double* adjring, double* cpart, int32_t n, hipStream_t st) {
-  for (int gi = 0; gi < 4; ++gi) {
-    const int32_t wb = a.group[gi], we = a.group[gi + 1];
-    if (we <= wb) continue;
-    const dim3 grid(a.grid[gi]), block(kBlock);
-    switch (gi) {
-      case 0: hipLaunchKernelGGL((k_adj_fused<5, RK, PHYS, FWD>), grid, block, 0, st, a.probs, a.work, wb, we, u,
-                                 lam, lamo, ring, adjring, cpart, n); break;
-      case 1: hipLaunchKernelGGL((k_adj_fused<4, RK, PHYS, FWD>), grid, block, 0, st, a.probs, a.work, wb, we, u,
-                                 lam, lamo, ring, adjring, cpart, n); break;
-      case 2: hipLaunchKernelGGL((k_adj_fused<3, RK, PHYS, FWD>), grid, block, 0, st, a.probs, a.work, wb, we, u,
-                                 lam, lamo, ring, adjring, cpart, n); break;
-      default: hipLaunchKernelGGL((k_adj_fused<2, RK, PHYS, FWD>), grid, block, 0, st, a.probs, a.work, wb, we, u,
-                                  lam, lamo, ring, adjring, cpart, n); break;
-    }
-  }
-}
-
-// Linear advection needs the forward stages only for dJ/da (u == nullptr:
-// skipped); Burgers always needs them for its Jacobian.
-template <int RK>
-static void adj_fused_rk(int phys, const AdjArgs& a, const double* u, const double* lam, double* lamo,
-                         const double* ring, double* adjring, double* cpart, int32_t n, hipStream_t st) {
-  const bool fwd = u != nullptr;
-  switch (phys) {
-    case PHYS_ADV_CENTRAL:
-      if (fwd) adj_fused_go<RK, PHYS_ADV_CENTRAL, true>(a, u, lam, lamo, ring, adjring, cpart, n, st);
-      else adj_fused_go<RK, PHYS_ADV_CENTRAL, false>(a, u, lam, lamo, ring, adjring, cpart, n, st);
-      break;
-    case PHYS_BURGERS_LLF: adj_fused_go<RK, PHYS_BURGERS_LLF, true>(a, u, lam, lamo, ring, adjring, cpart, n, st); break;
-    default:
-      if (fwd) adj_fused_go<RK, PHYS_ADV_UPWIND, true>(a, u, lam, lamo, ring, adjring, cpart, n, st);
-      else adj_fused_go<RK, PHYS_ADV_UPWIND, false>(a, u, lam, lamo, ring, adjring, cpart, n, st);
-      break;
-  }
-}
-
-template <int RK, int PHYS, int R>
-static void adj_fused2_go(const AdjArgs& a, const double* lam, double* lamo, double* adjring, int32_t n,
-                          hipStream_t st) {
-  for (int gi = 0; gi < 4; ++gi) {
-    const int32_t wb = a.group[gi], we = a.group[gi + 1];
-    if (we <= wb) continue;
-    const dim3 grid(a.grid[gi]), block(kBlock);
-    switch (gi) {
-      case 0: hipLaunchKernelGGL((k_adj_fused2<5, RK, PHYS, R>), grid, block, 0, st, a.probs, a.work, wb, we, lam,
-                                 lamo, adjring, n); break;
-      case 1: hipLaunchKernelGGL((k_adj_fused2<4, RK, PHYS, R>), grid, block, 0, st, a.probs, a.work, wb, we, lam,
-                                 lamo, adjring, n); break;
-      case 2: hipLaunchKernelGGL((k_adj_fused2<3, RK, PHYS, R>), grid, block, 0, st, a.probs, a.work, wb, we, lam,
-                                 lamo, adjring, n); break;
-      default: hipLaunchKernelGGL((k_adj_fused2<2, RK, PHYS, R>), grid, block, 0, st, a.probs, a.work, wb, we, lam,
-                                  lamo, adjring, n); break;
-    }
-  }
-}
-
-template <int RK, int PHYS>
-static void adj_fused2_r(const AdjArgs& a, const double* lam, double* lamo, double* adjring, int32_t n,
-                         hipStream_t st) {
-  if (a.lane_elems == 2) adj_fused2_go<RK, PHYS, 2>(a, lam, lamo, adjring, n, st);
-  else adj_fused2_go<RK, PHYS, 1>(a, lam, lamo, adjring, n, st);
-}
-
-template <int RK>
-static void adj_fused2_rk(int phys, const AdjArgs& a, const double* lam, double* lamo, double* adjring, int32_t n,
-                          hipStream_t st) {
-  if (phys == PHYS_ADV_CENTRAL) adj_fused2_r<RK, PHYS_ADV_CENTRAL>(a, lam, lamo, adjring, n, st);
-  else adj_fused2_r<RK, PHYS_ADV_UPWIND>(a, lam, lamo, adjring, n, st);
-}
-
-hipError_t launch_adj_fused2(int rk, int phys, const AdjArgs& a, const double* lam, double* lamo, double* adjring,
-                             int32_t n, hipStream_t stream) {
-  if (phys == PHYS_BURGERS_LLF) return hipErrorInvalidValue;  // the Burgers Jacobian needs the forward stages
-  if (a.lane_elems != 1 && a.lane_elems != 2) return hipErrorInvalidValue;
-  switch (rk) {
-    case RK_HEUN: adj_fused2_rk<RK_HEUN>(phys, a, lam, lamo, adjring, n, stream); break;
-    case RK_SSP3: adj_fused2_rk<RK_SSP3>(phys, a, lam, lamo, adjring, n, stream); break;
-    case RK_LS3: adj_fused2_rk<RK_LS3>(phys, a, lam, lamo, adjring, n, stream); break;
-    case RK_LS4: adj_fused2_rk<RK_LS4>(phys, a, lam, lamo, adjring, n, stream); break;
-    default: adj_fused2_rk<RK_RK4>(phys, a, lam, lamo, adjring, n, stream); break;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_adj_fused(int rk, int phys, const AdjArgs& a, const double* u, const double* lam, double* lamo,
-                            const double* ring, double* adjring, double* cpart, int32_t n, hipStream_t stream) {
-  switch (rk) {
-    case RK_HEUN: adj_fused_rk<RK_HEUN>(phys, a, u, lam, lamo, ring, adjring, cpart, n, stream); break;
-    case RK_SSP3: adj_fused_rk<RK_SSP3>(phys, a, u, lam, lamo, ring, adjring, cpart, n, stream); break;
-    case RK_LS3: adj_fused_rk<RK_LS3>(phys, a, u, lam, lamo, ring, adjring, cpart, n, stream); break;
-    case RK_LS4: adj_fused_rk<RK_LS4>(phys, a, u, lam, lamo, ring, adjring, cpart, n, stream); break;
-    default: adj_fused_rk<RK_RK4>(phys, a, u, lam, lamo, ring, adjring, cpart, n, stream); break;
   }
   return hipGetLastError();
 }

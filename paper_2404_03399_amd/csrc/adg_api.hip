@@ -339,14 +339,16 @@ struct Shape {
 
 struct Layout {
   Shape shape;               // launch shape of the fused kernel
+  Shape adj[2];              // of the fused reverse sweep, per list
   int depth_steps;           // steps per launch that the ring holds
   int64_t lin, lin_doubles;  // tables of the linear form
   int64_t probs, work_f, work_f2, work_s, first_s, ctr, ring, state2, y0, y1, acc, qbuf, part, stats_out;
   int64_t groups, gstats;  // ensemble statistics: group CSR (2n+1 int32) and 4 doubles per group
   // adjoint recording (-1 if not recording)
-  int64_t ckpt, useg, ybuf, lam, q, adjring, cpart, work_a, work_a2;
+  int64_t ckpt, useg, ybuf, lam, q, adjring, cpart, work_a[2];
   int64_t total;
-  int32_t n_work_f, n_work_f2, n_work_s, n_work_a, n_work_a2;
+  int32_t n_work_f, n_work_f2, n_work_s, n_work_a[2];
+  int64_t n_parts;  // partial sums of dJ/da of the fused reverse sweep
   int64_t total_doubles;
   int64_t ring_doubles;
   int64_t n_rec, ckpt_every, n_ckpt;
@@ -412,12 +414,6 @@ bool pe_split_of(const adg_problem* probs, int32_t n, const adg_options* opt) {
   }
   return any;
 }
-// linear advection can reverse two steps per launch (no forward stages needed)
-bool adj_two_steps(const adg_problem* probs) { return probs[0].equation == ADG_EQ_ADVECTION; }
-// elements per lane of the two-step reverse: the forward's, at most 2 (its
-// reverse stages keep R sets of Butcher accumulators in registers)
-int adj_lane_elems(int lane_elems) { return lane_elems >= 2 ? 2 : 1; }
-
 int64_t total_elems(const adg_problem* probs, int32_t n) {
   int64_t t = 0;
   for (int32_t i = 0; i < n; ++i) t += probs[i].n_elem;
@@ -506,10 +502,60 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   return s;
 }
 
+// Lists of the fused reverse sweep: with the forward stages, and (advection
+// only) without them, for dJ/du0 alone.
+enum AdjList : int { ADJ_FWD = 0, ADJ_LINEAR = 1 };
+
+// Its elements per lane R (at most the PE size) and the steps per launch K of
+// the list, like the forward kernels'.  With dJ/da the two are equal, so that a
+// wave owns whole tiles of the partial sums; four of either would take two
+// thirds of the registers for the forward stages alone.
+// Measured, us per step of a reverse sweep of 16, PE 256 (R and K in brackets):
+//   with dJ/da    p = 3, RK4, 2^20 elements (1,1) 33.1, (2,2) 23.5
+//   dJ/du0 alone  p = 3, RK4 2^12 (1,4) 2.35, (2,2) 3.61, (2,8) 2.35; 2^16 2.80,
+//                 3.89, 2.64; 2^18 (2,2) 6.27, (2,4) 5.04, (2,8) 5.04, (4,8) 5.26;
+//                 2^20 (2,4) 12.4, (2,8) 14.9, (4,8) 12.7; 2^22 (2,4) 42.6, (4,8)
+//                 42.0; central, SSP-RK3, p = 2 2^20 (2,4) 8.9, (2,8) 9.0, (4,8) 7.7;
+//                 2^20, LSRK3 p = 4 (2,4) 12.8, (4,8) 11.1; LSRK4 p = 2 (2,4) 14.1,
+//                 (4,4) 12.5, p = 3 (2,4) 17.0, (4,4) 18.9, p = 4 (2,2) 22.3, (2,4) 21.3
+//   Burgers       SSP-RK3, p = 2 2^12 (1,4) 4.62, (2,4) 4.86, (2,8) 4.32; 2^16 5.29,
+//                 5.20, 4.80; 2^18 10.3, 9.75, 9.88; 2^20 (2,2) 27.7, (2,4) 24.8,
+//                 (2,8) 26.5; RK4, p = 3 2^16 (1,4) 7.39, (2,4) 6.55, (2,8) 7.32
+Shape adj_shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int list) {
+  const bool nl = probs[0].equation == ADG_EQ_BURGERS, speed = list == ADJ_FWD && !nl;
+  const int rk = (int)probs[0].rk, steps = opt ? (int)opt->fused_steps : 0, lanes = opt ? (int)opt->lane_elems : 0;
+  const int64_t elems = total_elems(probs, n);
+  Shape s{2, 2};
+  int work = 0;  // the most nodes times stages, which the registers go with
+  for (int32_t i = 0; i < n; ++i) work = std::max(work, ((int)probs[i].degree + 1) * rk_stages(rk));
+  s.elems = speed ? (steps == 1 ? 1 : 2) : lanes != 0 ? lanes : (elems >= (int64_t)1 << 19 && work <= 15 ? 4 : 2);
+  if (list == ADJ_FWD) s.elems = std::min(s.elems, 2);
+  for (int32_t i = 0; i < n; ++i)
+    if (async_of(probs[i]))
+      while (probs[i].pe_size < s.elems) s.elems >>= 1;
+  if (speed || steps != 0) {
+    s.kmax = speed ? s.elems : steps;
+    return s;
+  }
+  const bool small = elems <= (int64_t)1 << 17;
+  const int most_halo = nl ? (small ? 13 : 10) : (small ? 20 : 12);
+  auto fits = [&](int K) {
+    if (adj_halo(rk, nl, s.elems, K) > most_halo) return false;
+    for (int32_t i = 0; i < n; ++i) {
+      const int faces = async_of(probs[i]) ? fused_faces(s.elems, probs[i].pe_size) : 0;
+      if (8 * kWavesPerBlock * adj_lds_words(rk_stages(rk), s.elems, K, faces, list == ADJ_FWD, false) > kFaceLdsBytes)
+        return false;
+    }
+    return true;
+  };
+  s.kmax = kMaxSteps;
+  while (s.kmax > 1 && !fits(s.kmax)) s.kmax >>= 1;
+  return s;
+}
+
 Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
   Layout L{};
   const int S = rk_stages((int)probs[0].rk);
-  const int R = std::max(1, lane_elems_of(probs, n, opt));
   const int kern = kernel_of(probs, opt);
   L.shape = shape_of(probs, n, opt, n_rec);
   // the list of several steps also where the option asks for one: the
@@ -523,9 +569,13 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   const int RK2 = std::max(2, rs.kmax);
   L.depth_steps = std::max(K2, RK2);
   std::set<LinKey> tables;
-  const int T1 = adj_tile_elems((int)probs[0].rk, probs[0].equation == ADG_EQ_BURGERS);
-  const int TA2 = adj_tile_elems2((int)probs[0].rk, adj_lane_elems(R));
-  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa = 0, nwa2 = 0, tot = 0, ring = 0, room1 = 0, room2 = 0,
+  const bool nl = probs[0].equation == ADG_EQ_BURGERS;
+  int TA[2];
+  for (int list = 0; list < 2; ++list) {
+    L.adj[list] = adj_shape_of(probs, n, opt, list);
+    TA[list] = adj_tile_elems((int)probs[0].rk, nl, L.adj[list].elems, L.adj[list].kmax);
+  }
+  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa[2] = {0, 0}, tot = 0, ring = 0, room1 = 0, room2 = 0,
           win[2] = {0, 0};
   const bool split = pe_split_of(probs, n, opt);
   for (int32_t i = 0; i < n; ++i) {
@@ -538,8 +588,8 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
     room1 += std::max(t1, tiles(tile_of(p, form, rs, 1)));
     room2 += std::max(t2, tiles(tile_of(p, form, rs, RK2)));
     if (form == FORM_LIN && tables.insert(lin_key(p)).second) L.lin_doubles += lin_tab_size((int)p.degree + 1, S);
-    nwa += (p.n_elem + T1 - 1) / T1;
-    nwa2 += (p.n_elem + TA2 - 1) / TA2;
+    for (int list = 0; list < 2; ++list) nwa[list] += tiles(TA[list]);
+    L.n_parts += tiles(adj_part_elems((int)p.rk));
     nws += (p.n_elem + kBlock - 1) / kBlock;
     tot += ld_of(p) * (p.degree + 1);
     if (split && async_of(p))  // room for the window items of a PE-face split
@@ -555,8 +605,8 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   L.n_work_f = (int32_t)nwf;
   L.n_work_f2 = (int32_t)nwf2;
   L.n_work_s = (int32_t)nws;
-  L.n_work_a = n_rec > 0 ? (int32_t)nwa : 0;
-  L.n_work_a2 = n_rec > 0 && adj_two_steps(probs) ? (int32_t)nwa2 : 0;
+  L.n_work_a[ADJ_FWD] = n_rec > 0 ? (int32_t)nwa[ADJ_FWD] : 0;
+  L.n_work_a[ADJ_LINEAR] = n_rec > 0 && probs[0].equation == ADG_EQ_ADVECTION ? (int32_t)nwa[ADJ_LINEAR] : 0;
   L.total_doubles = tot;
   L.ring_doubles = ring;
   int64_t off = 0;
@@ -582,7 +632,7 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   L.n_rec = n_rec;
   L.ckpt_every = (opt && opt->ckpt_every > 0) ? opt->ckpt_every : 64;
   L.n_ckpt = rec ? (n_rec + L.ckpt_every - 1) / L.ckpt_every : 0;
-  L.ckpt = L.useg = L.ybuf = L.lam = L.q = L.adjring = L.cpart = L.work_a = L.work_a2 = -1;
+  L.ckpt = L.useg = L.ybuf = L.lam = L.q = L.adjring = L.cpart = L.work_a[0] = L.work_a[1] = -1;
   if (rec) {
     // stage kernels recompute a segment into seg slots; the fused adjoint
     // reads the segment's first state from its checkpoint and needs seg - 1
@@ -596,9 +646,9 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
       L.q = take(8 * tot * (S - 1));
       L.cpart = take(8 * nws);
     } else {
-      L.work_a = take((int64_t)sizeof(WorkItem) * nwa);
-      if (L.n_work_a2 > 0) L.work_a2 = take((int64_t)sizeof(WorkItem) * nwa2);
-      L.cpart = take(8 * nwa);
+      for (int list = 0; list < 2; ++list)
+        if (L.n_work_a[list] > 0) L.work_a[list] = take((int64_t)sizeof(WorkItem) * L.n_work_a[list]);
+      L.cpart = take(8 * L.n_parts);
     }
   }
   L.total = off;
@@ -639,11 +689,9 @@ struct adg_ctx {
   int32_t single[2][kFusedRanges] = {};
   FaceRange faces[2][kFusedRanges] = {};
   int32_t one_launch = 0;  // ADG_OPT_ONE_LAUNCH
-  int32_t lane_elems = 2, fused_steps = 2;  // of the two-step reverse
+  int adj_steps = kMaxSteps;  // of a reverse launch at most, as the option asks
   // fused adjoint work list (recording contexts of the fused kernel)
-  std::vector<WorkItem> work_a, work_a2;
-  int32_t group_a[5] = {0, 0, 0, 0, 0}, group_a2[5] = {0, 0, 0, 0, 0};
-  int32_t grid_a[4] = {1, 1, 1, 1}, grid_a2[4] = {1, 1, 1, 1};
+  AdjArgs adj[2] = {};  // per list, but for the steps of a launch
 
   int list_steps(int list) const { return list == 0 ? 1 : std::max(2, L.shape.kmax); }
   StepArgs base_args(int64_t work_off, int32_t n_work, int K = 1) const {
@@ -673,13 +721,9 @@ struct adg_ctx {
   }
   StepArgs stage_args() const { return base_args(L.work_s, L.n_work_s); }
 
-  AdjArgs adj_args(int K = 1) const {
-    AdjArgs a{};
-    a.probs = (const DevProblem*)(ws + L.probs);
-    a.work = (const WorkItem*)(ws + (K == 2 ? L.work_a2 : L.work_a));
-    for (int i = 0; i < 5; ++i) a.group[i] = K == 2 ? group_a2[i] : group_a[i];
-    for (int i = 0; i < 4; ++i) a.grid[i] = K == 2 ? grid_a2[i] : grid_a[i];
-    a.lane_elems = K == 2 ? adj_lane_elems(lane_elems) : 1;
+  AdjArgs adj_args(int list, int K) const {
+    AdjArgs a = adj[list];
+    a.steps = K;
     return a;
   }
   int64_t* ctr() const { return (int64_t*)(ws + L.ctr); }
@@ -715,11 +759,12 @@ int launch_stages(adg_ctx* c, const StepArgs& a, double* U, int32_t step_offset,
 }
 
 // Steps of the next launch with `left` steps to go.
-int next_steps(const adg_ctx* c, int64_t left) {
-  int K = c->L.shape.kmax;
+int steps_within(int kmax, int64_t left) {
+  int K = kmax;
   while (K > left) K >>= 1;
   return K;
 }
+int next_steps(const adg_ctx* c, int64_t left) { return steps_within(c->L.shape.kmax, left); }
 
 // m steps, as many per launch as the kernel allows, the step counter included.
 // The state goes from *cur through `dst(i)` for each launch's result after i
@@ -960,7 +1005,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
 
   // descriptors
   c->dev.resize(n_probs);
-  int64_t uoff = 0, roff = 0;
+  int64_t uoff = 0, roff = 0, poff = 0;
   std::vector<double> lin_tabs;
   std::map<LinKey, int64_t> lin_at;
   for (int32_t i = 0; i < n_probs; ++i) {
@@ -989,6 +1034,8 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
         return fail(ADG_E_INVALID, "internal: division by pe_size failed self-check");
       }
     }
+    d.part_off = poff;
+    poff += (p.n_elem + adj_part_elems((int)p.rk) - 1) / adj_part_elems((int)p.rk);
     d.ring_off = roff;
     if (d.async_faces) {
       const int64_t one_ring = d.n_pe * c->S * (int64_t)d.depth;
@@ -1039,10 +1086,9 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   std::vector<int32_t> order(n_probs);
   for (int32_t i = 0; i < n_probs; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return probs[a].degree > probs[b].degree; });
-  c->lane_elems = lane_elems_of(probs, n_probs, opt);
-  c->fused_steps = fused_steps_of(opt);
   std::vector<WorkItem> wfk[2], ws_;
   std::vector<int32_t> first(n_probs + 1, 0);
+  if (opt && opt->fused_steps != 0) c->adj_steps = (int)opt->fused_steps;
   c->one_launch = (opt && (opt->flags & ADG_OPT_ONE_LAUNCH)) ? 1 : 0;
   for (int list = 0; list < 2; ++list) {  // one and several steps per launch
     const int K = c->list_steps(list);
@@ -1083,27 +1129,40 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     for (int64_t t = 0; t < nt; ++t) ws_.push_back(WorkItem{i, (int32_t)t});
   }
   first[n_probs] = (int32_t)ws_.size();
-  // fused adjoint: one element per lane, same degree grouping
-  auto adj_list = [&](int T1, std::vector<WorkItem>& wl, int32_t* grp, int32_t* grd) {
-    for (int np = 5, gi = 0; np >= 2; --np, ++gi) {
-      grp[gi] = (int32_t)wl.size();
+  // fused reverse sweep: ranges per degree, upwind with a > 0 first
+  std::vector<WorkItem> work_a[2];
+  for (int list = 0; list < 2; ++list) {
+    if (c->L.work_a[list] < 0) continue;
+    const Shape& sh = c->L.adj[list];
+    const bool nl = probs[0].equation == ADG_EQ_BURGERS;
+    const int T = adj_tile_elems(c->rk, nl, sh.elems, sh.kmax);
+    std::vector<WorkItem>& wl = work_a[list];
+    AdjArgs& a = c->adj[list];
+    a.probs = (const DevProblem*)(c->ws + c->L.probs);
+    a.work = (const WorkItem*)(c->ws + c->L.work_a[list]);
+    a.elems = sh.elems;
+    a.halo = adj_halo(c->rk, nl, sh.elems, sh.kmax);
+    for (int gi = 0; gi < kAdjRanges; ++gi) {
+      a.group[gi] = (int32_t)wl.size();
+      a.single[gi] = -1;
+      int n_in = 0;
+      FaceRange& fr = a.faces[gi];
       for (int32_t i : order) {
-        if ((int)probs[i].degree + 1 != np) continue;
-        const int64_t nt = (probs[i].n_elem + T1 - 1) / T1;
-        for (int64_t t = 0; t < nt; ++t) wl.push_back(WorkItem{i, (int32_t)t});
+        const adg_problem& p = probs[i];
+        const bool pos = phys_of(p) == PHYS_ADV_UPWIND && p.speed > 0.0;
+        if ((int)p.degree + 1 != 5 - gi / kAdjForms || (pos ? 0 : 1) != gi % kAdjForms) continue;
+        for (int64_t t = 0; t < (p.n_elem + T - 1) / T; ++t) wl.push_back(WorkItem{i, (int32_t)t});
+        a.single[gi] = n_in++ == 0 ? i : -1;
+        if (async_of(p)) fr.n_faces = std::max(fr.n_faces, fused_faces(sh.elems, p.pe_size));
       }
+      fr.lds_words = adj_lds_words(c->S, sh.elems, sh.kmax, fr.n_faces, list == ADJ_FWD, list == ADJ_FWD && !nl);
+      a.grid[gi] = fused_grid((int32_t)wl.size() - a.group[gi]);
     }
-    grp[4] = (int32_t)wl.size();
-    for (int gi = 0; gi < 4; ++gi) grd[gi] = fused_grid(grp[gi + 1] - grp[gi]);
-  };
-  if (c->L.work_a >= 0)
-    adj_list(adj_tile_elems(c->rk, probs[0].equation == ADG_EQ_BURGERS), c->work_a, c->group_a, c->grid_a);
-  if (c->L.work_a2 >= 0)
-    adj_list(adj_tile_elems2(c->rk, adj_lane_elems(c->lane_elems)), c->work_a2, c->group_a2, c->grid_a2);
-  if ((c->L.work_a >= 0 && (int64_t)c->work_a.size() != c->L.n_work_a) ||
-      (c->L.work_a2 >= 0 && (int64_t)c->work_a2.size() != c->L.n_work_a2)) {
-    delete c;
-    return fail(ADG_E_INVALID, "internal: adjoint work list does not match the workspace layout");
+    a.group[kAdjRanges] = (int32_t)wl.size();
+    if ((int64_t)wl.size() != c->L.n_work_a[list]) {
+      delete c;
+      return fail(ADG_E_INVALID, "internal: adjoint work list does not match the workspace layout");
+    }
   }
 
   auto up = [&](int64_t off, const void* src, int64_t bytes) -> int {
@@ -1116,10 +1175,10 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
       (rc = up(c->L.work_f2, wfk[1].data(), (int64_t)sizeof(WorkItem) * wfk[1].size())) ||
       (rc = up(c->L.work_s, ws_.data(), (int64_t)sizeof(WorkItem) * ws_.size())) ||
       (rc = up(c->L.first_s, first.data(), (int64_t)sizeof(int32_t) * first.size())) ||
-      (c->L.work_a >= 0 &&
-       (rc = up(c->L.work_a, c->work_a.data(), (int64_t)sizeof(WorkItem) * c->work_a.size()))) ||
-      (c->L.work_a2 >= 0 &&
-       (rc = up(c->L.work_a2, c->work_a2.data(), (int64_t)sizeof(WorkItem) * c->work_a2.size()))) ||
+      (c->L.work_a[0] >= 0 &&
+       (rc = up(c->L.work_a[0], work_a[0].data(), (int64_t)sizeof(WorkItem) * work_a[0].size()))) ||
+      (c->L.work_a[1] >= 0 &&
+       (rc = up(c->L.work_a[1], work_a[1].data(), (int64_t)sizeof(WorkItem) * work_a[1].size()))) ||
       (rc = reset_device(c))) {
     delete c;
     return rc;
@@ -1351,8 +1410,8 @@ int adjoint_stage(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
 
 // Adjoint with the fused kernels: each segment is recomputed out of place by
 // the fused step kernel (from the checkpointed state and PE-face records, so
-// the states are bitwise those of the recorded run), then every reverse step
-// is one launch per degree group.  The records of the current step are kept
+// the states are bitwise those of the recorded run), then reversed, several
+// steps per launch.  The records of the current step are kept
 // in the spare checkpoint slot and restored at the end, so the context can
 // keep stepping afterwards.
 int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double* h_grad_speed) {
@@ -1360,7 +1419,6 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   const int64_t tot = L.total_doubles, C = L.ckpt_every, N = c->rec_steps;
   char* ws = c->ws;
   hipStream_t st = c->stream;
-  const AdjArgs aa = c->adj_args();
   double* lam = (double*)(ws + L.lam);
   double* lamu = lam + tot;
   double* adjring = (double*)(ws + L.adjring);
@@ -1372,21 +1430,17 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
 
   ADG_HIP(hipMemcpyAsync(lam, d_cot_uT, bytes, hipMemcpyDeviceToDevice, st));
   ADG_HIP(launch_zero(adjring, 8 * std::max<int64_t>(L.ring_doubles, 1), st));
-  ADG_HIP(launch_zero(cpart, 8 * (size_t)std::max<int32_t>(L.n_work_a, 1), st));
+  ADG_HIP(launch_zero(cpart, 8 * (size_t)std::max<int64_t>(L.n_parts, 1), st));
 
   // linear advection: the reverse sweep does not depend on the forward states;
   // they are recomputed only for dJ/da
   const bool need_fwd = c->phys == PHYS_BURGERS_LLF || h_grad_speed != nullptr;
   if (!need_fwd) {
-    const AdjArgs aa2 = c->adj_args(2);
-    for (int64_t n = N - 1; n >= 0;) {
-      if (c->fused_steps == 2 && L.work_a2 >= 0 && n >= 1) {  // steps n and n - 1 in one launch
-        ADG_HIP(launch_adj_fused2(c->rk, c->phys, aa2, lam, lamu, adjring, (int32_t)(n - 1), st));
-        n -= 2;
-      } else {
-        ADG_HIP(launch_adj_fused(c->rk, c->phys, aa, nullptr, lam, lamu, ring, adjring, cpart, (int32_t)n, st));
-        n -= 1;
-      }
+    for (int64_t n = N; n > 0;) {
+      const int K = steps_within(std::min(L.adj[ADJ_LINEAR].kmax, c->adj_steps), n);
+      n -= K;
+      ADG_HIP(launch_adj_fused(c->rk, c->phys, c->adj_args(ADJ_LINEAR, K), nullptr, nullptr, 0, lam, lamu, ring,
+                               adjring, cpart, (int32_t)n, st));
       std::swap(lam, lamu);
     }
   }
@@ -1405,18 +1459,25 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
         return rc;
       i += K;
     }
-    for (int64_t i = len - 1; i >= 0; --i) {
-      ADG_HIP(launch_adj_fused(c->rk, c->phys, aa, state(i), lam, lamu, ring, adjring, cpart, (int32_t)(n0 + i),
-                               st));
+    for (int64_t i = len; i > 0;) {
+      const int K = steps_within(std::min(L.adj[ADJ_FWD].kmax, c->adj_steps), i);
+      i -= K;
+      ADG_HIP(launch_adj_fused(c->rk, c->phys, c->adj_args(ADJ_FWD, K), state(i), useg + tot * i, tot, lam, lamu, ring,
+                               adjring, cpart, (int32_t)(n0 + i), st));
       std::swap(lam, lamu);
     }
   }
   ADG_HIP(hipMemcpyAsync(d_grad_u0, lam, bytes, hipMemcpyDeviceToDevice, st));
   if (h_grad_speed) {
-    std::vector<double> part(c->work_a.size());
+    std::vector<double> part(L.n_parts);
     ADG_HIP(hipMemcpyAsync(part.data(), cpart, 8 * part.size(), hipMemcpyDeviceToHost, st));
     ADG_HIP(hipStreamSynchronize(st));
-    sum_speed_parts(c, part, c->work_a, h_grad_speed);
+    std::vector<WorkItem> items;  // contiguous per problem, in problem order
+    items.reserve(L.n_parts);
+    const int T = adj_part_elems(c->rk);
+    for (size_t i = 0; i < c->probs.size(); ++i)
+      for (int64_t t = 0; t < (c->probs[i].n_elem + T - 1) / T; ++t) items.push_back(WorkItem{(int32_t)i, (int32_t)t});
+    sum_speed_parts(c, part, items, h_grad_speed);
   }
   return ADG_OK;
 }

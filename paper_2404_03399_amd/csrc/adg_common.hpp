@@ -92,6 +92,7 @@ struct DevProblem {
   double Kdu[kMaxNp * kMaxNp];
   FastDiv depth_div;     // division by the ring depth (step indices < 2^31)
   int64_t lin_off;       // offset of the problem's LinTab in the table region (doubles), -1: none
+  int64_t part_off;      // the problem's first partial sum of dJ/da
   double atc[kMaxL][kMaxQ];    // c_j(k), j < q, k < L
 };
 

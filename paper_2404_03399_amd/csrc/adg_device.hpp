@@ -269,52 +269,6 @@ __device__ __forceinline__ void folded_rhs(const DevProblem& P, const double (&y
   }
 }
 
-// Lane of the i-th set bit (from 0) of a wave-uniform mask, 0 if there is none.
-__device__ __forceinline__ int nth_set_lane(uint64_t mask, int i) {
-  int lane = 0;
-  for (int c = 0; mask != 0; ++c) {
-    const int bit = __builtin_ctzll(mask);
-    mask &= mask - 1;
-    if (c == i) lane = bit;
-  }
-  return lane;
-}
-
-// Part of the AT sum of step m = n + ahead (delay kd >= 1) over the levels
-// m - kd - j that precede step n, j = q-1 down to 0, oldest first, one
-// explicit FMA per level; rb is the ring of one (boundary, stage), slot_n =
-// n mod depth.  The loads are unrolled over kMaxQ and issue together.
-// Its two halves: the loads (issued together, so that a caller can issue
-// other loads before it waits for these) and the sum.
-struct AtLevels {
-  double c[kMaxQ], v[kMaxQ];
-  bool use[kMaxQ];
-};
-
-__device__ __forceinline__ void at_old_levels_load(const DevProblem& P, const double* __restrict__ rb, int ahead,
-                                                   int kd, int slot_n, int depth, AtLevels& L) {
-#pragma unroll
-  for (int j = 0; j < kMaxQ; ++j) {
-    const int back = kd + j - ahead;  // level n - back
-    L.use[j] = kd > 0 && j < P.q && back >= 1;
-    L.c[j] = 0.0;
-    L.v[j] = 0.0;
-    if (L.use[j]) {
-      L.c[j] = P.atc[kd][j];
-      L.v[j] = rb[ring_slot(slot_n, back, depth)];
-    }
-  }
-}
-
-__device__ __forceinline__ double at_old_levels_sum(const AtLevels& L) {
-#pragma clang fp contract(off)
-  double acc = 0.0;
-#pragma unroll
-  for (int j = kMaxQ - 1; j >= 0; --j)
-    if (L.use[j]) acc = fma(L.c[j], L.v[j], acc);
-  return acc;
-}
-
 // --------------------------------------------------------------- adjoint ---
 // Butcher form of a 2N scheme: U_s = U + dt sum_{j<=s} beta_{s,j} K_j with
 // beta_{s,j} = sum_{l=j..s} B_l prod_{m=j+1..l} A_m (K_j the operator at
@@ -332,7 +286,7 @@ __host__ __device__ constexpr double ls_beta(int rk, int s, int j) {
 // Butcher form of the integrators (the same maps as the forward algebraic
 // forms): Y_i = U + dt sum_{j<i} a_ij K_j, U' = U + dt sum_i b_i K_i.
 template <int RK>
-__device__ constexpr double bt_a(int i, int j) {
+__host__ __device__ constexpr double bt_a(int i, int j) {
   if constexpr (RK == RK_LS3)  // Williamson's scheme in Butcher form: a21 = 1/3, a31 = -3/16, a32 = 15/16
     return i == 1 ? (j == 0 ? 1.0 / 3.0 : 0.0) : (i == 2 && j < 2 ? (j == 0 ? -3.0 / 16.0 : 15.0 / 16.0) : 0.0);
   if constexpr (RK == RK_LS4) return j < i ? ls_beta(RK, i - 1, j) : 0.0;
@@ -341,7 +295,7 @@ __device__ constexpr double bt_a(int i, int j) {
   else return (i == 1 && j == 0) ? 1.0 : 0.0;
 }
 template <int RK>
-__device__ constexpr double bt_b(int i) {
+__host__ __device__ constexpr double bt_b(int i) {
   if constexpr (RK == RK_LS3) return i == 0 ? 1.0 / 6.0 : (i == 1 ? 3.0 / 10.0 : 8.0 / 15.0);
   if constexpr (RK == RK_LS4) return ls_beta(RK, rk_stages(RK) - 1, i);
   if constexpr (RK == RK_RK4) return (i == 0 || i == 3) ? 1.0 / 6.0 : 1.0 / 3.0;

@@ -418,6 +418,23 @@ static void stage_phys(int phys, int si, const StepArgs& a, const double* yin, d
   }
 }
 
+hipError_t launch_adj_fused(int rk, int phys, const AdjArgs& a, const double* u_n, const double* u_next,
+                            int64_t u_stride, const double* lam, double* lamo, const double* ring, double* adjring,
+                            double* cpart, int32_t n, hipStream_t stream) {
+  switch (rk) {
+    case RK_HEUN:
+      return launch_adj_rk<RK_HEUN>(phys, a, u_n, u_next, u_stride, lam, lamo, ring, adjring, cpart, n, stream);
+    case RK_SSP3:
+      return launch_adj_rk<RK_SSP3>(phys, a, u_n, u_next, u_stride, lam, lamo, ring, adjring, cpart, n, stream);
+    case RK_LS3:
+      return launch_adj_rk<RK_LS3>(phys, a, u_n, u_next, u_stride, lam, lamo, ring, adjring, cpart, n, stream);
+    case RK_LS4:
+      return launch_adj_rk<RK_LS4>(phys, a, u_n, u_next, u_stride, lam, lamo, ring, adjring, cpart, n, stream);
+    default:
+      return launch_adj_rk<RK_RK4>(phys, a, u_n, u_next, u_stride, lam, lamo, ring, adjring, cpart, n, stream);
+  }
+}
+
 hipError_t launch_fused_step(int rk, int phys, const StepArgs& a, const double* uin, double* uout, int32_t step_offset,
                              hipStream_t stream) {
   switch (rk) {

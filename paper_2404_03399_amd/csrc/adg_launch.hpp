@@ -134,37 +134,49 @@ hipError_t launch_adj_stage(int rk, int phys, int stage, const StepArgs& a, cons
                             double* lamu, double* Q, int64_t qstride, const double* ring, double* adjring,
                             double* cpart, int32_t n, hipStream_t stream);
 
-// Fused adjoint geometry: one element per lane, halo of S lanes per side for
-// a constant Jacobian (linear advection) and 2S - 1 when the Jacobian depends
-// on the stage inputs (Burgers).  Work items are grouped by descending np
-// like the fused step's list.
-__host__ __device__ constexpr int adj_halo(int rk, bool nonlinear) {
-  return nonlinear ? 2 * rk_stages(rk) - 1 : rk_stages(rk);
+// Fused reverse sweep: R elements per lane, K steps per launch, a halo of K S
+// elements per side for a constant Jacobian (linear advection) and of
+// (K + 1) S - 1 where the Jacobian depends on the stage inputs (Burgers).
+__host__ __device__ constexpr int adj_halo(int rk, bool nonlinear, int R, int K) {
+  return ((nonlinear ? (K + 1) * rk_stages(rk) - 1 : K * rk_stages(rk)) + R - 1) / R;
 }
-__host__ __device__ constexpr int adj_tile_elems(int rk, bool nonlinear) { return kWave - 2 * adj_halo(rk, nonlinear); }
+__host__ __device__ constexpr int adj_tile_elems(int rk, bool nonlinear, int R, int K) {
+  return R * (kWave - 2 * adj_halo(rk, nonlinear, R, K));
+}
+// Elements of a partial sum of dJ/da.
+__host__ __device__ constexpr int adj_part_elems(int rk) { return kWave - 2 * rk_stages(rk); }
+// LDS of a wave in doubles (layout: adj_tile, AdjFaces)
+__host__ __device__ constexpr int adj_lds_words(int S, int R, int K, int n_faces, bool forward, bool speed) {
+  return (speed ? R * kWave : 0) + (n_faces > 0 ? kMaxL * kMaxQ + (forward ? 2 : 1) * (n_faces * K * S + S) +
+                                                      n_faces * (K + 1)
+                                                : 0);
+}
+// Work items are grouped by descending np and, within, upwind with a > 0 first.
+constexpr int kAdjForms = 2, kAdjRanges = 4 * kAdjForms;
 struct AdjArgs {
   const DevProblem* probs;
   const WorkItem* work;
-  int32_t group[5];
-  int32_t grid[4];
-  int32_t lane_elems;  // two-step reverse: elements per lane (1 or 2)
+  int32_t group[kAdjRanges + 1];
+  int32_t grid[kAdjRanges];
+  int32_t single[kAdjRanges];  // the range's only problem, or -1
+  FaceRange faces[kAdjRanges];
+  int32_t elems, steps;  // elements per lane, steps of this launch (a power of two, at most the list's)
+  int32_t halo;          // halo lanes per side of the work list
 };
 
-// Reverse of the whole RK step n (absolute index) for all problems in one
-// launch per degree group: lamo = lambda^n from lam = lambda^{n+1} and the
-// forward state u = u^n (stages recomputed on chip); adjoint-ring deposits for
-// delayed AT levels; cpart[work item] += dJ/da share (advection).
-hipError_t launch_adj_fused(int rk, int phys, const AdjArgs& a, const double* u, const double* lam, double* lamo,
-                            const double* ring, double* adjring, double* cpart, int32_t n, hipStream_t stream);
-
-// Reverse of steps n + 1 and n (absolute indices) for linear advection without
-// the forward states (dJ/du0 only): lamo = lambda^n from lam = lambda^{n+2},
-// R = a.lane_elems consecutive elements per lane, halo of 2S elements per
-// side (work list of adj_tile_elems2(rk, R) elements per item).
-hipError_t launch_adj_fused2(int rk, int phys, const AdjArgs& a, const double* lam, double* lamo, double* adjring,
-                             int32_t n, hipStream_t stream);
-__host__ __device__ constexpr int adj_halo2(int rk, int R) { return (2 * adj_halo(rk, false) + R - 1) / R; }
-__host__ __device__ constexpr int adj_tile_elems2(int rk, int R) { return R * (kWave - 2 * adj_halo2(rk, R)); }
+// Reverse of the a.steps whole RK steps n, ..., n + K - 1 (absolute indices) for
+// all problems in one launch per range: lamo = lambda^n from lam = lambda^{n+K};
+// adjoint-ring deposits for delayed AT levels.  With the forward states u^n at
+// u_n and u^{n+1}, u^{n+2}, ... at u_next, u_next + u_stride, ... (stages
+// recomputed on chip) advection adds its dJ/da shares to cpart; without them
+// (u_n == nullptr, advection only) dJ/du0 alone.  Compiled per integrator.
+template <int RK>
+hipError_t launch_adj_rk(int phys, const AdjArgs& a, const double* u_n, const double* u_next, int64_t u_stride,
+                         const double* lam, double* lamo, const double* ring, double* adjring, double* cpart,
+                         int32_t n, hipStream_t stream);
+hipError_t launch_adj_fused(int rk, int phys, const AdjArgs& a, const double* u_n, const double* u_next,
+                            int64_t u_stride, const double* lam, double* lamo, const double* ring, double* adjring,
+                            double* cpart, int32_t n, hipStream_t stream);
 
 // Zero fill of `bytes` bytes at p (8-byte aligned, a multiple of 8).
 hipError_t launch_zero(void* p, int64_t bytes, hipStream_t stream);

@@ -392,3 +392,46 @@ def test_burgers_gradient_against_central_difference(torch_cuda):
     fd = (J(u0 + h * v) - J(u0 - h * v)) / (2 * h)
     ad = float((g * v).sum())
     assert abs(ad - fd) <= 1e-6 * max(1.0, abs(fd)), (ad, fd)
+
+
+@pytest.mark.parametrize("scheme,rk,p,eq,flux,speed,ne,pe", [
+    ("adg_at", "rk4", 3, "advection", "upwind", 1.3, 225, 25),    # four partial sums and one element; odd PEs
+    ("adg_at", "rk4", 2, "advection", "upwind", -0.75, 112, 7),   # two partial sums exactly
+    ("adg", "lsrk4", 4, "advection", "central", 1.3, 55, 5),      # one element past a partial sum
+    ("adg_at", "ssprk3", 3, "advection", "upwind", 1.3, 3, 1),    # a mesh within the halo, one element per lane
+    ("dg", "heun", 1, "advection", "central", 1.3, 61, 61),
+    ("adg_at", "ssprk3", 2, "burgers", "llf", 1.0, 110, 11),
+    ("adg_at", "lsrk4", 1, "burgers", "llf", 1.0, 66, 2)])
+def test_reverse_launch_shapes_bitwise(torch_cuda, scheme, rk, p, eq, flux, speed, ne, pe):
+    """One, two and up to eight reverse steps per launch, with the forward
+    stages (segments of 9, 9 and 5 steps) and without, at every number of
+    elements per lane: dJ/du0 and dJ/da are bitwise the same, and dJ/du0
+    matches the oracle."""
+    from paper_2404_03399_amd.solver import Solver
+    dt = {1: 0.05, 2: 0.02, 3: 0.005, 4: 0.002}[p] * W.TWO_PI / ne * (0.2 if eq == "burgers" else 1.0)
+    w = W.Workload(name="rev", scheme=scheme, rk=rk, degree=p, n_elem=ne, pe_size=pe, equation=eq, flux=flux,
+                   probs=W.DELAYS_C2, seed=5, dt=dt, speed=speed, ic=W.PAPER_MULTISINE)
+    n = 23
+    _say(f"reverse launch shapes {scheme} {rk} p={p} {eq} {flux} a={speed} N={ne} pe={pe} steps={n}")
+    u0 = stepper.initial_state(w)
+    ref = np.random.default_rng(4).standard_normal(u0.shape)
+    _, g_o, _ = oadj.gradient(w, u0, n, oadj.misfit_cotangent(ref))
+    grads, speeds = [], []
+    for K in (1, 2, 0):
+        for R in (0, 1, 2, 4):
+            if scheme != "dg" and R > pe:
+                continue
+            s = Solver(w, kernel="fused", n_steps_record=n, ckpt_every=9, fused_steps=K, lane_elems=R)
+            u = s.pack(u0)
+            s.run(u, n, graph=True, record=True)
+            cot = s.pack(s.unpack(u)[0] - ref)
+            g, gs = s.adjoint(cot)
+            g2, _ = s.adjoint(cot, want_speed=False)
+            torch_cuda.cuda.synchronize()
+            grads += [s.unpack(g)[0], s.unpack(g2)[0]]
+            speeds.append(gs[0])
+            s.close()
+    for g in grads:
+        assert np.array_equal(g, grads[0])
+    assert all(x == speeds[0] for x in speeds), speeds
+    assert stats.rel_l2(grads[0], g_o) <= 1e-12, stats.rel_l2(grads[0], g_o)
