@@ -33,15 +33,41 @@ BYTES_PER_DOF_STAGE_STAGEK = {"rk4": 34.0, "ssprk3": 64.0 / 3, "heun": 28.0}
 FP64_VECTOR_PEAK_TFS = 78.6    # MI355X FP64 vector (no MFMA: the element operators are 4x4)
 
 
-def fused_flops_per_elem_step(np_: int) -> int:
-    """FP64 flops of one RK4 step of one element in the fused upwind kernel
-    (halo recompute excluded): per stage the upwind flux a u^- (1), the lift
-    and folded volume operator Kl F + Kdu y (np muls, np^2 FMAs); the RK4
-    updates 13 np (FMA = 2 flops)."""
-    return 4 * (2 * np_ * np_ + np_ + 1) + 13 * np_
+STAGES = {"rk4": 4, "ssprk3": 3, "heun": 2, "lsrk3": 3, "lsrk4": 5}
 
 
-FUSED_SOURCES = ("adg_fused.hip", "adg_device.hpp", "adg_common.hpp", "adg_launch.hpp")
+def fused_flops_per_elem_step(np_: int, stages: int = 4) -> int:
+    """FP64 flops of one RK step of one element in the fused kernel of upwind
+    advection (halo recompute excluded), in flux-sequence form: np node columns
+    of S - 1 fluxes and np new values, one column per flux of the fluxes that
+    follow it and the new values (an FMA each, 2 flops), and G_0 = a u_p."""
+    return 2 * (np_ * (stages - 1 + np_) + stages * (stages - 1) // 2 + stages * np_) + 1
+
+
+def launch_shape(s, ws):
+    """Elements per lane and steps per launch of a forward context: its options,
+    or the library's choice by size and halo where they are 0 (PE sizes of 64
+    and more, whose face records limit neither)."""
+    ws = ws if isinstance(ws, (list, tuple)) else [ws]
+    n, S = sum(w.n_elem for w in ws), STAGES[ws[0].rk]
+    ldg = ws[0].equation == "viscous_burgers"
+    lin = all(w.equation == "advection" and w.flux == "upwind" and w.speed > 0 and w.n_elem >= 1024 for w in ws)
+    two, four = (1 << 16, 1 << 19) if lin or ldg else (0, 1 << 18)
+    R = s.opt.lane_elems or (4 if n >= four else 2 if n >= two else 1)
+    if ldg:
+        most = (24 if n <= 1 << 16 else 16) // R
+    elif lin:
+        most = 40 if n <= 1 << 18 else 20
+    else:
+        most = 21 if n <= 1 << 16 else 8
+    K = 8
+    while K > 2 and -(-K * S // R) > most:
+        K //= 2
+    return R, s.opt.fused_steps or K
+
+
+FUSED_SOURCES = ("adg_fused.hip", "adg_linear.hip", "adg_linear.hpp", "adg_wave.hpp", "adg_device.hpp",
+                 "adg_common.hpp", "adg_launch.hpp")
 
 
 def kernel_source_hash() -> str:
@@ -58,7 +84,7 @@ def ring_bytes_per_step(w) -> float:
     if w.scheme == "dg" or w.n_pe <= 1:
         return 0.0
     q = (w.at_levels or w.degree + 1) if w.scheme == "adg_at" else 1
-    stages = {"rk4": 4, "ssprk3": 3, "heun": 2, "lsrk3": 3, "lsrk4": 5}[w.rk]
+    stages = STAGES[w.rk]
     return w.n_pe * stages * 8.0 * (1 + q)
 
 
@@ -126,8 +152,8 @@ def fused_roofline(w, launch_s: float, R: int, K: int, traffic=None, note: str =
            "unit": "TFLOP/s", "frac": flops / launch_s / 1e12 / FP64_VECTOR_PEAK_TFS, "traffic": traffic}
     roof, other = (dict(alu), hbm) if alu["frac"] > hbm["frac"] else (dict(hbm), alu)
     roof["other_roof"] = {k: other[k] for k in ("bound", "achieved", "peak", "unit", "frac")}
-    roof.update({"kernel": f"k_fused_step<p={w.degree}, {w.rk}, {w.flux}, R={R} element(s) per lane, "
-                           f"K={K} step(s) per launch>",
+    roof.update({"kernel": f"k_lin_step<p={w.degree}, {w.rk}, R={R} element(s) per lane>, "
+                           f"K={K} step(s) per launch",
                  "alg_bytes_per_launch": alg_bytes, "alg_flops_per_launch": flops, "launch_us": launch_s * 1e6,
                  "steps_per_launch": K, "lane_elems": R, "note": note})
     return roof
@@ -268,16 +294,15 @@ def adjoint_roofline(torch, W, Solver, n_elem: int, n1: int = 64, n2: int = 128)
     n1 and n2 steps; each adjoint call is timed with HIP events on the
     solver's stream (median of three), and the difference of the two calls
     per reverse launch drops the per-call copies and fills.  dJ/du0 only:
-    k_adj_fused2, two reverse steps per launch, reads lambda^{n+2} and writes
-    lambda^n (16 B per DOF); with dJ/da: k_adj_fused with the forward stages
-    recomputed in registers, every state kept (checkpoint interval 1, so no
-    segment is recomputed), reads u^n and lambda^{n+1} and writes lambda^n
-    (24 B per DOF)."""
+    four reverse steps per launch read lambda^{n+4} and write lambda^n (16 B per
+    DOF); with dJ/da the forward stages are recomputed in registers and, every
+    state kept (checkpoint interval 1, so no segment is recomputed), launches of
+    one step read u^n and lambda^{n+1} and write lambda^n (24 B per DOF)."""
     dofs = n_elem * 4
     out = {"n_elem": n_elem}
     for key, want, ckpt, per, bytes_dof, kern in (
-            ("two_step_reverse", False, 64, 2, 16, "k_adj_fused2<p=3, rk4, upwind, two steps, R=2>"),
-            ("one_step_reverse_with_speed", True, 1, 1, 24, "k_adj_fused<p=3, rk4, upwind, forward stages kept>")):
+            ("reverse_du0", False, 64, 4, 16, "k_adj_fused<p=3, rk4, upwind, R=2>, four steps per launch"),
+            ("one_step_reverse_with_speed", True, 1, 1, 24, "k_adj_fused<p=3, rk4, upwind, forward stages, R=2>, one step per launch")):
         ts = {}
         for n in (n1, n2):
             w = W.c5_adjoint_advection(n_elem=n_elem, n_steps=n)
@@ -380,7 +405,7 @@ def bench_burgers(torch, W, Solver, n_elem: int = 1 << 22, steps: int = 200):
     (q=3), SSP-RK3, 16384 PEs of 256, on the fused kernel at its tuned shape."""
     w = W.c3_burgers(n_elem=n_elem, n_steps=steps)
     s = Solver(w, lane_elems="auto")
-    K, R = s.opt.fused_steps or 2, s.opt.lane_elems or 1
+    R, K = launch_shape(s, w)
     u = s.initial_state()
     g, reps, _ = time_solver(torch, s, u, steps, 20)
     finite = bool(torch.isfinite(u).all().item())
@@ -412,7 +437,7 @@ def bench_viscous_burgers(torch, W, Solver, n_elem: int = 1 << 20, steps: int = 
     finite = True
     for kernel in ("fused", "stage"):
         s = Solver(w, kernel=kernel)
-        K = (s.opt.fused_steps or 2) if kernel == "fused" else 1
+        K = launch_shape(s, w)[1] if kernel == "fused" else 1
         u = s.initial_state()
         g, _, _ = time_solver(torch, s, u, steps, 20)
         finite = finite and bool(torch.isfinite(u).all().item())
@@ -438,7 +463,7 @@ def bench_ensemble(torch, W, Solver, n_steps: int, n_real: int, plain: bool, lan
     group = [int(w.name.split("_")[1][1:]) for w in ws]
     dofs = sum(w.n_elem * (w.degree + 1) for w in ws)
     s = Solver(ws, lane_elems="auto") if lane_elems < 0 else Solver(ws, lane_elems=lane_elems, fused_steps=2)
-    R, K = s.opt.lane_elems or 2, s.opt.fused_steps or 2
+    R, K = launch_shape(s, ws)
 
     def timed(sv, uu, init, reps):
         # the step graph is captured on this buffer first; every rep restarts
@@ -471,7 +496,7 @@ def bench_ensemble(torch, W, Solver, n_steps: int, n_real: int, plain: bool, lan
     ach = alg / adv_s / 1e9
     roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
             "traffic": read_traffic(R, K, profile="pmc_fused_step_ensemble_c4.md"),
-            "kernel": f"k_fused_step over all degree ranges of one {K}-step advance (R={R})",
+            "kernel": f"k_lin_step over all degree ranges of one {K}-step advance (R={R})",
             "alg_bytes_per_advance": alg, "advance_us": adv_s * 1e6, "steps_per_launch": K, "lane_elems": R,
             "note": f"state 2 x {8 * dofs / 1e9:.2f} GB: HBM-resident"}
     # reference: exact solution of each problem at its own final time
@@ -554,7 +579,7 @@ def bench_large(torch, W, Solver, steps: int, n_elem: int = 1 << 24):
     launch shape; with its own roofline block."""
     wl = W.c2_advection_large("adg_at", n_elem=n_elem)
     so = Solver(wl, lane_elems="auto")
-    R, K = so.opt.lane_elems or 1, so.opt.fused_steps or 2
+    R, K = launch_shape(so, wl)
     uu = so.initial_state()
     g, reps, _ = time_solver(torch, so, uu, steps, 16)
     finite = bool(torch.isfinite(uu).all().item())
@@ -632,8 +657,7 @@ def main():
     w = W.c2_advection_large("adg_at", n_elem=args.n_elem)
     s = Solver(w, kernel=args.kernel, lane_elems="auto" if args.lane_elems < 0 else args.lane_elems,
                fused_steps=args.fused_steps)
-    K = (s.opt.fused_steps or 2) if args.kernel == "fused" else 1
-    R = s.opt.lane_elems or 1
+    R, K = launch_shape(s, w) if args.kernel == "fused" else (1, 1)
     u = s.initial_state()
     gpu_s, rep_s, wall = time_solver(torch, s, u, args.steps, args.warmup)
     dofs = w.n_elem * (w.degree + 1)
