@@ -67,9 +67,9 @@ class Solver:
                  device: str = "cuda", stream=None, lane_elems=0, fused_steps: int = 0, scratch: bool = False,
                  pe_split=None, one_launch: bool = False):
         """scratch: take the library's static device workspace (adg_init_scratch)
-        instead of allocating one; no recording horizon.  pe_split: None for
-        the library's choice, True / False to force the fused kernel's
-        PE-face split on (where the PE sizes allow it) or off.  one_launch:
+        instead of allocating one; no recording horizon.  pe_split: accepted
+        (None, True where the PE sizes allow a split, False); it has no effect
+        on the kernels any more.  one_launch:
         one fused launch over every degree range (ADG_OPT_ONE_LAUNCH)."""
         if not isinstance(workloads, (list, tuple)):
             workloads = [workloads]
