@@ -335,6 +335,8 @@ LinKey lin_key(const adg_problem& p) { return LinKey{p.degree, p.speed, p.dt, p.
 // Launch shape of the fused kernel: elements per lane and most steps per launch.
 struct Shape {
   int elems, kmax;
+  int elems1 = 0;  // elements per lane of the one-step launches, if not elems
+  int elems_at(int K) const { return K == 1 && elems1 ? elems1 : elems; }
 };
 
 struct Layout {
@@ -426,9 +428,9 @@ int form_of(const adg_problem& p, int kernel, int64_t n_rec) {
 
 // Owned elements of a work item of the list for K steps.
 int tile_of(const adg_problem& p, int form, const Shape& s, int K) {
-  if (p.equation == ADG_EQ_VISCOUS_BURGERS) return ldg_tile_elems((int)p.rk, s.elems, K);
-  if (form == FORM_GEN) return fused_tile((int)p.rk, s.elems, K);
-  return fused_tile_left((int)p.rk, s.elems, K, async_of(p));
+  if (p.equation == ADG_EQ_VISCOUS_BURGERS) return ldg_tile_elems((int)p.rk, s.elems_at(K), K);
+  if (form == FORM_GEN) return fused_tile((int)p.rk, s.elems_at(K), K);
+  return fused_tile_left((int)p.rk, s.elems_at(K), K, async_of(p));
 }
 
 // Doubles of LDS per wave for problem p in launches of K steps.
@@ -456,6 +458,9 @@ int lds_of(const adg_problem& p, int elems, int K) {
 //                 2.76, 2.93; 2^18 5.01, 4.25, 4.12; 2^22 (2,4) 31.8, (4,4) 29.3,
 //                 (4,8) 31.0; five stages (lsrk4, p = 2) 2^22 (4,4) 27.0, (4,8)
 //                 30.6; 10^5, p = 4, lsrk4, PE 30 (2,2) 4.2, (2,4) 4.5, (2,8) 5.4
+//   one step per launch is bound by HBM, which two elements per lane, with more
+//                 waves in flight, reach better: single steps at 2^23, Burgers,
+//                 RK4 (2,1) 225, (4,1) 242; SSP-RK3, p = 2 171, 178
 //   general, Burgers, SSP-RK3, p = 2   2^22 (2,4) 26.2, (4,4) 24.0, (4,8) 23.7
 //   local DG, p = 2   Heun 2^14 (1,4) 2.02, (1,8) 1.79, (2,8) 1.85; 2^16 2.35, 2.10,
 //                 1.92; 2^18 (2,8) 3.16, (4,8) 3.53; 2^20 8.11, 7.43; SSP-RK3 2^14
@@ -486,6 +491,7 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   for (int32_t i = 0; i < n; ++i)
     if (async_of(probs[i]))
       while (probs[i].pe_size % s.elems) s.elems >>= 1;
+  if (!one_launch && (!opt || opt->lane_elems == 0)) s.elems1 = std::min(s.elems, 2);
   if ((opt && opt->fused_steps != 0) || one_launch) return s;
   const int most_halo = is_ldg(probs) ? (elems <= (int64_t)1 << 16 ? 24 : 16) / s.elems
                         : gen ? (elems <= (int64_t)1 << 16 ? 21 : 8)
@@ -708,10 +714,10 @@ struct adg_ctx {
     for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.faces[i] = faces[list][i];
     a.lin = (const double*)(ws + L.lin);
-    a.elems = L.shape.elems;
+    a.elems = L.shape.elems_at(list_steps(list));
     a.steps = K;
-    a.halo = fused_halo(rk, L.shape.elems, list_steps(list));
-    a.halo_right = ldg_halo_right(rk, L.shape.elems, list_steps(list));
+    a.halo = fused_halo(rk, a.elems, list_steps(list));
+    a.halo_right = ldg_halo_right(rk, a.elems, list_steps(list));
     a.one_launch = one_launch;
     a.qbuf = L.qbuf >= 0 ? (double*)(ws + L.qbuf) : nullptr;
     return a;
@@ -1108,8 +1114,8 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
         const int T = tile_of(p, form, c->L.shape, K);
         for (int64_t t = 0; t < (p.n_elem + T - 1) / T; ++t) wf.push_back(WorkItem{i, (int32_t)t});
         if (async_of(p)) {
-          fr.n_faces = std::max(fr.n_faces, fused_faces(c->L.shape.elems, p.pe_size));
-          fr.lds_words = std::max(fr.lds_words, lds_of(p, c->L.shape.elems, K));
+          fr.n_faces = std::max(fr.n_faces, fused_faces(c->L.shape.elems_at(K), p.pe_size));
+          fr.lds_words = std::max(fr.lds_words, lds_of(p, c->L.shape.elems_at(K), K));
         }
       }
       c->grid[list][gi] = fused_grid((int32_t)wf.size() - b);
