@@ -336,6 +336,7 @@ LinKey lin_key(const adg_problem& p) { return LinKey{p.degree, p.speed, p.dt, p.
 struct Shape {
   int elems, kmax;
   int elems1 = 0;  // elements per lane of the one-step launches, if not elems
+  bool any_face = false;  // two elements per lane although a PE size is odd (general stage form)
   int elems_at(int K) const { return K == 1 && elems1 ? elems1 : elems; }
 };
 
@@ -474,11 +475,13 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   if (kern != ADG_KERNEL_FUSED) return s;
   const int64_t elems = total_elems(probs, n);
   const bool one_launch = opt && (opt->flags & ADG_OPT_ONE_LAUNCH);
-  bool all_lin = true, gen = false;
+  bool all_lin = true, gen = false, all_gen = !is_ldg(probs), odd = false;
+  int64_t least = (int64_t)1 << 62;
   for (int32_t i = 0; i < n; ++i) {
     const int f = form_of(probs[i], kern, n_rec);
     all_lin = all_lin && f == FORM_LIN;
     gen = gen || f == FORM_GEN;
+    all_gen = all_gen && f == FORM_GEN;
   }
   if (one_launch)
     s.elems = 2;
@@ -490,7 +493,18 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   }
   for (int32_t i = 0; i < n; ++i)
     if (async_of(probs[i]))
-      while (probs[i].pe_size % s.elems) s.elems >>= 1;
+      odd = odd || probs[i].pe_size % 2, least = std::min(least, probs[i].pe_size);
+  // The general stage form can find a lane's PE face in any element; one
+  // element per lane would leave 44 of 64 lanes to five stages and two steps.
+  // Odd PEs (25), 4.7e6 elements, us per step with one and two: p = 4, a < 0, LSRK4
+  // 98.7, 75.2, SSP-RK3 71.7, 54.2; Burgers, RK4 82.5, 70.7.
+  s.any_face = all_gen && odd && !one_launch && s.elems >= 2 && least >= 2;
+  if (s.any_face)
+    s.elems = 2;
+  else
+    for (int32_t i = 0; i < n; ++i)
+      if (async_of(probs[i]))
+        while (probs[i].pe_size % s.elems) s.elems >>= 1;
   if (!one_launch && (!opt || opt->lane_elems == 0)) s.elems1 = std::min(s.elems, 2);
   if ((opt && opt->fused_steps != 0) || one_launch) return s;
   const int most_halo = is_ldg(probs) ? (elems <= (int64_t)1 << 16 ? 24 : 16) / s.elems
@@ -715,6 +729,7 @@ struct adg_ctx {
     for (int i = 0; i < kFusedRanges; ++i) a.faces[i] = faces[list][i];
     a.lin = (const double*)(ws + L.lin);
     a.elems = L.shape.elems_at(list_steps(list));
+    a.any_face = L.shape.any_face;
     a.steps = K;
     a.halo = fused_halo(rk, a.elems, list_steps(list));
     a.halo_right = ldg_halo_right(rk, a.elems, list_steps(list));

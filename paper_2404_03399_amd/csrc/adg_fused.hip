@@ -13,7 +13,7 @@ namespace adg {
 
 extern __shared__ double wave_lds[];
 
-template <int NP, int RK, int PHYS, int R>
+template <int NP, int RK, int PHYS, int R, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_fused_step(const DevProblem* __restrict__ probs,
                                                        const WorkItem* __restrict__ work,
                                                        const StepClock clock, double* __restrict__ ring,
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_step(const DevProblem* __restr
   const int64_t n = clock.tick(w == w_begin) + step_offset;
   // a range holding one problem lists its tiles in order: no work-list load
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
-  stage_tile<NP, RK, PHYS, R>(probs[wi.prob], wi, ring, n, K, HL, uin, uout, umid, mid_stride, n_faces_max,
+  stage_tile<NP, RK, PHYS, R, ANY>(probs[wi.prob], wi, ring, n, K, HL, uin, uout, umid, mid_stride, n_faces_max,
                               wave_lds + wv * lds_words, lane);
 }
 
@@ -131,10 +131,10 @@ static void fused_ldg_np(const StepArgs& a, const double* uin, double* uout, int
   }
 }
 
-template <int NP, int RK, int PHYS, int R>
+template <int NP, int RK, int PHYS, int R, bool ANY = false>
 static void fused_go_r(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   const FaceRange& fr = a.faces[gi];
-  hipLaunchKernelGGL((k_fused_step<NP, RK, PHYS, R>), dim3(a.grid[gi]), dim3(kBlock),
+  hipLaunchKernelGGL((k_fused_step<NP, RK, PHYS, R, ANY>), dim3(a.grid[gi]), dim3(kBlock),
                      8 * kWavesPerBlock * fr.lds_words, st, a.probs, a.work, a.clock, a.ring, a.group[gi],
                      a.group[gi + 1], uin, uout, a.umid, a.mid_stride, off, a.steps, a.halo, fr.n_faces, fr.lds_words,
                      a.single[gi]);
@@ -142,6 +142,8 @@ static void fused_go_r(const StepArgs& a, int gi, const double* uin, double* uou
 
 template <int NP, int RK, int PHYS>
 static void fused_go(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
+  if constexpr (PHYS != PHYS_ADV_UPWIND_POS)
+    if (a.any_face) return fused_go_r<NP, RK, PHYS, 2, true>(a, gi, uin, uout, off, st);
   switch (a.elems) {
     case 1: fused_go_r<NP, RK, PHYS, 1>(a, gi, uin, uout, off, st); break;
     case 4: fused_go_r<NP, RK, PHYS, 4>(a, gi, uin, uout, off, st); break;

@@ -59,6 +59,7 @@ struct StepArgs {
   FaceRange faces[kFusedRanges];     // fused kernel: PE faces per wave of a range
   int32_t elems;             // fused kernel: elements per lane (1, 2 or 4)
   int32_t steps;             // fused kernel: time steps of the launch (a power of two, at most the list's)
+  int32_t any_face;          // stage form, general flux, two elements per lane: a PE size is odd
   int32_t halo;              // fused kernel: halo lanes per side (upwind, a > 0: on the left) of the work list
   int32_t halo_right;        // local DG: halo lanes on the right
   double* qbuf;              // local DG: q = u_x of the current stage input (state layout)

@@ -25,7 +25,10 @@ namespace adg {
 // the wave it is in (explicit FMAs, contraction off): all launch shapes agree
 // bitwise.
 
-template <int NP, int RK, int PHYS, int R>
+// ANY: R does not divide every PE size, so a lane's PE face (at most one) is
+// the left face of any of its elements; selects find it in every stage, which
+// waves with a face pay for.
+template <int NP, int RK, int PHYS, int R, bool ANY = false>
 __device__ __forceinline__ void stage_tile(const DevProblem& P, const WorkItem wi, double* __restrict__ ring,
                                            int64_t n, int K, int HL, const double* __restrict__ uin,
                                            double* __restrict__ uout, double* __restrict__ umid, int64_t mid_stride,
@@ -33,6 +36,7 @@ __device__ __forceinline__ void stage_tile(const DevProblem& P, const WorkItem w
 #pragma clang fp contract(off)
   constexpr int S = rk_stages(RK);
   constexpr bool POS = PHYS == PHYS_ADV_UPWIND_POS;
+  static_assert(!(POS && ANY), "the correction of a right PE face knows the lane's last element only");
   const WaveElems<R> we(P, wi.tile, HL, POS ? (P.async_faces ? 1 : 0) : HL, lane);
   // the AT weights, ahead of the state in the queue of loads
   double atc = 0.0;
@@ -51,7 +55,16 @@ __device__ __forceinline__ void stage_tile(const DevProblem& P, const WorkItem w
     kl[i] = P.Kl[i];
     kr[i] = P.Kr[i];
   }
-  WaveFaces<S> wf(P, we.e[0], we.own_n > 0, atc, n, K, n_faces_max, lds, lane);
+  int at_r = 0;  // the element right of the lane's PE face
+  if constexpr (ANY)
+    if (P.async_faces)
+#pragma unroll
+      for (int r = 1; r < R; ++r)
+        if ((uint32_t)we.e[r] == fast_div((uint32_t)we.e[r], P.pe_div) * P.pe_div.d) at_r = r;
+  int e_face = we.e[0];
+#pragma unroll
+  for (int r = 1; r < R; ++r) e_face = at_r == r ? we.e[r] : e_face;
+  WaveFaces<S> wf(P, e_face, at_r < we.own_n, atc, n, K, n_faces_max, lds, lane);
   wf.draw(P, ring, n, K, lane);
 
   const double a = P.speed, dt = P.dt;
@@ -88,8 +101,13 @@ __device__ __forceinline__ void stage_tile(const DevProblem& P, const WorkItem w
 #pragma unroll
         for (int r = 1; r < R; ++r) F[r] = Physics<PHYS>::fhat(y[r - 1][NP - 1], y[r][0], a);
         if constexpr (PE) {
-          mine[s] = F[0];
-          F[0] = (kd & ((KdWord)0xff << (8 * s))) != 0 ? at[s] : F[0];
+          const bool late = (kd & ((KdWord)0xff << (8 * s))) != 0;
+          double raw = F[0];
+#pragma unroll
+          for (int r = 1; r < R; ++r) raw = at_r == r ? F[r] : raw;
+          mine[s] = raw;
+#pragma unroll
+          for (int r = 0; r < (ANY ? R : 1); ++r) F[r] = late && at_r == r ? at[s] : F[r];
         }
         double f_last = 0.0;
         if constexpr (!POS || PE) f_last = lane_from_right(F[0]);

@@ -134,3 +134,31 @@ def test_steps_in_a_callers_graph(torch_cuda, ne, n):
     assert np.array_equal(s.unpack(u)[0], ref.unpack(v)[0])
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("eq,flux,rk,p,speed,ne,pe", [
+    ("advection", "upwind", "lsrk4", 4, -0.75, 405, 15), ("advection", "central", "rk4", 3, 1.3, 129, 3),
+    ("burgers", "llf", "ssprk3", 2, 1.0, 125, 125), ("advection", "central", "heun", 1, 1.3, 9, 3)])
+def test_general_form_with_odd_pes(torch_cuda, eq, flux, rk, p, speed, ne, pe):
+    """Two elements per lane on odd PEs, whose faces lie left of either element
+    of a lane (odd meshes, whose lanes straddle the periodic wrap, and one
+    within the halo): bitwise one element per lane at one and at the library's
+    steps per launch, and the oracle's run."""
+    from paper_2404_03399_amd.solver import Solver
+    dt = {1: 0.05, 2: 0.02, 3: 0.005, 4: 0.001}[p] * W.TWO_PI / ne * (0.2 if eq == "burgers" else 1.0)
+    w = W.Workload(name="odd", scheme="adg_at", rk=rk, degree=p, n_elem=ne, pe_size=pe, equation=eq, flux=flux,
+                   probs=W.DELAYS_C2, seed=3, dt=dt, speed=speed, ic=W.PAPER_MULTISINE)
+    n = 21
+    u0 = stepper.initial_state(w)
+    out = {}
+    for R in (1, 2, 0):
+        for K in (1, 0):
+            s = Solver(w, kernel="fused", lane_elems=R, fused_steps=K)
+            u = s.pack(u0)
+            s.run(u, n, graph=R == 2)
+            torch_cuda.cuda.synchronize()
+            out[R, K] = s.unpack(u)[0]
+            s.close()
+    for key, v in out.items():
+        assert np.array_equal(v, out[1, 1]), key
+    assert stats.rel_l2(out[2, 0], stepper.Stepper(w).run(u0, n)) <= 1e-12
