@@ -1247,6 +1247,7 @@ int adg_init_scratch(adg_ctx** out, const adg_problem* probs, int32_t n_probs, c
 int adg_reset(adg_ctx* c) {
   if (!c) return fail(ADG_E_INVALID, "null context");
   if (int rc = check_live(c)) return rc;
+  note_capture(c);  // replays of a captured reset clear the device's counter alone
   return reset_device(c);
 }
 
