@@ -310,14 +310,15 @@ void lin_table(const DevProblem& d, int rk, double* out) {
     }
   }
   for (int i = 0; i < lin_tab_size(np, S); ++i) out[i] = 0.0;
-  for (int c = 0; c < cols; ++c) {
-    const int kind = c < np ? LIN_U : (c < np + S ? LIN_F : LIN_D), j = c - (kind == LIN_U ? 0 : np + (kind - 1) * S);
-    double* o = out + lin_col(np, S, kind, j);
-    // G_s less G_0 = a u_p (it holds no F or delta), u' less u
-    for (int s = kind == LIN_U ? 1 : j + 1; s < S; ++s)
-      *o++ = (double)(a * (y[s][np - 1][c] - (c == np - 1 ? 1.0L : 0.0L)));
-    for (int i = 0; i < np; ++i) *o++ = (double)(y[S][i][c] - (c == i ? 1.0L : 0.0L));
-  }
+  for (int kind = 0; kind < kLinCols; ++kind)
+    for (int j = 0; j < lin_cols(np, S, kind); ++j) {
+      double* o = out + lin_col(np, S, kind, j);
+      const int c = kind == LIN_Z || kind == LIN_A ? j : (kind == LIN_W || kind == LIN_PHI ? np : np + S) + j;
+      if (kind == LIN_Z || kind == LIN_W || kind == LIN_WR)  // g_s of the stages s that the column reaches
+        for (int s = kind == LIN_Z ? 1 : j + 1; s < S; ++s) *o++ = (double)(a * y[s][np - 1][c]);
+      else  // u' less u
+        for (int i = 0; i < np; ++i) *o++ = (double)(y[S][i][c] - (c == i ? 1.0L : 0.0L));
+    }
 }
 
 // Problems with the same operators (one mesh, many delay realizations) share

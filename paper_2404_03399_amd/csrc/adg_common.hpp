@@ -100,21 +100,30 @@ struct DevProblem {
 // upwind advection with a > 0 in flux-sequence form.  With M = dt Kdu,
 // y_s = u + sum_{j<s} a_sj k_j, k_j = M y_j + dt Kl F_j - dt Kr delta_j (F_j
 // the flux applied at the left face, delta_j the applied minus the raw flux at
-// the right face, 0 at an interior face):
-//   G_s = a y_s(last node) = G_0 + Z_s u + sum_{j<s} (W_sj F_j + WR_sj delta_j),  G_0 = a u_p,
-//   u'  = u + A u + sum_s (Phi_s F_s + Psi_s delta_s).
+// the right face, 0 at an interior face) the step is linear in u, F and delta;
+// a constant state with its flux stays as it is, so that only differences from
+// the last node's value u_p enter: d_j = u_j - u_p, f_s = F_s - a u_p,
+//   G_s = a y_s(last node) = a u_p + g_s,  g_0 = 0,
+//   g_s = sum_{j<p} Z_sj d_j + sum_{j<s} (W_sj f_j + WR_sj delta_j),
+//   u'  = u + sum_{j<p} A_j d_j + sum_s (Phi_s f_s + Psi_s delta_s).
 // The table holds columns, the coefficients that one input multiplies:
-//   node j:   Z_1j .. Z_{S-1,j}, A_0j .. A_pj
-//   F_s:      W_{s+1,s} .. W_{S-1,s}, Phi_0s .. Phi_ps
-//   delta_s:  WR, Psi in the same order
+//   LIN_Z j < p:         Z_1j .. Z_{S-1,j}
+//   LIN_W, LIN_WR s < S-1:  W_{s+1,s} .. W_{S-1,s}
+//   LIN_A j < p, LIN_PHI, LIN_PSI s < S:  the np nodes' coefficients
 // A kernel lane holds the entries (lane mod 16) of a run of 16, so a column
 // never crosses a multiple of 16: lin_col gives each column's first entry.
-enum LinCol : int { LIN_U = 0, LIN_F = 1, LIN_D = 2 };
-constexpr int lin_col_len(int np, int S, int kind, int j) { return kind == LIN_U ? S - 1 + np : S - 1 - j + np; }
+// What only PE faces need comes last.
+enum LinCol : int { LIN_Z = 0, LIN_W = 1, LIN_A = 2, LIN_PHI = 3, LIN_WR = 4, LIN_PSI = 5, kLinCols = 6 };
+constexpr int lin_cols(int np, int S, int kind) {
+  return kind == LIN_Z || kind == LIN_A ? np - 1 : (kind == LIN_W || kind == LIN_WR ? S - 1 : S);
+}
+constexpr int lin_col_len(int np, int S, int kind, int j) {
+  return kind == LIN_Z ? S - 1 : (kind == LIN_W || kind == LIN_WR ? S - 1 - j : np);
+}
 constexpr int lin_col(int np, int S, int kind, int j) {
   int at = 0;
-  for (int k = 0; k <= LIN_D; ++k)
-    for (int i = 0; i < (k == LIN_U ? np : S); ++i) {
+  for (int k = 0; k < kLinCols; ++k)
+    for (int i = 0; i < lin_cols(np, S, k); ++i) {
       const int n = lin_col_len(np, S, k, i);
       if (at / 16 != (at + n - 1) / 16) at = (at + 15) / 16 * 16;
       if (k == kind && i == j) return at;
@@ -123,7 +132,7 @@ constexpr int lin_col(int np, int S, int kind, int j) {
   return at;
 }
 // doubles of a table: whole runs of 16
-constexpr int lin_tab_size(int np, int S) { return (lin_col(np, S, LIN_D, S) + 15) / 16 * 16; }
+constexpr int lin_tab_size(int np, int S) { return (lin_col(np, S, kLinCols, 0) + 15) / 16 * 16; }
 
 struct WorkItem {
   int32_t prob;

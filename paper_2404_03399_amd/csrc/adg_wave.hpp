@@ -243,7 +243,7 @@ template <int L, int M>
 __device__ __forceinline__ void fmac_bcast(double c, double x, double* const (&a)[M]) {
 #define ADG_FM(i) "v_fmac_f64_dpp %" #i ", %[c], %[x] row_newbcast:%[l" #i "] row_mask:0xf bank_mask:0xf\n\t"
 #define ADG_IN [c] "v"(c), [x] "v"(x), [l0] "n"(L)
-  static_assert(M >= 1 && M <= 9 && L >= 0 && L + M <= 16, "a column lies within one run of 16");
+  static_assert(M >= 1 && M <= 5 && L >= 0 && L + M <= 16, "a column lies within one run of 16");
   if constexpr (M == 1)
     asm("s_nop 1\n\t" ADG_FM(0) : "+v"(*a[0]) : ADG_IN);
   else if constexpr (M == 2)
@@ -256,30 +256,10 @@ __device__ __forceinline__ void fmac_bcast(double c, double x, double* const (&a
     asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3)
         : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3])
         : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3));
-  else if constexpr (M == 5)
+  else
     asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3) ADG_FM(4)
         : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3]), "+v"(*a[4])
         : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4));
-  else if constexpr (M == 6)
-    asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3) ADG_FM(4) ADG_FM(5)
-        : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3]), "+v"(*a[4]), "+v"(*a[5])
-        : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4), [l5] "n"(L + 5));
-  else if constexpr (M == 7)
-    asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3) ADG_FM(4) ADG_FM(5) ADG_FM(6)
-        : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3]), "+v"(*a[4]), "+v"(*a[5]), "+v"(*a[6])
-        : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4), [l5] "n"(L + 5),
-          [l6] "n"(L + 6));
-  else if constexpr (M == 8)
-    asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3) ADG_FM(4) ADG_FM(5) ADG_FM(6) ADG_FM(7)
-        : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3]), "+v"(*a[4]), "+v"(*a[5]), "+v"(*a[6]), "+v"(*a[7])
-        : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4), [l5] "n"(L + 5),
-          [l6] "n"(L + 6), [l7] "n"(L + 7));
-  else
-    asm("s_nop 1\n\t" ADG_FM(0) ADG_FM(1) ADG_FM(2) ADG_FM(3) ADG_FM(4) ADG_FM(5) ADG_FM(6) ADG_FM(7) ADG_FM(8)
-        : "+v"(*a[0]), "+v"(*a[1]), "+v"(*a[2]), "+v"(*a[3]), "+v"(*a[4]), "+v"(*a[5]), "+v"(*a[6]), "+v"(*a[7]),
-          "+v"(*a[8])
-        : ADG_IN, [l1] "n"(L + 1), [l2] "n"(L + 2), [l3] "n"(L + 3), [l4] "n"(L + 4), [l5] "n"(L + 5),
-          [l6] "n"(L + 6), [l7] "n"(L + 7), [l8] "n"(L + 8));
 #undef ADG_FM
 #undef ADG_IN
 }
