@@ -38,10 +38,12 @@ STAGES = {"rk4": 4, "ssprk3": 3, "heun": 2, "lsrk3": 3, "lsrk4": 5}
 
 def fused_flops_per_elem_step(np_: int, stages: int = 4) -> int:
     """FP64 flops of one RK step of one element in the fused kernel of upwind
-    advection (halo recompute excluded), in flux-sequence form: np node columns
-    of S - 1 fluxes and np new values, one column per flux of the fluxes that
-    follow it and the new values (an FMA each, 2 flops), and G_0 = a u_p."""
-    return 2 * (np_ * (stages - 1 + np_) + stages * (stages - 1) // 2 + stages * np_) + 1
+    advection (halo recompute excluded), in flux-sequence form: the columns of
+    np - 1 differences and of S fluxes that give the S - 1 later fluxes and the np
+    new values (an FMA each, 2 flops, the first of a sum 1), the differences, formed
+    twice, the left face's difference and its flux, the S - 1 and np sums."""
+    fma = (np_ - 1) * (stages - 1 + np_) + stages * (stages - 1) // 2 + stages * np_
+    return 2 * fma - (stages - 1 + np_) + 2 * (np_ - 1) + 2 + (stages - 1) + np_
 
 
 def launch_shape(s, ws):
