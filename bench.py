@@ -46,28 +46,6 @@ def fused_flops_per_elem_step(np_: int, stages: int = 4) -> int:
     return 2 * fma - (stages - 1 + np_) + 2 * (np_ - 1) + 2 + (stages - 1) + np_
 
 
-def launch_shape(s, ws):
-    """Elements per lane and steps per launch of a forward context: its options,
-    or the library's choice by size and halo where they are 0 (PE sizes of 64
-    and more, whose face records limit neither)."""
-    ws = ws if isinstance(ws, (list, tuple)) else [ws]
-    n, S = sum(w.n_elem for w in ws), STAGES[ws[0].rk]
-    ldg = ws[0].equation == "viscous_burgers"
-    lin = all(w.equation == "advection" and w.flux == "upwind" and w.speed > 0 and w.n_elem >= 1024 for w in ws)
-    two, four = (1 << 16, 1 << 19) if lin or ldg else (0, 1 << 18)
-    R = s.opt.lane_elems or (4 if n >= four else 2 if n >= two else 1)
-    if ldg:
-        most = (24 if n <= 1 << 16 else 16) // R
-    elif lin:
-        most = 40 if n <= 1 << 18 else 20
-    else:
-        most = 21 if n <= 1 << 16 else 8
-    K = 8
-    while K > 2 and -(-K * S // R) > most:
-        K //= 2
-    return R, s.opt.fused_steps or K
-
-
 FUSED_SOURCES = ("adg_fused.hip", "adg_linear.hip", "adg_linear.hpp", "adg_wave.hpp", "adg_device.hpp",
                  "adg_common.hpp", "adg_launch.hpp")
 
@@ -407,7 +385,7 @@ def bench_burgers(torch, W, Solver, n_elem: int = 1 << 22, steps: int = 200):
     (q=3), SSP-RK3, 16384 PEs of 256, on the fused kernel at its tuned shape."""
     w = W.c3_burgers(n_elem=n_elem, n_steps=steps)
     s = Solver(w, lane_elems="auto")
-    R, K = launch_shape(s, w)
+    R, K = s.launch_shape()
     u = s.initial_state()
     g, reps, _ = time_solver(torch, s, u, steps, 20)
     finite = bool(torch.isfinite(u).all().item())
@@ -439,7 +417,7 @@ def bench_viscous_burgers(torch, W, Solver, n_elem: int = 1 << 20, steps: int = 
     finite = True
     for kernel in ("fused", "stage"):
         s = Solver(w, kernel=kernel)
-        K = launch_shape(s, w)[1] if kernel == "fused" else 1
+        K = s.launch_shape()[1] if kernel == "fused" else 1
         u = s.initial_state()
         g, _, _ = time_solver(torch, s, u, steps, 20)
         finite = finite and bool(torch.isfinite(u).all().item())
@@ -465,7 +443,7 @@ def bench_ensemble(torch, W, Solver, n_steps: int, n_real: int, plain: bool, lan
     group = [int(w.name.split("_")[1][1:]) for w in ws]
     dofs = sum(w.n_elem * (w.degree + 1) for w in ws)
     s = Solver(ws, lane_elems="auto") if lane_elems < 0 else Solver(ws, lane_elems=lane_elems, fused_steps=2)
-    R, K = launch_shape(s, ws)
+    R, K = s.launch_shape()
 
     def timed(sv, uu, init, reps):
         # the step graph is captured on this buffer first; every rep restarts
@@ -581,7 +559,7 @@ def bench_large(torch, W, Solver, steps: int, n_elem: int = 1 << 24):
     launch shape; with its own roofline block."""
     wl = W.c2_advection_large("adg_at", n_elem=n_elem)
     so = Solver(wl, lane_elems="auto")
-    R, K = launch_shape(so, wl)
+    R, K = so.launch_shape()
     uu = so.initial_state()
     g, reps, _ = time_solver(torch, so, uu, steps, 16)
     finite = bool(torch.isfinite(uu).all().item())
@@ -659,7 +637,7 @@ def main():
     w = W.c2_advection_large("adg_at", n_elem=args.n_elem)
     s = Solver(w, kernel=args.kernel, lane_elems="auto" if args.lane_elems < 0 else args.lane_elems,
                fused_steps=args.fused_steps)
-    R, K = launch_shape(s, w) if args.kernel == "fused" else (1, 1)
+    R, K = s.launch_shape() if args.kernel == "fused" else (1, 1)
     u = s.initial_state()
     gpu_s, rep_s, wall = time_solver(torch, s, u, args.steps, args.warmup)
     dofs = w.n_elem * (w.degree + 1)

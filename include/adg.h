@@ -193,6 +193,16 @@ int adg_state_layout(const adg_problem* probs, int32_t n_probs, int64_t* offsets
 int adg_workspace_size(const adg_problem* probs, int32_t n_probs, const adg_options* opt,
                        int64_t n_steps_record, int64_t* bytes_out);
 
+/* Launch shape that adg_run takes for these problems, options and horizon:
+ * time steps of the first launch of a call of n_steps >= 1 steps, and
+ * consecutive elements per lane in it (1 and 1 for ADG_KERNEL_STAGE).  Results
+ * do not depend on it; it is for callers that time or count launches.  A
+ * context on the scratch array may take fewer steps (see adg_init_scratch).
+ * Host-only; ADG_E_INVALID for null outputs, n_steps < 1 and what
+ * adg_workspace_size refuses. */
+int adg_launch_shape(const adg_problem* probs, int32_t n_probs, const adg_options* opt, int64_t n_steps_record,
+                     int64_t n_steps, int32_t* lane_elems, int32_t* steps_per_launch);
+
 /* Set up the problem statement: u_t + f(u)_x = 0 on a periodic interval
  * split into n_elem elements (Sec. 2, model problem and mesh), grouped into
  * P = n_elem / pe_size processing elements (Sec. 2 parallel implementation,

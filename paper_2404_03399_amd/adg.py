@@ -41,7 +41,7 @@ ADG_RUN_CHECK_FINITE = 4
 
 SYMBOLS = [
     "adg_abi_version", "adg_last_error", "adg_build_id", "adg_nodes", "adg_state_layout", "adg_workspace_size",
-    "adg_init", "adg_init_scratch", "adg_reset", "adg_step_count", "adg_step", "adg_run", "adg_adjoint",
+    "adg_launch_shape", "adg_init", "adg_init_scratch", "adg_reset", "adg_step_count", "adg_step", "adg_run", "adg_adjoint",
     "adg_error_stats", "adg_ensemble_stats", "adg_delay_schedule", "adg_destroy",
 ]
 
@@ -97,6 +97,7 @@ def lib() -> C.CDLL:
             "adg_nodes": ([I32, P(D)], C.c_int),
             "adg_state_layout": ([P(adg_problem), I32, P(I64), P(I64), P(I64)], C.c_int),
             "adg_workspace_size": ([P(adg_problem), I32, P(adg_options), I64, P(I64)], C.c_int),
+            "adg_launch_shape": ([P(adg_problem), I32, P(adg_options), I64, I64, P(I32), P(I32)], C.c_int),
             "adg_init": ([P(vp), P(adg_problem), I32, P(adg_options), I64, vp, I64, vp], C.c_int),
             "adg_init_scratch": ([P(vp), P(adg_problem), I32, P(adg_options), vp], C.c_int),
             "adg_reset": ([vp], C.c_int),
@@ -155,6 +156,16 @@ def adg_workspace_size(probs, opt: adg_options, n_steps_record: int = 0) -> int:
     out = C.c_int64()
     check(lib().adg_workspace_size(arr, n, C.byref(opt), n_steps_record, C.byref(out)), "adg_workspace_size")
     return out.value
+
+
+def adg_launch_shape(probs, opt: adg_options, n_steps_record: int, n_steps: int):
+    """(elements per lane, steps) of the first launch of a call of n_steps steps."""
+    n = len(probs)
+    arr = (adg_problem * n)(*probs)
+    r, k = C.c_int32(), C.c_int32()
+    check(lib().adg_launch_shape(arr, n, C.byref(opt), n_steps_record, n_steps, C.byref(r), C.byref(k)),
+          "adg_launch_shape")
+    return r.value, k.value
 
 
 def adg_init(probs, opt: adg_options, n_steps_record: int, d_workspace: int, workspace_bytes: int, stream: int):

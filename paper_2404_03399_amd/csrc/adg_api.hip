@@ -1003,6 +1003,23 @@ int adg_workspace_size(const adg_problem* probs, int32_t n_probs, const adg_opti
   return ADG_OK;
 }
 
+int adg_launch_shape(const adg_problem* probs, int32_t n_probs, const adg_options* opt, int64_t n_steps_record,
+                     int64_t n_steps, int32_t* lane_elems, int32_t* steps_per_launch) {
+  int64_t need = 0;
+  const int rc = adg_workspace_size(probs, n_probs, opt, n_steps_record, &need);
+  if (rc) return rc;
+  if (!lane_elems || !steps_per_launch || n_steps < 1) return fail(ADG_E_INVALID, "adg_launch_shape: bad arguments");
+  if (kernel_of(probs, opt) != ADG_KERNEL_FUSED) {
+    *lane_elems = *steps_per_launch = 1;
+    return ADG_OK;
+  }
+  const Shape s = shape_of(probs, n_probs, opt, n_steps_record);
+  const int K = steps_within(s.kmax, n_steps);
+  *lane_elems = s.elems_at(K);
+  *steps_per_launch = K;
+  return ADG_OK;
+}
+
 int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg_options* opt, int64_t n_steps_record,
              void* d_workspace, int64_t workspace_bytes, void* hip_stream) {
   if (!out) return fail(ADG_E_INVALID, "out is null");

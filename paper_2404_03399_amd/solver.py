@@ -93,6 +93,7 @@ class Solver:
             self.opt.flags = adg.ADG_OPT_PE_SPLIT_ON if pe_split else adg.ADG_OPT_PE_SPLIT_OFF
         if one_launch:
             self.opt.flags |= adg.ADG_OPT_ONE_LAUNCH
+        self.n_steps_record = n_steps_record
         self.ws_bytes = adg.adg_workspace_size(self.probs, self.opt, n_steps_record)
         self.stream = stream
         if scratch:
@@ -202,6 +203,11 @@ class Solver:
         flags = (adg.ADG_RUN_GRAPH if graph else 0) | (adg.ADG_RUN_RECORD if record else 0) | \
                 (adg.ADG_RUN_CHECK_FINITE if check_finite else 0)
         adg.adg_run(self.ctx, self.state_ptr(u), n_steps, flags)
+
+    def launch_shape(self, n_steps: int = 16):
+        """(elements per lane, steps) of the first launch of a run of n_steps
+        steps (adg_launch_shape)."""
+        return adg.adg_launch_shape(self.probs, self.opt, self.n_steps_record, n_steps)
 
     def capture_graph(self, u: torch.Tensor):
         """Capture the step graph for buffer u without stepping (adg_run with
