@@ -35,6 +35,7 @@ bool state_aligned(const void* p) { return ((uintptr_t)p & 15u) == 0; }
   } while (0)
 
 constexpr int64_t kAlign = 256;
+constexpr int kGraphSteps = 16;  // steps of a batch: an even number of launches, which ends in the caller's buffer
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
 // ------------------------------------------------ reference element (host) --
@@ -333,12 +334,19 @@ struct LinKey {
 };
 LinKey lin_key(const adg_problem& p) { return LinKey{p.degree, p.speed, p.dt, p.length, p.n_elem}; }
 
+// Work lists of the fused kernel, one per number of steps: a launch of K steps
+// takes tiles whose halo holds K.
+constexpr int kLists = 4;
+static_assert(1 << (kLists - 1) == kMaxSteps, "lists of 1, 2, 4 and 8 steps");
+int list_of(int K) { return __builtin_ctz((unsigned)K); }
+
 // Launch shape of the fused kernel: elements per lane and most steps per launch.
 struct Shape {
   int elems, kmax;
-  int elems1 = 0;  // elements per lane of the one-step launches, if not elems
+  int elems1 = 0, elems2 = 0;  // elements per lane of launches of one and two steps, if not elems
   bool any_face = false;  // two elements per lane although a PE size is odd (general stage form)
-  int elems_at(int K) const { return K == 1 && elems1 ? elems1 : elems; }
+  bool halve4 = false, halve8 = false;  // halves_first may split a launch of four, of eight steps
+  int elems_at(int K) const { return K == 1 && elems1 ? elems1 : (K == 2 && elems2 ? elems2 : elems); }
 };
 
 struct Layout {
@@ -346,12 +354,14 @@ struct Layout {
   Shape adj[2];              // of the fused reverse sweep, per list
   int depth_steps;           // steps per launch that the ring holds
   int64_t lin, lin_doubles;  // tables of the linear form
-  int64_t probs, work_f, work_f2, work_s, first_s, ctr, ring, state2, y0, y1, acc, qbuf, part, stats_out;
+  int64_t probs, work_f, work_s, first_s, ctr, ring, state2, y0, y1, acc, qbuf, part, stats_out;
   int64_t groups, gstats;  // ensemble statistics: group CSR (2n+1 int32) and 4 doubles per group
   // adjoint recording (-1 if not recording)
   int64_t ckpt, useg, ybuf, lam, q, adjring, cpart, work_a[2];
   int64_t total;
-  int32_t n_work_f, n_work_f2, n_work_s, n_work_a[2];
+  int32_t n_work_f[kLists];    // items of the fused kernel's lists,
+  int32_t at_f[kLists + 1];    // where each list's room starts in work_f, and the end
+  int32_t n_work_s, n_work_a[2];
   int64_t n_parts;  // partial sums of dJ/da of the fused reverse sweep
   int64_t total_doubles;
   int64_t ring_doubles;
@@ -460,9 +470,11 @@ int lds_of(const adg_problem& p, int elems, int K) {
 //                 2.76, 2.93; 2^18 5.01, 4.25, 4.12; 2^22 (2,4) 31.8, (4,4) 29.3,
 //                 (4,8) 31.0; five stages (lsrk4, p = 2) 2^22 (4,4) 27.0, (4,8)
 //                 30.6; 10^5, p = 4, lsrk4, PE 30 (2,2) 4.2, (2,4) 4.5, (2,8) 5.4
-//   one step per launch is bound by HBM, which two elements per lane, with more
-//                 waves in flight, reach better: single steps at 2^23, Burgers,
-//                 RK4 (2,1) 225, (4,1) 242; SSP-RK3, p = 2 171, 178
+//   one and two steps per launch are bound by HBM, which two elements per lane,
+//                 with more waves in flight, reach better (an explicit number of
+//                 elements keeps its own for two): 2^20 central (2,1) 16.9, (4,1)
+//                 19.1, (2,2) 11.0, (4,2) 11.7; Burgers, SSP-RK3, p = 2 14.1, 16.1,
+//                 9.3, 10.0; a > 0 14.8, 17.6, 8.6, 9.6; local DG 14.4, 15.9, 9.1, 9.8
 //   general, Burgers, SSP-RK3, p = 2   2^22 (2,4) 26.2, (4,4) 24.0, (4,8) 23.7
 //   local DG, p = 2   Heun 2^14 (1,4) 2.02, (1,8) 1.79, (2,8) 1.85; 2^16 2.35, 2.10,
 //                 1.92; 2^18 (2,8) 3.16, (4,8) 3.53; 2^20 8.11, 7.43; SSP-RK3 2^14
@@ -475,6 +487,8 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   Shape s{std::max(1, lane_elems_of(probs, n, opt)), kern == ADG_KERNEL_FUSED ? std::max(1, fused_steps_of(opt)) : 1};
   if (kern != ADG_KERNEL_FUSED) return s;
   const int64_t elems = total_elems(probs, n);
+  uint32_t degree = 0;
+  for (int32_t i = 0; i < n; ++i) degree = std::max(degree, probs[i].degree);
   const bool one_launch = opt && (opt->flags & ADG_OPT_ONE_LAUNCH);
   bool all_lin = true, gen = false, all_gen = !is_ldg(probs), odd = false;
   int64_t least = (int64_t)1 << 62;
@@ -506,7 +520,12 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
     for (int32_t i = 0; i < n; ++i)
       if (async_of(probs[i]))
         while (probs[i].pe_size % s.elems) s.elems >>= 1;
-  if (!one_launch && (!opt || opt->lane_elems == 0)) s.elems1 = std::min(s.elems, 2);
+  s.halve8 = elems >= (int64_t)1 << 18;
+  s.halve4 = s.halve8 && (elems < (int64_t)1 << 21 || is_ldg(probs) || (!all_lin && degree >= 2));
+  if (!one_launch) {
+    s.elems1 = std::min(s.elems, 2);
+    if (!opt || opt->lane_elems == 0) s.elems2 = s.elems1;
+  }
   if ((opt && opt->fused_steps != 0) || one_launch) return s;
   const int most_halo = is_ldg(probs) ? (elems <= (int64_t)1 << 16 ? 24 : 16) / s.elems
                         : gen ? (elems <= (int64_t)1 << 16 ? 21 : 8)
@@ -521,6 +540,36 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   while (K > 2 && !fits(K)) K >>= 1;
   s.kmax = K;
   return s;
+}
+
+// Steps of the next launch with `left` steps to go.
+int steps_within(int kmax, int64_t left) {
+  int K = kmax;
+  while (K > left) K >>= 1;
+  return K;
+}
+
+// Whether the last m steps of a call (all of them, up to a batch), from the
+// caller's buffer (in_place) or the other one, halve their first launch: an odd
+// number of launches ends in the other buffer and costs a copy of the state.  One
+// more launch is the cheaper one from 2^18 elements on, for eight steps always,
+// for four unless they are bound by HBM, as the copy is (the linear form and p = 1
+// from 2^21 on).  us per step with the copy and halved, calls of four and of
+// eight steps, PE 256:
+//   central, RK4, p = 3   2^17 3.58, 3.56 and 2.31, 2.32; 2^18 5.82, 4.49 and 4.07,
+//                         3.65; 2^20 10.9, 10.5 and 9.1, 8.0; 2^22 36.8, 33.4 and
+//                         31.0, 24.8
+//   upwind, RK4, p = 3    2^18 4.62, 3.74 and 3.02, 2.53; 2^20 8.96, 8.49 and 5.92,
+//                         6.01; 2^22 29.4, 30.1 and 19.0, 17.1
+//   upwind, Heun, p = 1   2^17 2.29, 2.54; 2^20 6.64, 5.35 and 4.05, 3.37; 2^22 14.0,
+//                         14.2 and 9.5, 8.8; 2^23 29.5, 33.1 and 18.9, 17.6
+//   local DG, Heun, p = 2 2^18 4.40, 3.89 and 2.98, 2.68; 2^22 26.3, 24.1 and 20.9, 18.9
+bool halves_first(const Shape& s, int32_t m, bool in_place) {
+  const int K = steps_within(s.kmax, m);
+  if (!(K == 8 ? s.halve8 : (K == 4 && s.halve4))) return false;
+  int launches = 0;
+  for (int32_t i = 0; i < m; ++launches) i += steps_within(s.kmax, m - i);
+  return (launches % 2 == 1) == in_place;
 }
 
 // Lists of the fused reverse sweep: with the forward stages, and (advection
@@ -579,16 +628,12 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   const int S = rk_stages((int)probs[0].rk);
   const int kern = kernel_of(probs, opt);
   L.shape = shape_of(probs, n, opt, n_rec);
-  // the list of several steps also where the option asks for one: the
-  // recording of every state can take it
-  const int K2 = std::max(2, L.shape.kmax);
   // room as without ADG_OPT_ONE_LAUNCH (whose own shape may be another), so
   // that the workspace does not depend on it
   adg_options plain = opt ? *opt : adg_options{};
   plain.flags &= ~ADG_OPT_ONE_LAUNCH;
   const Shape rs = shape_of(probs, n, &plain, n_rec);
-  const int RK2 = std::max(2, rs.kmax);
-  L.depth_steps = std::max(K2, RK2);
+  L.depth_steps = std::max({2, L.shape.kmax, rs.kmax});
   std::set<LinKey> tables;
   const bool nl = probs[0].equation == ADG_EQ_BURGERS;
   int TA[2];
@@ -596,18 +641,18 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
     L.adj[list] = adj_shape_of(probs, n, opt, list);
     TA[list] = adj_tile_elems((int)probs[0].rk, nl, L.adj[list].elems, L.adj[list].kmax);
   }
-  int64_t nwf = 0, nwf2 = 0, nws = 0, nwa[2] = {0, 0}, tot = 0, ring = 0, room1 = 0, room2 = 0,
-          win[2] = {0, 0};
+  int64_t nwf[kLists] = {}, room[kLists] = {}, nws = 0, nwa[2] = {0, 0}, tot = 0, ring = 0;
   const bool split = pe_split_of(probs, n, opt);
   for (int32_t i = 0; i < n; ++i) {
     const adg_problem& p = probs[i];
     const int form = form_of(p, kern, n_rec);
     auto tiles = [&](int T) { return (p.n_elem + T - 1) / T; };
-    const int64_t t1 = tiles(tile_of(p, form, L.shape, 1)), t2 = tiles(tile_of(p, form, L.shape, K2));
-    nwf += t1;
-    nwf2 += t2;
-    room1 += std::max(t1, tiles(tile_of(p, form, rs, 1)));
-    room2 += std::max(t2, tiles(tile_of(p, form, rs, RK2)));
+    for (int li = 0; li < kLists; ++li) {
+      const int K = 1 << li;
+      const int64_t t = K <= L.shape.kmax ? tiles(tile_of(p, form, L.shape, K)) : 0;
+      nwf[li] += t;
+      room[li] += K <= rs.kmax ? std::max(t, tiles(tile_of(p, form, rs, K))) : t;
+    }
     if (form == FORM_LIN && tables.insert(lin_key(p)).second) L.lin_doubles += lin_tab_size((int)p.degree + 1, S);
     for (int list = 0; list < 2; ++list) nwa[list] += tiles(TA[list]);
     L.n_parts += tiles(adj_part_elems((int)p.rk));
@@ -616,15 +661,17 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
     if (split && async_of(p))  // room for the window items of a PE-face split
       for (int K = 1; K <= 2; ++K) {
         const int64_t fw = fused_windows_per_wave((int)p.rk, K);
-        win[K - 1] += (p.n_elem / p.pe_size + fw - 1) / fw;
+        room[list_of(K)] += (p.n_elem / p.pe_size + fw - 1) / fw;
       }
     if (async_of(p)) {
       // local DG keeps a second ring of the same shape for u-hat
       ring += (is_ldg(probs) ? 2 : 1) * (p.n_elem / p.pe_size) * S * depth_of(p, n_rec, L.depth_steps);
     }
   }
-  L.n_work_f = (int32_t)nwf;
-  L.n_work_f2 = (int32_t)nwf2;
+  for (int li = 0; li < kLists; ++li) {
+    L.n_work_f[li] = (int32_t)nwf[li];
+    L.at_f[li + 1] = L.at_f[li] + (int32_t)room[li];
+  }
   L.n_work_s = (int32_t)nws;
   L.n_work_a[ADJ_FWD] = n_rec > 0 ? (int32_t)nwa[ADJ_FWD] : 0;
   L.n_work_a[ADJ_LINEAR] = n_rec > 0 && probs[0].equation == ADG_EQ_ADVECTION ? (int32_t)nwa[ADJ_LINEAR] : 0;
@@ -634,8 +681,7 @@ Layout make_layout(const adg_problem* probs, int32_t n, const adg_options* opt, 
   auto take = [&](int64_t bytes) { const int64_t o = off; off = align_up(off + bytes, kAlign); return o; };
   L.probs = take((int64_t)sizeof(DevProblem) * n);
   L.lin = take(8 * L.lin_doubles);
-  L.work_f = take((int64_t)sizeof(WorkItem) * (room1 + win[0]));
-  L.work_f2 = take((int64_t)sizeof(WorkItem) * (room2 + win[1]));
+  L.work_f = take((int64_t)sizeof(WorkItem) * L.at_f[kLists]);
   L.work_s = take((int64_t)sizeof(WorkItem) * nws);
   L.first_s = take((int64_t)sizeof(int32_t) * (n + 1));
   L.ctr = take(8 * sizeof(int64_t));
@@ -703,21 +749,19 @@ struct adg_ctx {
   const double* graph_u = nullptr;
   int graph_steps = 0;
 
-  // fused work lists: one step per launch, and several (the list's halo holds
-  // kmax steps, or two)
-  int32_t group[2][kFusedRanges + 1] = {};
-  int32_t grid[2][kFusedRanges] = {};
-  int32_t single[2][kFusedRanges] = {};
-  FaceRange faces[2][kFusedRanges] = {};
+  // fused work lists
+  int32_t group[kLists][kFusedRanges + 1] = {};
+  int32_t grid[kLists][kFusedRanges] = {};
+  int32_t single[kLists][kFusedRanges] = {};
+  FaceRange faces[kLists][kFusedRanges] = {};
   int32_t one_launch = 0;  // ADG_OPT_ONE_LAUNCH
   int adj_steps = kMaxSteps;  // of a reverse launch at most, as the option asks
   // fused adjoint work list (recording contexts of the fused kernel)
   AdjArgs adj[2] = {};  // per list, but for the steps of a launch
 
-  int list_steps(int list) const { return list == 0 ? 1 : std::max(2, L.shape.kmax); }
   StepArgs base_args(int64_t work_off, int32_t n_work, int K = 1) const {
     StepArgs a{};
-    const int list = K > 1 ? 1 : 0;  // work list
+    const int list = list_of(K);
     a.probs = (const DevProblem*)(ws + L.probs);
     a.work = (const WorkItem*)(ws + work_off);
     a.n_work = n_work;
@@ -729,17 +773,18 @@ struct adg_ctx {
     for (int i = 0; i < kFusedRanges; ++i) a.single[i] = single[list][i];
     for (int i = 0; i < kFusedRanges; ++i) a.faces[i] = faces[list][i];
     a.lin = (const double*)(ws + L.lin);
-    a.elems = L.shape.elems_at(list_steps(list));
+    a.elems = L.shape.elems_at(K);
     a.any_face = L.shape.any_face;
     a.steps = K;
-    a.halo = fused_halo(rk, a.elems, list_steps(list));
-    a.halo_right = ldg_halo_right(rk, a.elems, list_steps(list));
+    a.halo = fused_halo(rk, a.elems, K);
+    a.halo_right = ldg_halo_right(rk, a.elems, K);
     a.one_launch = one_launch;
     a.qbuf = L.qbuf >= 0 ? (double*)(ws + L.qbuf) : nullptr;
     return a;
   }
   StepArgs fused_args(int K = 1) const {
-    return K > 1 ? base_args(L.work_f2, L.n_work_f2, K) : base_args(L.work_f, L.n_work_f, 1);
+    const int list = list_of(K);
+    return base_args(L.work_f + (int64_t)sizeof(WorkItem) * L.at_f[list], L.n_work_f[list], K);
   }
   StepArgs stage_args() const { return base_args(L.work_s, L.n_work_s); }
 
@@ -780,20 +825,16 @@ int launch_stages(adg_ctx* c, const StepArgs& a, double* U, int32_t step_offset,
   return ADG_OK;
 }
 
-// Steps of the next launch with `left` steps to go.
-int steps_within(int kmax, int64_t left) {
-  int K = kmax;
-  while (K > left) K >>= 1;
-  return K;
-}
 int next_steps(const adg_ctx* c, int64_t left) { return steps_within(c->L.shape.kmax, left); }
 
 // m steps, as many per launch as the kernel allows, the step counter included.
 // The state goes from *cur through `dst(i)` for each launch's result after i
 // steps of the batch (mid(i): states within a launch, or null).  n0: index of
 // the first step, or -1 to count from the device's counter.
+// halve: the first launch takes half of its steps and a second one the others.
 template <class Dst, class Mid>
-int enqueue_batch(adg_ctx* c, double* cur, int32_t m, int64_t n0, hipStream_t st, Dst dst, Mid mid) {
+int enqueue_batch(adg_ctx* c, double* cur, int32_t m, int64_t n0, hipStream_t st, Dst dst, Mid mid,
+                  bool halve = false) {
   int64_t* ctr = c->ctr();
   if (c->kernel != ADG_KERNEL_FUSED) {
     const StepArgs a = c->stage_args();
@@ -802,8 +843,9 @@ int enqueue_batch(adg_ctx* c, double* cur, int32_t m, int64_t n0, hipStream_t st
     ADG_HIP(launch_advance(ctr, m, st));
     return ADG_OK;
   }
+  const int K0 = next_steps(c, m);
   for (int32_t i = 0; i < m;) {
-    const int K = next_steps(c, m - i);
+    const int K = halve && i < K0 ? K0 / 2 : next_steps(c, m - i);
     const bool first = i == 0, last = i + K >= m;
     StepClock clock{ctr + (n0 >= 0 ? CTR_ZERO : (first ? CTR_DONE : CTR_BATCH)), nullptr, 0};
     if (n0 >= 0) {
@@ -823,14 +865,14 @@ int enqueue_batch(adg_ctx* c, double* cur, int32_t m, int64_t n0, hipStream_t st
 }
 
 // The same between *cur and *other, which are swapped with every launch.
-int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, int64_t n0, hipStream_t st) {
+int enqueue_batch(adg_ctx* c, double** cur, double** other, int32_t m, int64_t n0, hipStream_t st, bool halve = false) {
   return enqueue_batch(
       c, *cur, m, n0, st,
       [&](int32_t) {
         std::swap(*cur, *other);
         return *cur;
       },
-      [](int32_t) { return (double*)nullptr; });
+      [](int32_t) { return (double*)nullptr; }, halve);
 }
 
 // Whether the context's stream is being captured by the caller (then, and from
@@ -860,8 +902,6 @@ void drop_graph(adg_ctx* c) {
   c->graph_u = nullptr;
   c->graph_steps = 0;
 }
-
-constexpr int kGraphSteps = 16;  // even: the fused ping-pong ends in the caller's buffer
 
 int build_graph(adg_ctx* c, double* d_u) {
   drop_graph(c);
@@ -1014,7 +1054,8 @@ int adg_launch_shape(const adg_problem* probs, int32_t n_probs, const adg_option
     return ADG_OK;
   }
   const Shape s = shape_of(probs, n_probs, opt, n_steps_record);
-  const int K = steps_within(s.kmax, n_steps);
+  int K = steps_within(s.kmax, n_steps);
+  if (n_steps <= kGraphSteps && halves_first(s, (int32_t)n_steps, true)) K /= 2;
   *lane_elems = s.elems_at(K);
   *steps_per_launch = K;
   return ADG_OK;
@@ -1125,14 +1166,14 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   std::vector<int32_t> order(n_probs);
   for (int32_t i = 0; i < n_probs; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return probs[a].degree > probs[b].degree; });
-  std::vector<WorkItem> wfk[2], ws_;
+  std::vector<WorkItem> wf_all(c->L.at_f[kLists]), ws_;
   std::vector<int32_t> first(n_probs + 1, 0);
   if (opt && opt->fused_steps != 0) c->adj_steps = (int)opt->fused_steps;
   c->one_launch = (opt && (opt->flags & ADG_OPT_ONE_LAUNCH)) ? 1 : 0;
-  for (int list = 0; list < 2; ++list) {  // one and several steps per launch
-    const int K = c->list_steps(list);
-    std::vector<WorkItem>& wf = wfk[list];
-    wf.reserve(list == 0 ? c->L.n_work_f : c->L.n_work_f2);
+  for (int list = 0; list < kLists && 1 << list <= c->L.shape.kmax; ++list) {
+    const int K = 1 << list;
+    std::vector<WorkItem> wf;
+    wf.reserve(c->L.n_work_f[list]);
     // ranges per degree, np = 5, 4, 3, 2 (order is sorted by degree,
     // descending), each split by form
     for (int gi = 0; gi < kFusedRanges; ++gi) {
@@ -1157,10 +1198,11 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
       c->single[list][gi] = n_in == 1 ? wf[b].prob : -1;
     }
     c->group[list][kFusedRanges] = (int32_t)wf.size();
-    if ((int64_t)wf.size() != (list == 0 ? c->L.n_work_f : c->L.n_work_f2)) {
+    if ((int64_t)wf.size() != c->L.n_work_f[list] || (int64_t)wf.size() > c->L.at_f[list + 1] - c->L.at_f[list]) {
       delete c;
       return fail(ADG_E_INVALID, "internal: fused work list does not match the workspace layout");
     }
+    std::copy(wf.begin(), wf.end(), wf_all.begin() + c->L.at_f[list]);
   }
   for (int32_t i = 0; i < n_probs; ++i) {  // stage/stats list in problem order (contiguous per problem)
     first[i] = (int32_t)ws_.size();
@@ -1210,8 +1252,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   };
   if ((rc = up(c->L.probs, c->dev.data(), (int64_t)sizeof(DevProblem) * n_probs)) ||
       (c->L.lin_doubles > 0 && (rc = up(c->L.lin, lin_tabs.data(), 8 * c->L.lin_doubles))) ||
-      (rc = up(c->L.work_f, wfk[0].data(), (int64_t)sizeof(WorkItem) * wfk[0].size())) ||
-      (rc = up(c->L.work_f2, wfk[1].data(), (int64_t)sizeof(WorkItem) * wfk[1].size())) ||
+      (rc = up(c->L.work_f, wf_all.data(), (int64_t)sizeof(WorkItem) * wf_all.size())) ||
       (rc = up(c->L.work_s, ws_.data(), (int64_t)sizeof(WorkItem) * ws_.size())) ||
       (rc = up(c->L.first_s, first.data(), (int64_t)sizeof(int32_t) * first.size())) ||
       (c->L.work_a[0] >= 0 &&
@@ -1342,7 +1383,9 @@ int adg_run(adg_ctx* c, double* d_u, int64_t n_steps, uint32_t flags) {
   // remaining steps in batches of at most kGraphSteps
   while (left > 0) {
     const int32_t m = (int32_t)std::min<int64_t>(left, kGraphSteps);
-    if ((rc = enqueue_batch(c, &cur, &other, m, c->device_clock ? -1 : c->steps + n_steps - left, c->stream))) return rc;
+    const bool halve = c->kernel == ADG_KERNEL_FUSED && left == m && halves_first(c->L.shape, m, cur == d_u);
+    if ((rc = enqueue_batch(c, &cur, &other, m, c->device_clock ? -1 : c->steps + n_steps - left, c->stream, halve)))
+      return rc;
     left -= m;
   }
   if (cur != d_u)

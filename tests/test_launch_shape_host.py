@@ -50,6 +50,19 @@ def test_one_step_launches_take_two_elements():
     assert _shape(w, 16, fused_steps=1) == (2, 1)
 
 
+def test_calls_of_few_steps():
+    """Each number of steps has a list of its own, so that a launch of two steps
+    takes two elements per lane where eight take four; a call whose launches
+    would end in the other buffer halves its first one from 2^18 elements on."""
+    w = _w(1 << 20, 256, flux="central")
+    assert [_shape(w, n)[1] for n in (1, 2, 3, 4, 5, 6, 7, 8, 9, 14, 15, 16, 100)] == [
+        1, 2, 2, 2, 4, 4, 2, 4, 8, 4, 8, 8, 8]
+    assert _shape(w, 2) == (2, 2) and _shape(w, 16) == (4, 8)
+    assert _shape(_w(1 << 17, 256), 8)[1] == 8 and _shape(_w(1 << 18, 256), 8)[1] == 4
+    assert _shape(_w(1 << 22, 256), 4)[1] == 4 and _shape(_w(1 << 22, 256), 8)[1] == 4
+    assert _shape(w, 4, lane_elems=4)[0] == 4 and _shape(w, 1, lane_elems=4)[0] == 2
+
+
 def test_bad_arguments():
     with pytest.raises(adg.AdgError):
         _shape(_w(64, 16), 0)
