@@ -23,6 +23,7 @@ import re
 import statistics
 import sys
 import time
+from fractions import Fraction
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
@@ -60,12 +61,12 @@ def kernel_source_hash() -> str:
 
 def ring_bytes_per_step(w) -> float:
     """PE-face ring traffic per step: each stage writes one flux per boundary
-    and reads up to q past levels."""
+    and, where its delay is not 0, reads up to q past levels."""
     if w.scheme == "dg" or w.n_pe <= 1:
         return 0.0
     q = (w.at_levels or w.degree + 1) if w.scheme == "adg_at" else 1
-    stages = STAGES[w.rk]
-    return w.n_pe * stages * 8.0 * (1 + q)
+    late = 2 / 5 if w.caa else 1.0 - float(Fraction(w.probs[0]))
+    return w.n_pe * STAGES[w.rk] * 8.0 * (1 + late * q)
 
 
 def read_traffic(lane_elems: int, steps_per_launch: int, n_elem: int = 1 << 20, profile: str = ""):

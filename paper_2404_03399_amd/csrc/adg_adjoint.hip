@@ -74,19 +74,20 @@ __device__ __forceinline__ double adj_elem(const DevProblem& P, int tile, const 
     const int slot_n = (int)(n % (int64_t)depth);
     const uint32_t bl = fast_div((uint32_t)e, P.pe_div);
     if ((uint32_t)e == bl * pes) {
-      const int64_t rb = P.ring_off + ((int64_t)bl * S + SI) * depth;
+      const int64_t rb = P.ring_off + ((int64_t)bl * S + SI);
       const int kd = pe_delay(P, n, SI, bl);
-      raw_l = (kd == 0 ? lf_l : 0.0) + A.adjring[rb + slot_n];
+      raw_l = (kd == 0 ? lf_l : 0.0) + A.adjring[rb + slot_n * P.ring_stride];
       if (kd > 0) {
         fl = at_past_sum(P, A.ring + rb, kd, slot_n);
-        for (int j = 0; j < P.q; ++j) A.adjring[rb + ring_slot(slot_n, kd + j, depth)] += P.atc[kd][j] * lf_l;
+        for (int j = 0; j < P.q; ++j)
+          A.adjring[rb + ring_slot(slot_n, kd + j, depth) * P.ring_stride] += P.atc[kd][j] * lf_l;
       }
     }
     const uint32_t br = fast_div((uint32_t)e1, P.pe_div);
     if ((uint32_t)e1 == br * pes) {
-      const int64_t rb = P.ring_off + ((int64_t)br * S + SI) * depth;
+      const int64_t rb = P.ring_off + ((int64_t)br * S + SI);
       const int kd = pe_delay(P, n, SI, br);
-      raw_r = (kd == 0 ? lf_r : 0.0) + A.adjring[rb + slot_n];
+      raw_r = (kd == 0 ? lf_r : 0.0) + A.adjring[rb + slot_n * P.ring_stride];
       if (kd > 0) fr = at_past_sum(P, A.ring + rb, kd, slot_n);
     }
   }

@@ -1117,6 +1117,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
     d.part_off = poff;
     poff += (p.n_elem + adj_part_elems((int)p.rk) - 1) / adj_part_elems((int)p.rk);
     d.ring_off = roff;
+    d.ring_stride = d.n_pe * c->S;
     if (d.async_faces) {
       const int64_t one_ring = d.n_pe * c->S * (int64_t)d.depth;
       d.ring2_off = roff + one_ring;

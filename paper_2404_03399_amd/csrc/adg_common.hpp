@@ -58,12 +58,14 @@ struct DevProblem {
   int64_t n_pe;          // P (1: no PE faces)
   int64_t ld;            // plane stride of the state
   int64_t u_off;         // offset of the problem in the state vector
-  int64_t ring_off;      // offset of the problem's delay ring (doubles)
+  int64_t ring_off;      // offset of the problem's delay ring (doubles): [slot][boundary][stage], so that a
+                         // step's reads and writes stay in whole lines of few slots
+  int64_t ring_stride;   // distance of its slots: boundaries x stages
   int64_t ring2_off;     // local DG: offset of the u-hat ring (same shape as the flux ring)
   int32_t np;            // degree + 1
   int32_t q;             // AT levels (1 for ADG)
   int32_t n_delays;      // L
-  int32_t depth;         // ring slots per (boundary, stage): L + q, or the recorded steps + L + q
+  int32_t depth;         // ring slots: L + q + most steps per launch - 2, and the recorded steps
   int32_t per_stage;     // delay key includes the stage
   int32_t scheme;        // Scheme
   int32_t async_faces;   // 1 if PE faces use delayed data (scheme != DG and P > 1)

@@ -78,12 +78,12 @@ __device__ __forceinline__ int pe_delay(const DevProblem& P, int64_t n, int s, u
   return clamp_delay(k, n, P.q);
 }
 
-// sum_{j<q} c_j(k) F^{n-k-j} over the ring of (boundary, stage); k >= 1, so
-// every level is a past one.
+// sum_{j<q} c_j(k) F^{n-k-j} over the ring entries of a (boundary, stage), r its
+// entry in slot 0; k >= 1, so every level is a past one.
 __device__ __forceinline__ double at_past_sum(const DevProblem& P, const double* __restrict__ r, int k,
                                               int slot_n) {
   double acc = 0.0;  // oldest level first, as in every other path
-  for (int j = P.q - 1; j >= 0; --j) acc = fma(P.atc[k][j], r[ring_slot(slot_n, k + j, P.depth)], acc);
+  for (int j = P.q - 1; j >= 0; --j) acc = fma(P.atc[k][j], r[ring_slot(slot_n, k + j, P.depth) * P.ring_stride], acc);
   return acc;
 }
 

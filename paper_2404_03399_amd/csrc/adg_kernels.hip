@@ -63,14 +63,14 @@ __device__ __forceinline__ void stage_elem(const DevProblem& P, int tile, const 
     const int slot_n = (int)(n % (int64_t)P.depth);
     const uint32_t bl = fast_div((uint32_t)e, P.pe_div);
     if ((uint32_t)e == bl * pes) {
-      const double* r = ring + P.ring_off + ((int64_t)bl * S + SI) * P.depth;
+      double* r = ring + P.ring_off + ((int64_t)bl * S + SI);
       const int kd = pe_delay(P, n, SI, bl);
-      ring[P.ring_off + ((int64_t)bl * S + SI) * P.depth + slot_n] = fl;
+      r[slot_n * P.ring_stride] = fl;
       if (kd > 0) fl = at_past_sum(P, r, kd, slot_n);
     }
     const uint32_t br = fast_div((uint32_t)e1, P.pe_div);
     if ((uint32_t)e1 == br * pes) {
-      const double* r = ring + P.ring_off + ((int64_t)br * S + SI) * P.depth;
+      const double* r = ring + P.ring_off + ((int64_t)br * S + SI);
       const int kd = pe_delay(P, n, SI, br);
       if (kd > 0) fr = at_past_sum(P, r, kd, slot_n);
     }
@@ -194,15 +194,15 @@ __device__ __forceinline__ void ldg_q_elem(const DevProblem& P, int tile, const 
     const int slot_n = (int)(n % (int64_t)P.depth);
     const uint32_t bl = fast_div((uint32_t)e, P.pe_div);
     if ((uint32_t)e == bl * pes) {
-      const int64_t rb = P.ring2_off + ((int64_t)bl * S + SI) * P.depth;
+      const int64_t rb = P.ring2_off + ((int64_t)bl * S + SI);
       const int kd = pe_delay(P, n, SI, bl);
-      ring[rb + slot_n] = hl;
+      ring[rb + slot_n * P.ring_stride] = hl;
       if (kd > 0) hl = at_past_sum(P, ring + rb, kd, slot_n);
     }
     const uint32_t br = fast_div((uint32_t)e1, P.pe_div);
     if ((uint32_t)e1 == br * pes) {
       const int kd = pe_delay(P, n, SI, br);
-      if (kd > 0) hr = at_past_sum(P, ring + P.ring2_off + ((int64_t)br * S + SI) * P.depth, kd, slot_n);
+      if (kd > 0) hr = at_past_sum(P, ring + P.ring2_off + ((int64_t)br * S + SI), kd, slot_n);
     }
   }
 #pragma unroll

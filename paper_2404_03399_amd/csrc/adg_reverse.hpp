@@ -78,17 +78,17 @@ struct AdjFaces {
       if (g < n_jobs) {
         const int ik = g / S, s = g - ik * S, i = ik >> kshift, t = ik - (i << kshift);
         const uint32_t b = face(P, i);
-        const int64_t rb = P.ring_off + ((int64_t)b * S + s) * depth;
+        const int64_t rb = P.ring_off + (int64_t)b * S + s;
         const int k = pe_delay(P, n + t, s, b);
         int sl = slot_n + t;
         while (sl >= depth) sl -= depth;
-        const double collected = adjring[rb + sl];
+        const double collected = adjring[rb + sl * P.ring_stride];
         if constexpr (FWD) {
           double lv[kMaxQ];
 #pragma unroll
           for (int j = 0; j < kMaxQ; ++j) {
             lv[j] = 0.0;
-            if (j < P.q && k > 0) lv[j] = ring[rb + ring_slot(sl, k + j, depth)];
+            if (j < P.q && k > 0) lv[j] = ring[rb + ring_slot(sl, k + j, depth) * P.ring_stride];
           }
           double sum = 0.0;
 #pragma unroll
@@ -134,7 +134,8 @@ struct AdjFaces {
       const int g = g0 + lane;
       const int i = g / (S * W), x = g - i * (S * W), s = x / W, d = 1 + (x - s * W);
       if (i < n_faces && own[i] && d < depth) {
-        double* __restrict__ at_d = adjring + P.ring_off + ((int64_t)face(P, i) * S + s) * depth + ring_slot(slot_n, d, depth);
+        double* __restrict__ at_d =
+            adjring + P.ring_off + (int64_t)face(P, i) * S + s + ring_slot(slot_n, d, depth) * P.ring_stride;
         bool reached = false;
         double v = 0.0;
         for (int t = K - 1; t >= 0; --t) {

@@ -157,7 +157,7 @@ struct WaveFaces {
         const int ik = g / S, s = g - ik * S, i = ik >> kshift, kk = ik - (i << kshift);
         const uint32_t b = face(P, i);
         const int k = pe_delay(P, n + kk, s, b);
-        const int64_t rb = ((int64_t)b * S + s) * depth;
+        const int64_t rb = (int64_t)b * S + s;
         double lv[V][kMaxQ];
 #pragma unroll
         for (int j = 0; j < kMaxQ; ++j) {
@@ -168,7 +168,7 @@ struct WaveFaces {
             if (k > 0 && back > 0)
 #pragma unroll
               for (int v = 0; v < V; ++v)
-                lv[v][j] = ring[(v == 0 ? P.ring_off : P.ring2_off) + rb + ring_slot(slot_n, back, depth)];
+                lv[v][j] = ring[(v == 0 ? P.ring_off : P.ring2_off) + rb + ring_slot(slot_n, back, depth) * P.ring_stride];
           }
         }
         reinterpret_cast<uint8_t*>(kd + ik)[s] = (uint8_t)k;
@@ -225,7 +225,8 @@ struct WaveFaces {
           while (sl >= depth) sl -= depth;
 #pragma unroll
           for (int v = 0; v < V; ++v)
-            ring[(v == 0 ? P.ring_off : P.ring2_off) + ((int64_t)face(P, i) * S + s) * depth + sl] = at[v * vstride + g];
+            ring[(v == 0 ? P.ring_off : P.ring2_off) + (int64_t)face(P, i) * S + s + sl * P.ring_stride] =
+                at[v * vstride + g];
         }
       }
     }

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kw", [
     dict(ne=(1 << 18) + 256), dict(ne=1 << 18, speed=-1.0, rk="heun", degree=1),
-    dict(ne=(1 << 18) + 50, pe=25, flux="central", degree=1, rk="ssprk3"),
+    dict(ne=(1 << 18) + 6, pe=25, flux="central", degree=1, rk="ssprk3"),
     dict(ne=1 << 18, equation="burgers", flux="llf", degree=2, rk="lsrk3"),
     dict(ne=1 << 18, equation="viscous_burgers", flux="llf", degree=1, rk="heun", viscosity=0.1, at_levels=2),
     dict(ne=1024, degree=2), dict(ne=320, pe=64, degree=2)], ids=lambda k: "-".join(f"{a}{b}" for a, b in k.items()))
@@ -40,14 +40,14 @@ def test_any_calls_give_the_same_states(kw, opt):
     for i, c in enumerate(calls):
         s.run(u, c, graph=i % 3 == 2)
         ref.run(v, c, graph=False)
-        assert torch.equal(u, v), (c, calls[:i])
-    assert bool(torch.isfinite(u).all())
+        assert torch.equal(s.view(u), ref.view(v)), (c, calls[:i])  # a padded plane's end is nobody's
+    assert bool(torch.isfinite(s.view(u)).all())
     if rec:
         for ck in (4, 7, 12):  # segments of so many steps each, the states kept of any
             t = Solver(w, n_steps_record=n, ckpt_every=ck)
             x = t.initial_state()
             t.run(x, n, record=True)
-            assert torch.equal(x, u), ck
+            assert torch.equal(t.view(x), s.view(u)), ck
             t.close()
     s.close()
     ref.close()
