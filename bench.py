@@ -278,12 +278,13 @@ def adjoint_roofline(torch, W, Solver, n_elem: int, n1: int = 64, n2: int = 128)
     four reverse steps per launch read lambda^{n+4} and write lambda^n (16 B per
     DOF); with dJ/da the forward stages are recomputed in registers and, every
     state kept (checkpoint interval 1, so no segment is recomputed), launches of
-    one step read u^n and lambda^{n+1} and write lambda^n (24 B per DOF)."""
+    two steps read u^n, u^{n+1} and lambda^{n+2} and write lambda^n (32 B per
+    DOF)."""
     dofs = n_elem * 4
     out = {"n_elem": n_elem}
     for key, want, ckpt, per, bytes_dof, kern in (
             ("reverse_du0", False, 64, 4, 16, "k_adj_fused<p=3, rk4, upwind, R=2>, four steps per launch"),
-            ("one_step_reverse_with_speed", True, 1, 1, 24, "k_adj_fused<p=3, rk4, upwind, forward stages, R=2>, one step per launch")):
+            ("reverse_with_speed", True, 1, 2, 32, "k_adj_fused<p=3, rk4, upwind, forward stages, R=2>, two steps per launch")):
         ts = {}
         for n in (n1, n2):
             w = W.c5_adjoint_advection(n_elem=n_elem, n_steps=n)
