@@ -579,7 +579,9 @@ enum AdjList : int { ADJ_FWD = 0, ADJ_LINEAR = 1 };
 // Its elements per lane R (at most the PE size) and the steps per launch K of
 // the list, like the forward kernels'.  With dJ/da the two are equal, so that a
 // wave owns whole tiles of the partial sums; four of either would take two
-// thirds of the registers for the forward stages alone.
+// thirds of the registers for the forward stages alone.  options.fused_steps is
+// the forward launches' alone: one reverse step per launch where it is 1 took
+// 71.6 us per step of a recorded run and its adjoint at 2^20 against 61.1.
 // Measured, us per step of a reverse sweep of 16, PE 256 (R and K in brackets):
 //   with dJ/da    p = 3, RK4, 2^20 elements (1,1) 33.1, (2,2) 23.5
 //   dJ/du0 alone  p = 3, RK4 2^12 (1,4) 2.35, (2,2) 3.61, (2,8) 2.35; 2^16 2.80,
@@ -593,18 +595,18 @@ enum AdjList : int { ADJ_FWD = 0, ADJ_LINEAR = 1 };
 //                 (2,8) 26.5; RK4, p = 3 2^16 (1,4) 7.39, (2,4) 6.55, (2,8) 7.32
 Shape adj_shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int list) {
   const bool nl = probs[0].equation == ADG_EQ_BURGERS, speed = list == ADJ_FWD && !nl;
-  const int rk = (int)probs[0].rk, steps = opt ? (int)opt->fused_steps : 0, lanes = opt ? (int)opt->lane_elems : 0;
+  const int rk = (int)probs[0].rk, lanes = opt ? (int)opt->lane_elems : 0;
   const int64_t elems = total_elems(probs, n);
   Shape s{2, 2};
   int work = 0;  // the most nodes times stages, which the registers go with
   for (int32_t i = 0; i < n; ++i) work = std::max(work, ((int)probs[i].degree + 1) * rk_stages(rk));
-  s.elems = speed ? (steps == 1 ? 1 : 2) : lanes != 0 ? lanes : (elems >= (int64_t)1 << 19 && work <= 15 ? 4 : 2);
+  s.elems = speed ? 2 : lanes != 0 ? lanes : (elems >= (int64_t)1 << 19 && work <= 15 ? 4 : 2);
   if (list == ADJ_FWD) s.elems = std::min(s.elems, 2);
   for (int32_t i = 0; i < n; ++i)
     if (async_of(probs[i]))
       while (probs[i].pe_size < s.elems) s.elems >>= 1;
-  if (speed || steps != 0) {
-    s.kmax = speed ? s.elems : steps;
+  if (speed) {
+    s.kmax = s.elems;
     return s;
   }
   const bool small = elems <= (int64_t)1 << 17;
@@ -755,7 +757,6 @@ struct adg_ctx {
   int32_t single[kLists][kFusedRanges] = {};
   FaceRange faces[kLists][kFusedRanges] = {};
   int32_t one_launch = 0;  // ADG_OPT_ONE_LAUNCH
-  int adj_steps = kMaxSteps;  // of a reverse launch at most, as the option asks
   // fused adjoint work list (recording contexts of the fused kernel)
   AdjArgs adj[2] = {};  // per list, but for the steps of a launch
 
@@ -1169,7 +1170,6 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return probs[a].degree > probs[b].degree; });
   std::vector<WorkItem> wf_all(c->L.at_f[kLists]), ws_;
   std::vector<int32_t> first(n_probs + 1, 0);
-  if (opt && opt->fused_steps != 0) c->adj_steps = (int)opt->fused_steps;
   c->one_launch = (opt && (opt->flags & ADG_OPT_ONE_LAUNCH)) ? 1 : 0;
   for (int list = 0; list < kLists && 1 << list <= c->L.shape.kmax; ++list) {
     const int K = 1 << list;
@@ -1522,7 +1522,7 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
   const bool need_fwd = c->phys == PHYS_BURGERS_LLF || h_grad_speed != nullptr;
   if (!need_fwd) {
     for (int64_t n = N; n > 0;) {
-      const int K = steps_within(std::min(L.adj[ADJ_LINEAR].kmax, c->adj_steps), n);
+      const int K = steps_within(L.adj[ADJ_LINEAR].kmax, n);
       n -= K;
       ADG_HIP(launch_adj_fused(c->rk, c->phys, c->adj_args(ADJ_LINEAR, K), nullptr, nullptr, 0, lam, lamu, ring,
                                adjring, cpart, (int32_t)n, st));
@@ -1546,7 +1546,7 @@ int adjoint_fused(adg_ctx* c, const double* d_cot_uT, double* d_grad_u0, double*
       i += K;
     }
     for (int64_t i = len; i > 0;) {
-      const int K = steps_within(std::min(L.adj[ADJ_FWD].kmax, c->adj_steps), i);
+      const int K = steps_within(L.adj[ADJ_FWD].kmax, i);
       i -= K;
       ADG_HIP(launch_adj_fused(c->rk, c->phys, c->adj_args(ADJ_FWD, K), state(i), state(i + 1), tot, lam, lamu, ring,
                                adjring, cpart, (int32_t)(n0 + i), st));
