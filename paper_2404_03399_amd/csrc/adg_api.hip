@@ -344,7 +344,7 @@ int list_of(int K) { return __builtin_ctz((unsigned)K); }
 struct Shape {
   int elems, kmax;
   int elems1 = 0, elems2 = 0;  // elements per lane of launches of one and two steps, if not elems
-  bool any_face = false;  // two elements per lane although a PE size is odd (general stage form)
+  bool any_face = false;  // two elements per lane although a PE size is odd (general stage form, local DG)
   bool halve4 = false, halve8 = false;  // halves_first may split a launch of four, of eight steps
   int elems_at(int K) const { return K == 1 && elems1 ? elems1 : (K == 2 && elems2 ? elems2 : elems); }
 };
@@ -490,7 +490,7 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   uint32_t degree = 0;
   for (int32_t i = 0; i < n; ++i) degree = std::max(degree, probs[i].degree);
   const bool one_launch = opt && (opt->flags & ADG_OPT_ONE_LAUNCH);
-  bool all_lin = true, gen = false, all_gen = !is_ldg(probs), odd = false;
+  bool all_lin = true, gen = false, all_gen = true, odd = false;
   int64_t least = (int64_t)1 << 62;
   for (int32_t i = 0; i < n; ++i) {
     const int f = form_of(probs[i], kern, n_rec);
@@ -509,10 +509,11 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   for (int32_t i = 0; i < n; ++i)
     if (async_of(probs[i]))
       odd = odd || probs[i].pe_size % 2, least = std::min(least, probs[i].pe_size);
-  // The general stage form can find a lane's PE face in any element; one
-  // element per lane would leave 44 of 64 lanes to five stages and two steps.
-  // Odd PEs (25), 4.7e6 elements, us per step with one and two: p = 4, a < 0, LSRK4
-  // 98.7, 75.2, SSP-RK3 71.7, 54.2; Burgers, RK4 82.5, 70.7.
+  // The general stage form and local DG can find a lane's PE face in any element;
+  // one element per lane would leave 44 of 64 lanes to five stages and two steps, 31
+  // to Heun and eight.  Odd PEs (25), us per step with one and two: 4.7e6 elements,
+  // p = 4, a < 0, LSRK4 98.7, 75.2, SSP-RK3 71.7, 54.2; Burgers, RK4 82.5, 70.7; local
+  // DG, p = 2, 2^22, Heun 41.2, 26.8, SSP-RK3 55.0, 36.6; 2^18 3.76, 3.03 and 5.08, 4.43.
   s.any_face = all_gen && odd && !one_launch && s.elems >= 2 && least >= 2;
   if (s.any_face)
     s.elems = 2;

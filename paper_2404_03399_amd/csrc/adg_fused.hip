@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_all(const DevProblem* __restri
   }
 }
 
-template <int NP, int RK, int R>
+template <int NP, int RK, int R, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_fused_ldg(const DevProblem* __restrict__ probs,
                                                       const WorkItem* __restrict__ work, const StepClock clock,
                                                       double* __restrict__ ring, int32_t w_begin, int32_t w_end,
@@ -98,19 +98,20 @@ __global__ __launch_bounds__(kBlock) void k_fused_ldg(const DevProblem* __restri
   if (w >= w_end) return;  // whole wave
   const int64_t n = clock.tick(w == w_begin) + step_offset;
   const WorkItem wi = single_prob >= 0 ? WorkItem{single_prob, w - w_begin} : work[w];
-  ldg_tile<NP, RK, R>(probs[wi.prob], wi, ring, n, K, HL, HR, uin, uout, n_faces_max, wave_lds + wv * lds_words, lane);
+  ldg_tile<NP, RK, R, ANY>(probs[wi.prob], wi, ring, n, K, HL, HR, uin, uout, n_faces_max, wave_lds + wv * lds_words, lane);
 }
 
-template <int NP, int RK, int R>
+template <int NP, int RK, int R, bool ANY = false>
 static void fused_ldg_go_r(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
   const FaceRange& fr = a.faces[gi];
-  hipLaunchKernelGGL((k_fused_ldg<NP, RK, R>), dim3(a.grid[gi]), dim3(kBlock), 8 * kWavesPerBlock * fr.lds_words, st,
+  hipLaunchKernelGGL((k_fused_ldg<NP, RK, R, ANY>), dim3(a.grid[gi]), dim3(kBlock), 8 * kWavesPerBlock * fr.lds_words, st,
                      a.probs, a.work, a.clock, a.ring, a.group[gi], a.group[gi + 1], uin, uout, off, a.steps, a.halo,
                      a.halo_right, fr.n_faces, fr.lds_words, a.single[gi]);
 }
 
 template <int NP, int RK>
 static void fused_ldg_go(const StepArgs& a, int gi, const double* uin, double* uout, int32_t off, hipStream_t st) {
+  if (a.any_face) return fused_ldg_go_r<NP, RK, 2, true>(a, gi, uin, uout, off, st);
   switch (a.elems) {
     case 1: fused_ldg_go_r<NP, RK, 1>(a, gi, uin, uout, off, st); break;
     case 4: fused_ldg_go_r<NP, RK, 4>(a, gi, uin, uout, off, st); break;

@@ -58,9 +58,9 @@ struct StepArgs {
   int32_t single[kFusedRanges];      // fused kernel: the only problem of a range, or -1
   FaceRange faces[kFusedRanges];     // fused kernel: PE faces per wave of a range
   int32_t elems;             // fused kernel: elements per lane (1, 2 or 4)
-  int32_t steps;             // fused kernel: time steps of the launch (a power of two, at most the list's)
-  int32_t any_face;          // stage form, general flux, two elements per lane: a PE size is odd
-  int32_t halo;              // fused kernel: halo lanes per side (upwind, a > 0: on the left) of the work list
+  int32_t steps;             // fused kernel: time steps of the launch, a power of two
+  int32_t any_face;          // two elements per lane although a PE size is odd (general stage form, local DG)
+  int32_t halo;              // fused kernel: halo lanes per side (upwind, a > 0: on the left)
   int32_t halo_right;        // local DG: halo lanes on the right
   double* qbuf;              // local DG: q = u_x of the current stage input (state layout)
   double* umid;              // fused kernel, several steps per launch: also write the states after
@@ -88,7 +88,7 @@ __host__ __device__ constexpr int ldg_halo_right(int rk, int R, int K) { return 
 __host__ __device__ constexpr int ldg_tile_elems(int rk, int R, int K) {
   return R * (kWave - fused_halo(rk, R, K) - ldg_halo_right(rk, R, K));
 }
-// PE faces of a wave's 64 R elements at most (R divides the PE size, so one per lane)
+// PE faces of a wave's 64 R elements at most, one to a lane
 __host__ __device__ constexpr int fused_faces(int R, int64_t pe_size) {
   return (int)((kWave * R - 1) / pe_size) + 1;
 }

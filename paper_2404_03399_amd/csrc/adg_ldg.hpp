@@ -17,11 +17,14 @@ namespace adg {
 // one element more on the right covers the last lane's PE face, whose u-hat no
 // lane holds.
 //
+// ANY: a lane's PE face may be the left face of any of its elements (as in
+// stage_tile).
+//
 // Bound by FP64 issue (two operator products per stage).  Heun, p = 2, AT2, PE
 // 256, 2^20 elements: 11.4 us per step with two elements per lane, two steps
 // per launch and the operator in SGPRs; 7.4 with four, eight and the operator
 // broadcast from a register pair.
-template <int NP, int RK, int R>
+template <int NP, int RK, int R, bool ANY = false>
 __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi, double* __restrict__ ring, int64_t n,
                                          int K, int HL, int HR, const double* __restrict__ uin,
                                          double* __restrict__ uout, int n_faces_max, double* __restrict__ lds,
@@ -46,7 +49,9 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
     kl[i] = P.Kl[i];
     kr[i] = P.Kr[i];
   }
-  WaveFaces<S, 2> wf(P, we.e[0], we.own_n > 0, atc, n, K, n_faces_max, lds, lane);
+  int at_r = 0, e_face = we.e[0];
+  lane_face<R, ANY>(P, we, at_r, e_face);
+  WaveFaces<S, 2> wf(P, e_face, at_r < we.own_n, atc, n, K, n_faces_max, lds, lane);
   wf.draw(P, ring, n, K, lane);
 
   const double nu2 = 2.0 * P.nu, dt2 = 0.5 * P.dt;
@@ -75,21 +80,27 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
 #pragma unroll
         for (int r = 1; r < R; ++r) um[r] = y[r - 1][NP - 1];
         bool late = false;
-        double hl0 = um[0], at_g = 0.0, hr_last = y[R - 1][NP - 1];
+        double hl[R], at_g = 0.0, hr_last = y[R - 1][NP - 1];  // hl: the applied u-hat of the left faces
+#pragma unroll
+        for (int r = 0; r < R; ++r) hl[r] = um[r];
         if constexpr (PE) {
           late = (kd & ((KdWord)0xff << (8 * s))) != 0;
           const double at_u = mine_u[s];
           at_g = mine_g[s];
-          mine_u[s] = um[0];
-          hl0 = late ? at_u : um[0];
-          const double h = lane_from_right(hl0);
+          double raw = um[0];
+#pragma unroll
+          for (int r = 1; r < R; ++r) raw = ANY && at_r == r ? um[r] : raw;
+          mine_u[s] = raw;
+#pragma unroll
+          for (int r = 0; r < (ANY ? R : 1); ++r) hl[r] = late && at_r == r ? at_u : um[r];
+          const double h = lane_from_right(hl[0]);
           hr_last = rpe ? h : hr_last;
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          const double hl = r == 0 ? hl0 : um[r], hr = r + 1 < R ? y[r][NP - 1] : hr_last;
+          const double hr = r + 1 < R ? hl[r + 1 < R ? r + 1 : r] : hr_last;
 #pragma unroll
-          for (int i = 0; i < NP; ++i) v[r][i] = fma(kl[i], hl, -kr[i] * hr);
+          for (int i = 0; i < NP; ++i) v[r][i] = fma(kl[i], hl[r], -kr[i] * hr);
           fmac_operator<NP>(op, y[r], v[r]);  // -q
 #pragma unroll
           for (int i = 0; i < NP; ++i) v[r][i] *= nu2;
@@ -98,8 +109,12 @@ __device__ __forceinline__ void ldg_tile(const DevProblem& P, const WorkItem wi,
           __builtin_amdgcn_sched_barrier(0);  // one element after the other
         }
         if constexpr (PE) {
-          mine_g[s] = 0.5 * G[0];
-          G[0] = late ? 2.0 * at_g : G[0];
+          double raw = G[0];
+#pragma unroll
+          for (int r = 1; r < R; ++r) raw = ANY && at_r == r ? G[r] : raw;
+          mine_g[s] = 0.5 * raw;
+#pragma unroll
+          for (int r = 0; r < (ANY ? R : 1); ++r) G[r] = late && at_r == r ? 2.0 * at_g : G[r];
         }
         const double g_last = lane_from_right(G[0]);
 #pragma unroll

@@ -55,15 +55,8 @@ __device__ __forceinline__ void stage_tile(const DevProblem& P, const WorkItem w
     kl[i] = P.Kl[i];
     kr[i] = P.Kr[i];
   }
-  int at_r = 0;  // the element right of the lane's PE face
-  if constexpr (ANY)
-    if (P.async_faces)
-#pragma unroll
-      for (int r = 1; r < R; ++r)
-        if ((uint32_t)we.e[r] == fast_div((uint32_t)we.e[r], P.pe_div) * P.pe_div.d) at_r = r;
-  int e_face = we.e[0];
-#pragma unroll
-  for (int r = 1; r < R; ++r) e_face = at_r == r ? we.e[r] : e_face;
+  int at_r = 0, e_face = we.e[0];  // the element right of the lane's PE face
+  lane_face<R, ANY>(P, we, at_r, e_face);
   WaveFaces<S> wf(P, e_face, at_r < we.own_n, atc, n, K, n_faces_max, lds, lane);
   wf.draw(P, ring, n, K, lane);
 

@@ -82,8 +82,22 @@ struct WaveElems {
   }
 };
 
-// PE faces of a wave (Secs. 3-5) over a launch of K steps.  R divides every PE
-// size, so a PE face is always the left face of a lane's first element.  Every
+// Where R does not divide every PE size (ANY) a lane's PE face, at most one, is
+// the left face of its element at_r, e_face; else of its first.
+template <int R, bool ANY>
+__device__ __forceinline__ void lane_face(const DevProblem& P, const WaveElems<R>& we, int& at_r, int& e_face) {
+  if constexpr (ANY) {
+    if (P.async_faces)
+#pragma unroll
+      for (int r = 1; r < R; ++r)
+        if ((uint32_t)we.e[r] == fast_div((uint32_t)we.e[r], P.pe_div) * P.pe_div.d) at_r = r;
+#pragma unroll
+    for (int r = 1; r < R; ++r) e_face = at_r == r ? we.e[r] : e_face;
+  }
+}
+
+// PE faces of a wave (Secs. 3-5) over a launch of K steps, at most one to a lane,
+// the left face of its first element unless the tile says otherwise.  Every
 // wave that holds a face (its owner's and those with the face in their halo,
 // which see bitwise the same raw fluxes) draws its delays and sums the ring
 // levels before the launch itself, one job lane per (face, step, stage) while

@@ -81,3 +81,11 @@ def test_bench_asks_the_library():
                    (_w(25 * 160000, 25, speed=-1.0, rk="lsrk4"), {}), (_w(1 << 20, 4), {})):
         s.probs, s.opt = [solver.to_problem(w)], adg.adg_options(**opt)
         assert s.launch_shape(100) == _shape(w, 100, **opt)
+
+
+def test_odd_pes_of_local_dg_take_two_elements():
+    """One element per lane leaves Heun and eight steps 31 of 64 lanes."""
+    kw = dict(equation="viscous_burgers", viscosity=0.1, rk="heun", degree=2)
+    odd, even = _w(25 * 40000, 25, **kw), _w(1 << 20, 256, **kw)
+    assert _shape(odd, 16) == (2, 8)
+    assert _shape([odd, even], 16) == (2, 8)
