@@ -5,8 +5,8 @@ The best number depends on the problem set: register pressure grows with the
 elements per lane (fewer resident waves), larger tiles cut the halo recompute
 and the number of waves.  The tuner times each admissible one on the caller's
 own problems (same kernels, a few graph-replayed steps on a scratch copy of
-the initial state) and caches the winner in a JSON file keyed by device,
-integrator, equation/flux, degrees and size.  Every launch shape gives bitwise
+the initial state) and caches the winner in a JSON file keyed by what the
+kernels go by (`_key`).  Every launch shape gives bitwise
 the same states (the kernels use explicit FMAs with contraction off), so
 tuning never changes results.
 
@@ -44,13 +44,21 @@ def kernel_source_hash() -> str:
 
 
 def _key(workloads, device_name: str) -> str:
-    degrees = sorted({w.degree for w in workloads})
+    """What the kernels and their times go by: device, sources, scheme, the size,
+    every problem's degree, sign of the speed and power of two of its mesh (upwind
+    meshes of 1024 elements or more with a > 0 run another kernel), the PE sizes,
+    and the shape each candidate runs (which the PE sizes' parity decides too)."""
+    from . import adg
+    from .solver import to_problem
     total = sum(w.n_elem for w in workloads)
     bucket = int(round(math.log2(max(total, 1))))
-    pes = min((w.pe_size for w in workloads if w.scheme != "dg" and w.n_elem // w.pe_size > 1), default=0)
+    kinds = sorted({(w.degree, w.speed > 0.0, w.n_elem.bit_length()) for w in workloads})
+    pes = sorted({min(w.pe_size, 256) for w in workloads if w.scheme != "dg" and w.n_elem // w.pe_size > 1})
+    probs = [to_problem(w) for w in workloads]
+    shapes = [adg.adg_launch_shape(probs, adg.adg_options(lane_elems=r), 0, 16) for r in admissible(workloads)]
     w0 = workloads[0]
     return "|".join(str(x) for x in (device_name, kernel_source_hash(), w0.rk, w0.equation, w0.flux, w0.scheme,
-                                     degrees, bucket, len(workloads) > 1, min(pes, 4)))
+                                     kinds, bucket, len(workloads) > 1, pes, shapes))
 
 
 def admissible(workloads) -> List[int]:

@@ -471,8 +471,8 @@ int lds_of(const adg_problem& p, int elems, int K) {
 //                 (4,8) 31.0; five stages (lsrk4, p = 2) 2^22 (4,4) 27.0, (4,8)
 //                 30.6; 10^5, p = 4, lsrk4, PE 30 (2,2) 4.2, (2,4) 4.5, (2,8) 5.4
 //   one and two steps per launch are bound by HBM, which two elements per lane,
-//                 with more waves in flight, reach better (an explicit number of
-//                 elements keeps its own for two): 2^20 central (2,1) 16.9, (4,1)
+//                 with more waves in flight, reach better (four for two steps only
+//                 where the options ask for both): 2^20 central (2,1) 16.9, (4,1)
 //                 19.1, (2,2) 11.0, (4,2) 11.7; Burgers, SSP-RK3, p = 2 14.1, 16.1,
 //                 9.3, 10.0; a > 0 14.8, 17.6, 8.6, 9.6; local DG 14.4, 15.9, 9.1, 9.8
 //   general, Burgers, SSP-RK3, p = 2   2^22 (2,4) 26.2, (4,4) 24.0, (4,8) 23.7
@@ -525,7 +525,7 @@ Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int6
   s.halve4 = s.halve8 && (elems < (int64_t)1 << 21 || is_ldg(probs) || (!all_lin && degree >= 2));
   if (!one_launch) {
     s.elems1 = std::min(s.elems, 2);
-    if (!opt || opt->lane_elems == 0) s.elems2 = s.elems1;
+    if (!opt || opt->lane_elems == 0 || opt->fused_steps == 0) s.elems2 = s.elems1;
   }
   if ((opt && opt->fused_steps != 0) || one_launch) return s;
   const int most_halo = is_ldg(probs) ? (elems <= (int64_t)1 << 16 ? 24 : 16) / s.elems

@@ -60,7 +60,8 @@ def test_calls_of_few_steps():
     assert _shape(w, 2) == (2, 2) and _shape(w, 16) == (4, 8)
     assert _shape(_w(1 << 17, 256), 8)[1] == 8 and _shape(_w(1 << 18, 256), 8)[1] == 4
     assert _shape(_w(1 << 22, 256), 4)[1] == 4 and _shape(_w(1 << 22, 256), 8)[1] == 4
-    assert _shape(w, 4, lane_elems=4)[0] == 4 and _shape(w, 1, lane_elems=4)[0] == 2
+    assert _shape(w, 16, lane_elems=4) == (4, 8) and _shape(w, 2, lane_elems=4, fused_steps=2) == (4, 2)
+    assert _shape(w, 2, lane_elems=4) == (2, 2) and _shape(w, 1, lane_elems=4) == (2, 1)
 
 
 def test_bad_arguments():
