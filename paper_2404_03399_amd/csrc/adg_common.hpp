@@ -136,6 +136,16 @@ constexpr int lin_col(int np, int S, int kind, int j) {
 // doubles of a table: whole runs of 16
 constexpr int lin_tab_size(int np, int S) { return (lin_col(np, S, kLinCols, 0) + 15) / 16 * 16; }
 
+// x / 3 correctly rounded, subnormal quotients included: the residual of the
+// product with the rounded reciprocal corrects it (Markstein, IBM J. Res. Dev. 34,
+// 1990).  Where the residual is zero (a zero x keeps its sign) or NaN (an infinite
+// x) the product stands.  A division instruction sequence in its place is half of
+// an SSP-RK3 update.
+__host__ __device__ inline double third_of(double x) {
+  const double z = 1.0 / 3.0, q = x * z, r = fma(-3.0, q, x);
+  return fabs(r) > 0.0 ? fma(r, z, q) : q;
+}
+
 struct WorkItem {
   int32_t prob;
   int32_t tile;

@@ -137,15 +137,6 @@ __host__ __device__ constexpr double ls_b(int rk, int s) {
 }
 __host__ __device__ constexpr bool low_storage(int rk) { return rk == RK_LS3 || rk == RK_LS4; }
 
-// x / 3 correctly rounded: the residual of the product with the rounded
-// reciprocal corrects it (Markstein, IBM J. Res. Dev. 34, 1990); an infinite x
-// gives a NaN residual and keeps the product.  A division instruction sequence
-// in its place is half of an SSP-RK3 update.
-__device__ __forceinline__ double third_of(double x) {
-  const double z = 1.0 / 3.0, q = x * z, r = fma(-3.0, q, x);
-  return r == r ? fma(r, z, q) : q;
-}
-
 // RK update after the stage-s operator value k (oracle's algebraic forms).
 // Every multiply-add is an explicit FMA and nothing else is contracted, so
 // the rounding does not depend on how the compiler schedules the caller
