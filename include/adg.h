@@ -236,7 +236,7 @@ int adg_init(adg_ctx** out, const adg_problem* probs, int32_t n_probs, const adg
  * array.  The step counter and rings are cleared as by adg_init.
  * Where the library's choice of steps per launch (fused_steps 0) does not fit,
  * two steps per launch are taken; the operator tables of upwind advection
- * (1.4 KB at most per problem) come on top of the array's size.
+ * (1.4 KB at most per problem) and the work lists come on top of the array's size.
  * adg_run with ADG_RUN_GRAPH creates a capture stream and a graph; run
  * without that flag when nothing may be created. */
 #define ADG_SCRATCH_BYTES (64ll << 20)

@@ -939,7 +939,9 @@ int build_graph(adg_ctx* c, double* d_u) {
 // Host code never uses this name as a device address (on the host it is a
 // stand-in); its per-device address comes from hipGetSymbolAddress.
 // The linear form's tables (1.4 KB at most for a problem of 1024 elements or
-// more) come on top of the documented size.
+// more) and the work lists (longer than two elements per lane make them where odd
+// PEs take one) come on top of the documented size, so that what fitted without
+// them fits.
 constexpr int64_t kScratchBytes = ADG_SCRATCH_BYTES;
 constexpr int64_t kScratchTables = 8ll << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchTables];
@@ -1285,7 +1287,8 @@ int adg_init_scratch(adg_ctx** out, const adg_problem* probs, int32_t n_probs, c
   // does not fit, two steps
   auto beside_tables = [&](const adg_options* o) {
     const Layout L = make_layout(probs, n_probs, o, 0);
-    return L.total - align_up(8 * L.lin_doubles, kAlign);
+    return L.total - align_up(8 * L.lin_doubles, kAlign) -
+           align_up((int64_t)sizeof(WorkItem) * L.at_f[kLists], kAlign);
   };
   adg_options two = opt ? *opt : adg_options{};
   if (two.fused_steps == 0) two.fused_steps = 2;

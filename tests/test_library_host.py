@@ -385,3 +385,19 @@ def test_autotune_candidates_include_the_pe_split():
     c = autotune.configs([small])
     assert (1, 1, True) in c and (1, 2, None) in c and (1, 2, True) not in c
     assert all(sp is None for _, _, sp in autotune.configs([replace(w, scheme="dg")]))
+
+
+def test_scratch_holds_odd_pes(L):
+    """Largest numbers of PEs that the scratch array held when every tile took two
+    elements per lane: odd PE sizes, whose tiles take one, still fit (the call
+    then fails for want of a device or succeeds, never for the workspace)."""
+    import ctypes as C
+    for p, rk, pe, n_pe in ((1, "heun", 4099, 1004), (1, "rk4", 4099, 1002), (1, "heun", 100003, 41), (3, "rk4", 4099, 506),
+                            (1, "rk4", 100003, 41)):
+        w = W.Workload(name="scratch", rk=rk, degree=p, n_elem=pe * n_pe, pe_size=pe, probs=("1/2", "1/2"), dt=1e-9)
+        ctx = C.c_void_p()
+        arr = (adg.adg_problem * 1)(solver.to_problem(w))
+        rc = L.adg_init_scratch(C.byref(ctx), arr, 1, C.byref(adg.adg_options()), None)
+        assert rc in (adg.ADG_OK, adg.ADG_E_HIP), (p, rk, pe, L.adg_last_error())
+        if rc == adg.ADG_OK:
+            L.adg_destroy(ctx)
