@@ -236,12 +236,17 @@ int validate(const adg_problem* probs, int32_t n) {
 // The fused kernel's linear form: upwind advection with a > 0 on meshes of
 // kLinMinElems elements or more, whatever the PEs and delays (so that a problem
 // without delays and its synchronous twin agree bit for bit), no recording.
-// Below that a launch is latency and the forms are equal: 64 elements, p = 2,
-// RK4, 255 steps 375 us against 397 stage by stage, 160 problems of 512
-// elements, p = 1, Heun, 200 steps 360 against 324.  Recorded runs keep the
-// stage form: dJ/da can be a sum that cancels down to rounding (a misfit
-// without a mode in common with the state), where its value is that of the
-// order of operations.
+// us per step, linear form and stage by stage, Heun / RK4 / LSRK4: one mesh of 256
+// elements, p = 1 1.06, 1.11 / 1.23, 1.28 / 1.62, 1.61, p = 4 1.19, 1.25 / 1.37, 1.52 / 1.83,
+// 2.00; 160 of 512, p = 1 1.74, 1.25 / 2.33, 1.92 / 2.54, 2.87, p = 4 1.74, 1.55 / 2.51,
+// 2.80 / 2.95, 4.31; 160 of 1024, p = 1 1.30, 1.36 / 1.84, 1.93 / 2.30, 2.77, p = 4 1.70,
+// 1.94 / 2.39, 2.96 / 2.91, 4.27; 160 of 4096, p = 4 3.25, 4.08 / 4.04, 5.84 / 5.40, 8.83;
+// 2^20, p = 3 RK4 4.75, 6.55, 2^24 53.9, 84.2.  From 1024 elements on it is the faster
+// one for every degree and integrator, below it depends on them, and a launch is
+// latency for a single mesh.  Recorded runs keep the stage form (so their states are
+// an unrecorded run's to rounding only): dJ/da can be a sum that cancels down to
+// rounding (a misfit without a mode in common with the state), where its value is
+// that of the order of operations.
 constexpr int64_t kLinMinElems = 1024;
 bool lin_of(const adg_problem& p, int kernel, int64_t n_rec) {
   return kernel == ADG_KERNEL_FUSED && phys_of(p) == PHYS_ADV_UPWIND && p.speed > 0.0 && n_rec == 0 &&
@@ -456,13 +461,16 @@ int lds_of(const adg_problem& p, int elems, int K) {
 // many make the halo small.  Steps per launch K: the option's, or the library's
 // choice: the most, eight, as long as the halo leaves enough of the lanes (on
 // small meshes, where a launch is latency, few are enough) and a workgroup's
-// PE-face records leave room for three workgroups in the 160 KB of LDS.
+// values at PE faces leave room for five workgroups in the 160 KB of LDS: below
+// 32 KB, and with room for three, below 48, us per step at 2^22 elements, linear
+// form PE 2 89, 133, PE 4 59, 72, PE 8 39, 48; central 97, 149, 66, 79, 51, 61;
+// Burgers, SSP-RK3, p = 2 70, 86, 48, 50, 34, 39; local DG, Heun, p = 2 63, 79, 43, 46,
+// 31, 34; dJ/du0 alone, a run and its adjoint, 2^20 103, 129, 58, 63, 37, 39, but 2^16
+// 26.0, 23.5, 14.0, 12.1.
 // Measured, us per step, PE 256, p = 3, RK4 unless stated (R and K in brackets):
-//   linear form   2^14 elements (1,8) 1.58, (2,8) 1.68, (4,8) 2.04; 2^16 1.82,
-//                 1.74, 2.08; 2^18 3.13, 2.54, 2.68; 2^19 4.80, 3.54, 3.46; 2^20
-//                 7.55, 5.67, 5.19; (1,4) 3.32 at 2^18, 6.99 at 2^20; (4,2) 10.1,
-//                 (4,4) 7.0 at 2^20; 2^22, PE 4 (4,2) 135 (below 32 KB of LDS),
-//                 (4,4) 88 (below 48 KB)
+//   linear form   2^14 elements (1,8) 1.35, (2,8) 1.50, (4,8) 1.87; 2^16 1.53,
+//                 1.51, 1.90; 2^18 2.74, 2.25, 2.45; 2^19 (1,4) 4.38, (2,8) 3.38,
+//                 (4,8) 3.19; 2^20 6.75, 5.22, 4.76, (4,2) 9.96
 //   a > 0, stage  64 elements, p = 2 (1,8) 1.57, (2,8) 2.19, (4,8) 3.45; recorded
 //                 2^20 (128 steps and their adjoint, ms) (2,4) 6.32, (2,8) 6.18,
 //                 (4,4) 6.30, (4,8) 5.95
@@ -481,7 +489,7 @@ int lds_of(const adg_problem& p, int elems, int K) {
 //                 (1,4) 2.25, (1,8) 2.14; 2^18 (2,4) 4.81, (2,8) 5.07; 2^20 (4,4)
 //                 11.75, (4,8) 11.96; RK4, p = 3 2^14 (1,4) 2.63, (2,8) 2.87; 2^20
 //                 (4,4) 17.8, (4,8) 18.7
-constexpr int kFaceLdsBytes = 48 * 1024;
+constexpr int kFaceLdsBytes = 32 * 1024;
 Shape shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, int64_t n_rec) {
   const int kern = kernel_of(probs, opt);
   Shape s{std::max(1, lane_elems_of(probs, n, opt)), kern == ADG_KERNEL_FUSED ? std::max(1, fused_steps_of(opt)) : 1};
@@ -612,11 +620,12 @@ Shape adj_shape_of(const adg_problem* probs, int32_t n, const adg_options* opt, 
   }
   const bool small = elems <= (int64_t)1 << 17;
   const int most_halo = nl ? (small ? 13 : 10) : (small ? 20 : 12);
+  const int most_lds = small && list == ADJ_LINEAR ? 48 * 1024 : kFaceLdsBytes;
   auto fits = [&](int K) {
     if (adj_halo(rk, nl, s.elems, K) > most_halo) return false;
     for (int32_t i = 0; i < n; ++i) {
       const int faces = async_of(probs[i]) ? fused_faces(s.elems, probs[i].pe_size) : 0;
-      if (8 * kWavesPerBlock * adj_lds_words(rk_stages(rk), s.elems, K, faces, list == ADJ_FWD, false) > kFaceLdsBytes)
+      if (8 * kWavesPerBlock * adj_lds_words(rk_stages(rk), s.elems, K, faces, list == ADJ_FWD, false) > most_lds)
         return false;
     }
     return true;
