@@ -127,14 +127,15 @@ typedef struct adg_options {
                                   straight into its slot, and the adjoint recomputes nothing) */
   int32_t kernel;              /* adg_kernel; AUTO -> FUSED */
   int32_t lane_elems;          /* fused kernel: consecutive elements per lane, 1, 2 or 4 (<= every
-                                  asynchronous problem's pe_size); 0 -> the library's choice (by the
-                                  form and the total size; viscous Burgers: 2, or 1 for a PE size of 1).
-                                  Where it does not divide every PE size, half of it, until it does */
+                                  asynchronous problem's pe_size); 0 -> the library's choice, by the
+                                  form and the total size.  Where it does not divide every PE size, two
+                                  (general flux, Burgers, viscous Burgers) or half of it, until it does
+                                  (upwind advection with a > 0); at most two in launches of one step */
   uint32_t flags;              /* ADG_OPT_* bits, 0 = defaults */
-  uint32_t fused_steps;        /* fused kernel: time steps per launch, 1 or 2 (halo of 2S elements per side,
-                                  half the state traffic per step); 0 -> the library's choice, up to 8 by
-                                  the sizes (viscous Burgers: 2).  Every (lane_elems, fused_steps) pair gives
-                                  bitwise the same results. */
+  uint32_t fused_steps;        /* fused kernel: time steps per forward launch at most, 1 or 2; 0 -> the
+                                  library's choice, up to 8 by the sizes.  adg_launch_shape tells the shape
+                                  that runs.  Every (lane_elems, fused_steps) pair gives bitwise the same
+                                  results. */
 } adg_options;
 
 /* adg_options.flags.  ADG_OPT_PE_SPLIT_ON / OFF chose between two forms of the
@@ -186,8 +187,8 @@ int adg_state_layout(const adg_problem* probs, int32_t n_probs, int64_t* offsets
 
 /* Device workspace bytes needed by adg_init for these problems, options and
  * an adjoint recording horizon of n_steps_record steps (0 if adg_adjoint
- * is not used): descriptors, work lists, the per-PE-boundary rings of past
- * face fluxes (depth L + q levels, Secs. 3, 5), the fused kernel's second
+ * is not used): descriptors, work lists, the rings of past PE-face fluxes
+ * (L + q levels and, for K steps per launch, K - 2 more, Secs. 3, 5), the fused kernel's second
  * state, and with a horizon the checkpoints.  Host-only; ADG_E_INVALID for
  * invalid problems or options. */
 int adg_workspace_size(const adg_problem* probs, int32_t n_probs, const adg_options* opt,
@@ -265,7 +266,10 @@ int adg_step(adg_ctx* ctx, double* d_u);
  * for this d_u on first use; with n_steps = 0 the graph is only captured, so
  * that a later timed run replays it without capture cost), ADG_RUN_RECORD
  * (the context must be at step 0 and n_steps <= the recording horizon given
- * to adg_init), ADG_RUN_CHECK_FINITE.  Errors: ADG_E_INVALID (null or
+ * to adg_init; the states are bitwise those of an unrecorded run in a context with
+ * the same horizon, and for upwind advection with a > 0 on 1024 elements or more
+ * those of a context without a horizon to rounding, bitwise for everything else),
+ * ADG_RUN_CHECK_FINITE.  Errors: ADG_E_INVALID (null or
  * misaligned d_u, n_steps < 0, step index past 2^31 - 1, unknown flags),
  * ADG_E_STATE (recording misuse), ADG_E_HIP, ADG_E_NONFINITE. */
 int adg_run(adg_ctx* ctx, double* d_u, int64_t n_steps, uint32_t flags);

@@ -408,15 +408,11 @@ int kernel_of(const adg_problem*, const adg_options* opt) {
 
 bool is_ldg(const adg_problem* probs) { return probs[0].equation == ADG_EQ_VISCOUS_BURGERS; }
 
-// PE-face split of the fused kernel (fused_mode): tile waves with every
-// PE-face path compiled out and window waves centred on the PE faces, in one
-// launch.  Every asynchronous problem's PE size must hold one window of the
-// longest launch (one face per window).  By default the split is used only
-// where a wave holds at least two windows and every PE size holds four: the
-// windows' extra work then stays below what the lighter tile waves save
-// (measured on 2^20 and 2^24 elements: 10-11 % faster per step at PE size
-// 256 with RK4 and two steps per launch, 7 % slower at PE size 64, and
-// slower for the five-stage scheme, whose 40-element window fills a wave).
+// Whether the workspace holds room for window lists around the PE faces: what
+// ADG_OPT_PE_SPLIT_ON and OFF still decide.  No kernel reads it: the fused kernel
+// keeps waves with and without PE faces apart by itself.  By default where every
+// asynchronous problem's PE size holds four windows of the longest launch of one or
+// two steps and a wave two.
 bool pe_split_of(const adg_problem* probs, int32_t n, const adg_options* opt) {
   const uint32_t f = opt ? opt->flags : 0u;
   if ((f & (ADG_OPT_PE_SPLIT_OFF | ADG_OPT_ONE_LAUNCH)) || kernel_of(probs, opt) != ADG_KERNEL_FUSED || is_ldg(probs))

@@ -100,8 +100,10 @@ __host__ __device__ constexpr int fused_lds_words(int S, int K, int n_faces, int
 template <int S>
 void launch_lin_s(const StepArgs& a, int gi, const double* uin, double* uout, int32_t step_offset, hipStream_t stream);
 
-// Windows of 4 K S elements around a PE face and how many fit a wave: sizes of
-// the room that the workspace keeps for ADG_OPT_PE_SPLIT_ON.
+// Windows of 4 K S elements around a PE face and how many fit a wave: they size
+// the room that the workspace holds with ADG_OPT_PE_SPLIT_ON, or by default on
+// large PEs (part of the interface's documented effect of the flags; no kernel
+// reads it).
 __host__ __device__ constexpr int fused_window(int rk, int K) { return 4 * K * rk_stages(rk); }
 __host__ __device__ constexpr int fused_windows_per_wave(int rk, int K) { return kWave / fused_window(rk, K); }
 

@@ -15,7 +15,7 @@ namespace adg {
 // lane's first left face, received by a lane shift.  No workgroup barrier: the
 // waves of a workgroup are independent.  PE faces as in WaveFaces.
 //
-// The kernel is bound by FP64 issue (p = 3, RK4, a > 0: 116 operations per
+// The kernel is bound by FP64 issue (p = 3, RK4, a > 0: 112 operations per
 // element and step), so what it spends beside them counts: the operator sits
 // in one or two register pairs and is read by DPP row broadcasts (as scalars
 // loaded inside the stages it cost a wait per stage), and waves with and
