@@ -73,11 +73,18 @@ struct WaveElems {
                                                  (int)(8 * j * ld), 0);
         }
     } else {
+      // the elements from the first one: kept from the load they are R - 1
+      // registers through every step (p = 4, RK4, four elements per lane, linear
+      // form: 132 registers, three waves per SIMD, and 128, four)
+      int x = e[0];
+      asm volatile("" : "+v"(x));
 #pragma unroll
-      for (int r = 0; r < R; ++r)
+      for (int r = 0; r < R; ++r) {
         if (r < own_n)
 #pragma unroll
-          for (int j = 0; j < NP; ++j) p[j * ld + e[r]] = u[r][j];
+          for (int j = 0; j < NP; ++j) p[j * ld + x] = u[r][j];
+        x = x + 1 == (int)P.n_elem ? 0 : x + 1;
+      }
     }
   }
 };
