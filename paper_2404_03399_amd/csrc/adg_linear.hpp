@@ -28,6 +28,11 @@ namespace adg {
 // as at 0.001.  With the fluxes added to u one by one, or coefficients on the
 // nodes' own values, it was 1.7 to 6.
 //
+// Bound by VALU issue: at p = 3, RK4, PE 256, 2^24 elements, four per lane and eight
+// steps, 2945 instructions per wave, 63 % of them FP64, and a quarter of the wave
+// cycles waiting.  us per step, this form and stage by stage: 2^20 elements 4.79,
+// 6.55; 2^24 53.9, 84.2.
+//
 // At a PE face the raw flux G_s of the element on the left is replaced by the
 // AT combination of delayed levels (WaveFaces) where the drawn delay is not 0;
 // the element left of the face then takes the difference delta_s between
@@ -166,7 +171,7 @@ __device__ __forceinline__ void lin_tile(const DevProblem& P, const double* __re
     }
   };
   // one loop after the other, of which one takes all steps: as the two sides of
-  // a branch the compiler keeps the state twice (137 registers instead of 103)
+  // a branch the compiler keeps the state twice (144 registers instead of 112)
   steps(std::true_type{}, wf.m_pe ? K : 0);
   steps(std::false_type{}, K);
 

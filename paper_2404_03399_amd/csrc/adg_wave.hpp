@@ -207,8 +207,7 @@ struct WaveFaces {
 
   // This lane's face in step kk: where its AT sums stand and its raw fluxes go
   // (lanes without a face have a place of their own, so that no branch cuts the
-  // stages into blocks: with one the linear form took 167 registers instead of
-  // 137), and its delays (0 without a face).
+  // stages into blocks), and its delays (0 without a face).
   __device__ __forceinline__ double* sums(int K, int kk, int v = 0) const {
     return at + v * vstride + ((pe ? slot : n_faces_max) * K + (pe ? kk : 0)) * S;
   }
