@@ -80,8 +80,8 @@ def split_possible(workloads, k: int) -> bool:
 
 
 def configs(workloads) -> List[Tuple[int, int, Optional[bool]]]:
-    """Candidate (R, K, split): split None where the PE-face split does not
-    apply (the library then has nothing to choose)."""
+    """The (R, K, split) that options can ask for: split None where the PE-face
+    split's flags do not apply.  `tune` times `timed_configs`."""
     out = []
     for r in admissible(workloads):
         for k in STEPS_PER_LAUNCH:
